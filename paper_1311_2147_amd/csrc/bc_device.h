@@ -63,13 +63,10 @@ struct GraphCtl {
     unsigned long long changed_total;
     unsigned long long scan_bytes_last;  // row-scan bytes of the last update (see k_commit)
     unsigned long long scan_bytes_total;
-    alignas(256) int32_t work_next;    // next item of the persistent per-source kernel
+    alignas(256) int32_t work_next;    // items handed out by atomic (static pass; rows past the first per workgroup)
     alignas(256) int32_t dag_count;    // listed sources with many changed targets: dlist[0 .. dag_count)
     alignas(256) int32_t dag_back;     // listed sources with few: dlist[n - dag_back .. n)
-    alignas(256) int32_t dag_next;     // next listed source with many changed targets (DAG kernel)
-    alignas(256) int32_t dag_next_light;  // next listed source with few
     alignas(256) int32_t big_count;    // deferred (large) sources of the update in flight
-    alignas(256) int32_t big_next;     // next deferred source to process
     alignas(256) unsigned long long changed_pairs;  // statistic of the last update
 };
 
@@ -92,12 +89,16 @@ struct DItem {
 };
 
 // Target pool of one update step: the changed targets (with their new d and
-// sigma) of every listed source of every job, bump-allocated.
+// sigma) of every listed source of every job, bump-allocated.  The work
+// counters of the step's DAG and wide kernels sit beside its allocator, each
+// on a 256-byte line of its own.
 struct StepPool {
     int32_t *t;
     int32_t *d;
     uint64_t *s;
     unsigned long long *next;
+    int32_t *src_next;   // listed sources handed out past the first per workgroup
+    int32_t *wide_next;  // units of the wide kernel handed out past the first per workgroup
     int64_t cap;
 };
 

@@ -305,6 +305,8 @@ StepPool step_pool(bc_ctx *ctx) {
     p.d = p.t + p.cap;
     p.s = (uint64_t *)(p.d + p.cap);
     p.next = (unsigned long long *)(misc_dev(ctx) + 2048);
+    p.src_next = (int32_t *)(misc_dev(ctx) + 2304);
+    p.wide_next = (int32_t *)(misc_dev(ctx) + 2560);
     return p;
 }
 int wide_slots_for(int slots) { return std::min(slots, WIDE_SLOTS_MAX); }
@@ -539,7 +541,7 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part)
         HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
         hipLaunchKernelGGL(k_source_wide, dim3(L.wide_slots), dim3(ctx->wide_block),
                            source_lds_bytes(L.wide_lds_cap, ctx->wide_block, 0), st, jobs, nj, L.wide_base,
-                           L.wide_bytes, L.wide_lds_cap, L.n_layout, L.items_base, L.item_regions);
+                           L.wide_bytes, L.wide_lds_cap, L.n_layout, L.items_base, L.item_regions, pool);
         const size_t lds = source_lds_bytes(L.src_lds_cap, ctx->block, ctx->table);
         if (ctx->table == 128)
             hipLaunchKernelGGL(k_source<128>, dim3(L.slots), dim3(ctx->block), lds, ctx->side, jobs, nj, L.src_base,

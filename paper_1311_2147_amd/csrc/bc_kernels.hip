@@ -630,7 +630,8 @@ __global__ void __launch_bounds__(256) k_es_place(const UpdateJob *__restrict__ 
 
 struct BlockShared {
     int32_t head, tail, next, nlev;
-    int32_t item;
+    int32_t item, seg, source, role;
+    int32_t wl_total, wl_seg, wl_lo, wl_hi, wl_first;  // WorkList
     int32_t nb, nf;
     int32_t ovf, progress;
     int32_t nk, kpos;
@@ -2363,7 +2364,7 @@ __device__ __forceinline__ RowV row_v_of(const UpdateJob &J) {
 // straight from the lanes; the listing rules are those of k_rows, with the
 // pool and list reservations of a wave's rows taken in one atomic each.
 __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_t count, const int32_t t_count,
-                                 const int32_t cap, const StepPool &pool) {
+                                 const int32_t cap, const StepPool &pool, const int32_t turn) {
     GraphCtl *ctl = J.g.ctl;
     const int32_t n = J.g.n;
     const int lane = lane_id();
@@ -2381,10 +2382,10 @@ __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_
     const int32_t rvvd = has_t && R.has_out ? R.rvvD[t] : INF32;
     bool ovf_s = false, ovf_d = false;
     int32_t listed_pairs = 0;
+    // the wave's first rows by its turn, the others from the counter (see k_rows)
+    const int32_t wpb = (int32_t)blockDim.x >> 6, dealt = (int32_t)gridDim.x * wpb * rpw;
+    int32_t base = (turn * wpb + ((int32_t)threadIdx.x >> 6)) * rpw;
     for (;;) {
-        int32_t base = 0;
-        if (lane == 0) base = atomicAdd(&ctl->work_next, rpw);
-        base = __shfl(base, 0, 64);
         if (base >= count) break;
         const int32_t item = base + g;
         const bool row_ok = item < count;
@@ -2459,6 +2460,9 @@ __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_
             pool.d[p] = d;
             pool.s[p] = sg;
         }
+        if (count <= dealt) break;
+        if (lane == 0) base = dealt + atomicAdd(&ctl->work_next, rpw);
+        base = __shfl(base, 0, 64);
     }
     if (ovf_s) atomicOr(&ctl->status, ST_SIGMA_OVF);
     if (ovf_d) atomicOr(&ctl->status, ST_DIST_OVF);
@@ -2468,8 +2472,13 @@ __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_
     if (lane == 0 && listed_pairs) atomicAdd(&ctl->changed_pairs, (unsigned long long)listed_pairs);
 }
 
-// Row kernel (persistent): workgroups pull affected sources from a device
-// counter and scan their rows (scan_row).  A source's changed targets are
+// Row kernel (persistent): each workgroup's first affected source of a job is
+// its turn in a deal over the grid (the deal goes on from job to job), the
+// others come from a device counter; it scans their rows (scan_row).  With
+// the first one dealt, a job with no more sources than workgroups makes no
+// claim at all: 1024 workgroups' claims on one counter are serialized where
+// it lives (with WorkList in the other two kernels, 16 updates of a 64-vertex
+// graph went from 2.12 to 1.61 ms, 64 of an n = 4096 one from 15.4 to 13.5).  A source's changed targets are
 // collected in LDS; up to big_b of them are copied to the step's target pool
 // and the source is listed for the DAG kernel, more (or a full pool) defer
 // the source to the wide kernel, which scans the row again.  Nothing in D or
@@ -2483,26 +2492,33 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
     const int tid = threadIdx.x, bs = blockDim.x;
     const int njobs = *njobs_p;
     const BList L{lt, ld, ls, min(big_b, LCAP)};
+    const int32_t grid = (int32_t)gridDim.x;
+    int32_t dealt = 0;  // sources dealt by the jobs before this one, modulo the grid
     for (int j = 0; j < njobs; ++j) {
         const UpdateJob &J = jobs[j];
         if (job_halted(J)) continue;
         GraphCtl *ctl = J.g.ctl;
         const int32_t n = J.g.n;
         const int32_t count = *(volatile int32_t *)&ctl->a_count;
+        int32_t turn = (int32_t)blockIdx.x - dealt;
+        if (turn < 0) turn += grid;
         const RowV R = row_v_of(J);
         const int32_t t_count = *(volatile int32_t *)&ctl->t_count;
         const bool use_tlist = (int64_t)t_count * 8 <= (int64_t)n;
         if (use_tlist && t_count <= 64) {
             // a row without candidates cannot change
-            if (t_count > 0) rows_few_targets(J, R, count, t_count, L.cap, pool);
+            if (t_count > 0) rows_few_targets(J, R, count, t_count, L.cap, pool, turn);
             continue;
         }
+        dealt = (int32_t)(((int64_t)dealt + min(count, grid)) % grid);
+        if (turn >= count) continue;
         if (tid == 0) sh.counter = 0;
         bool ovf_s = false, ovf_d = false;
-        for (;;) {
+        for (bool first = true;; first = false) {
+            if (!first && count <= grid) break;
             __syncthreads();
             if (tid == 0) {
-                sh.item = atomicAdd(&ctl->work_next, 1);
+                sh.item = first ? turn : grid + atomicAdd(&ctl->work_next, 1);
                 sh.nb = 0;
                 sh.nf = 0;
             }
@@ -2637,8 +2653,92 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     if (!preds_done && !edge) refresh_preds<4>(Drow, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, pred_row, sh, es);
 }
 
-// DAG kernel (persistent): workgroups pull the sources the row kernel listed
-// and run update_source on each.  The row is staged in LDS when n <= lds_cap
+// The sources of a step's segments (one list per job, or two), numbered
+// through in segment order and shared out over the persistent workgroups in
+// units: the first max_pairs sources are two units each, the others one.
+// Workgroup b takes unit b first and then units past the grid from a device
+// counter, and makes no claim where there are no more units than workgroups.
+// Claims on one counter are serialized where it lives, and 2560 workgroups with
+// a claim per list took 48 us in a 64-vertex update (see k_rows).  Wave 0 keeps the segment of its last source and looks 64 segments
+// up at a time when it moves on; it alone reads the halted flags, so that a
+// job halted in between stops whole workgroups.
+// Its state is in LDS (the DAG kernel has no register to spare for it).
+template <typename F, typename H>
+struct WorkList {
+    const int32_t segs, max_pairs;
+    int32_t *const counter;
+    const F count;
+    const H halted;
+    BlockShared &sh;
+    __device__ __forceinline__ WorkList(const int32_t nseg, const int32_t pairs, int32_t *next_unit, const F &f,
+                                        const H &h, BlockShared &s)
+        : segs(nseg), max_pairs(pairs), counter(next_unit), count(f), halted(h), sh(s) {
+        if (threadIdx.x >= 64) return;
+        int32_t total = 0;
+        for (int32_t q = lane_id(); q < segs; q += 64) total += count(q);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o, 64);
+        if (lane_id() == 0) {
+            sh.wl_total = total;
+            sh.wl_seg = -1;
+            sh.wl_lo = sh.wl_hi = 0;
+            sh.wl_first = 1;
+        }
+    }
+    // The workgroup's next unit: sh.seg, sh.item (its source's place in the
+    // segment), sh.source (its number) and sh.role (0 and 1 of a pair, else
+    // 2); false when all are taken.  Every thread of the workgroup calls it.
+    __device__ __forceinline__ bool next() {
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            const int32_t total = sh.wl_total, pairs = min(max_pairs, total), units = total + pairs;
+            const int32_t grid = (int32_t)gridDim.x;
+            int32_t seg = sh.wl_seg, lo = sh.wl_lo, hi = sh.wl_hi, unit, src = -1;
+            bool first = sh.wl_first != 0;
+            do {
+                unit = first ? (int32_t)blockIdx.x : units;
+                if (!first && units > grid) {
+                    if (lane_id() == 0) unit = grid + atomicAdd(counter, 1);
+                    unit = __shfl(unit, 0, 64);
+                }
+                first = false;
+                if (unit >= units) break;
+                src = unit < 2 * pairs ? unit >> 1 : unit - pairs;
+                while (src >= hi) {
+                    const int32_t q = seg + 1 + lane_id();
+                    const int32_t c = q < segs ? count(q) : 0;
+                    int32_t incl = c;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const int32_t v = __shfl_up(incl, o, 64);
+                        if (lane_id() >= o) incl += v;
+                    }
+                    const uint64_t past = __ballot(hi + incl > src);
+                    const int at = past ? __ffsll((unsigned long long)past) - 1 : 63;
+                    const int32_t end = hi + __shfl(incl, at, 64), mine = __shfl(c, at, 64);
+                    seg += 1 + at;
+                    lo = end - mine;
+                    hi = end;
+                }
+            } while (halted(seg));
+            if (lane_id() == 0) {
+                sh.item = unit < units ? src - lo : -1;
+                sh.seg = seg;
+                sh.source = src;
+                sh.role = unit < 2 * pairs ? (unit & 1) : 2;
+                sh.wl_seg = seg;
+                sh.wl_lo = lo;
+                sh.wl_hi = hi;
+                sh.wl_first = 0;
+            }
+        }
+        __syncthreads();
+        return sh.item >= 0;
+    }
+};
+
+// DAG kernel (persistent): workgroups take the sources the row kernel listed
+// (WorkList) and run update_source on each.  The row is staged in LDS when n <= lds_cap
 // (dynamic LDS of 4*lds_cap bytes).  Every workgroup's slot is laid out for
 // the context-wide n_layout (the largest graph), so the zero-kept arrays sit
 // at the same place for every job.  The work is bound by dependent gathers, so
@@ -2661,30 +2761,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))
     // the heavy sources of every job first (the front of each job's list),
     // then the light ones (the back): a step's long sub-DAG passes start
     // early whatever job they belong to, and the light sources fill the tail
-    for (int phase = 0; phase < 2; ++phase)
-    for (int j = 0; j < njobs; ++j) {
-        const UpdateJob &J = jobs[j];
-        if (job_halted(J)) continue;
-        GraphCtl *ctl = J.g.ctl;
+    auto seg_count = [&](const int32_t q) {
+        const GraphCtl *c = jobs[q < njobs ? q : q - njobs].g.ctl;
+        return q < njobs ? *(const volatile int32_t *)&c->dag_count : *(const volatile int32_t *)&c->dag_back;
+    };
+    auto seg_halted = [&](const int32_t q) { return job_halted(jobs[q < njobs ? q : q - njobs]); };
+    WorkList wl(2 * njobs, 0, pool.src_next, seg_count, seg_halted, sh);
+    while (wl.next()) {
+        const int32_t seg = sh.seg, item = sh.item;
+        const UpdateJob &J = jobs[seg < njobs ? seg : seg - njobs];
         const int32_t n = J.g.n;
         const bool lds = n <= lds_cap;
-        const int32_t count = phase == 0 ? *(volatile int32_t *)&ctl->dag_count : *(volatile int32_t *)&ctl->dag_back;
-        int32_t *const next = phase == 0 ? &ctl->dag_next : &ctl->dag_next_light;
-        for (;;) {
+        const DItem it = J.g.dlist[seg < njobs ? item : n - 1 - item];
+        if (lds) {
+            const int32_t *Dg = J.g.D + (size_t)it.s * n;
+            for (int32_t t = tid; t < n; t += bs) lds_row[t] = Dg[t];
             __syncthreads();
-            if (tid == 0) sh.item = atomicAdd(next, 1);
-            __syncthreads();
-            const int32_t item = sh.item;
-            if (item >= count) break;
-            const DItem it = J.g.dlist[phase == 0 ? item : n - 1 - item];
-            if (lds) {
-                const int32_t *Dg = J.g.D + (size_t)it.s * n;
-                for (int32_t t = tid; t < n; t += bs) lds_row[t] = Dg[t];
-                __syncthreads();
-            }
-            update_source<TS>(J, it.s, pool.t + it.off, pool.d + it.off, pool.s + it.off, it.nb, lds, lds_row, u, sh, es,
-                          sd, dd);
         }
+        update_source<TS>(J, it.s, pool.t + it.off, pool.d + it.off, pool.s + it.off, it.nb, lds, lds_row, u, sh, es,
+                          sd, dd);
     }
 }
 
@@ -2715,7 +2810,7 @@ __device__ __forceinline__ void copy_row(T *dst, const T *__restrict__ src, cons
 __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restrict__ jobs,
                                                       const int32_t *__restrict__ njobs_p, char *__restrict__ scratch,
                                                       size_t slot_bytes, int32_t lds_cap, int32_t n_layout,
-                                                      char *__restrict__ items, int32_t item_regions) {
+                                                      char *__restrict__ items, int32_t item_regions, StepPool pool) {
     extern __shared__ __align__(16) char dyn_lds[];
     int32_t *const lds_row = (int32_t *)dyn_lds;
     const ExpandShared es = expand_at(dyn_lds, lds_cap);
@@ -2724,133 +2819,118 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
     const int njobs = *njobs_p;
     const USlot u = wslot_at(scratch + (size_t)blockIdx.x * slot_bytes, n_layout);
     const size_t region_bytes = item_region_bytes(n_layout);
-    int32_t region0 = 0;  // first item region of the job
-    for (int j = 0; j < njobs; ++j) {
-        const UpdateJob &J = jobs[j];
+    // the deferred sources of the jobs in order; source k of the first
+    // item_regions has item region k (k_wide_apply counts them the same way)
+    auto seg_count = [&](const int32_t q) { return *(const volatile int32_t *)&jobs[q].g.ctl->big_count; };
+    auto seg_halted = [&](const int32_t q) { return job_halted(jobs[q]); };
+    WorkList wl(njobs, item_regions, pool.wide_next, seg_count, seg_halted, sh);
+    while (wl.next()) {
+        const UpdateJob &J = jobs[sh.seg];
         GraphCtl *ctl = J.g.ctl;
         const int32_t n = J.g.n;
         const bool lds = n <= lds_cap;
-        // the item regions of a job follow those of the jobs before it, halted
-        // or not (k_wide_apply counts them the same way)
-        const int32_t count = *(volatile int32_t *)&ctl->big_count;
-        const int32_t paired = min(count, item_regions - region0);
-        if (job_halted(J)) {
-            region0 += paired;
-            continue;
-        }
-        const int32_t units = 2 * paired + (count - paired);
         const RowV R = row_v_of(J);
         const int32_t t_count = *(volatile int32_t *)&ctl->t_count;
         const bool use_tlist = (int64_t)t_count * 8 <= (int64_t)n;
         const BList L{u.bl_t, u.bl_d, u.bl_s, n};
         const bool edge = one_arc_job(J);
-        if (tid == 0) sh.counter = 0;
         bool ovf_s = false, ovf_d = false;
-        for (;;) {
-            __syncthreads();
-            if (tid == 0) {
-                sh.item = atomicAdd(&ctl->big_next, 1);
-                sh.nb = 0;
-                sh.nf = 0;
-            }
-            __syncthreads();
-            const int32_t unit = sh.item;
-            if (unit >= units) break;
-            // role 0: old pass, 1: new pass, 2: the whole update of the source
-            const int32_t item = unit < 2 * paired ? unit >> 1 : paired + (unit - 2 * paired);
-            const int role = unit < 2 * paired ? (unit & 1) : 2;
-            const int32_t s = J.g.biglist[item];
-            const SrcScal sc = J.g.scal[s];
-            int32_t *const pred_row = J.g.pred + (size_t)s * n;
-            const int32_t *Dg = J.g.D + (size_t)s * n;
-            const uint64_t *Sg = J.g.S + (size_t)s * n;
-            if (lds) {
-                copy_row<4>(lds_row, Dg, n);
-                __syncthreads();
-            }
-            scan_row<4>(J, R, sc, (sc.flags & 1) != 0, lds ? lds_row : Dg, Sg, use_tlist, t_count, u.q1, n, L, sh,
-                        ovf_s, ovf_d);
-            __syncthreads();
-            const int32_t nb = sh.nb;
-            if (role == 0) {
-                const ItemRegion ir = item_region_at(items + (size_t)(region0 + item) * region_bytes, n_layout);
-                for (int32_t i = tid; i < nb; i += bs) {
-                    ir.t[i] = u.bl_t[i];
-                    ir.d[i] = u.bl_d[i];
-                    ir.s[i] = u.bl_s[i];
-                }
-                if (tid == 0) *ir.nb = nb;
-            }
-            if (nb == 0) continue;
-            if (role != 1 && tid == 0) sh.counter += (unsigned long long)nb;
-            // a B of half the row or more makes the sub-DAG most of DAG(s):
-            // take every vertex's DAG in-arcs instead of walking back from B.
-            // Below that the walk is cheaper: a hub update's changed targets
-            // hang mostly below the hub, so their new ancestors are little
-            // more than B itself (a hub update with 19 000 deferred sources
-            // took 80 ms this way, 127 ms with whole-DAG passes from 1/16)
-            const bool full = (int64_t)nb * 2 >= (int64_t)n;
-            bool preds_done = false;
-            // phase 0: old pass (roles 0 and 2); phase 1: new pass (roles 1 and 2)
-            for (int ph = role == 1 ? 1 : 0; ph <= (role == 0 ? 0 : 1); ++ph) {
-                const int32_t *Dr = lds ? lds_row : Dg;
-                const uint64_t *Sr = Sg;
-                if (ph == 1) {
-                    if (role == 1) {
-                        // the new row and counts: the old ones with the changed pairs in
-                        int32_t *Dn = lds ? lds_row : u.dnew;
-                        if (!lds)
-                            for (int32_t t = tid; t < n; t += bs) u.dnew[t] = Dg[t];
-                        for (int32_t t = tid; t < n; t += bs) u.snew[t] = Sg[t];
-                        __syncthreads();
-                        for (int32_t i = tid; i < nb; i += bs) {
-                            const int32_t t = u.bl_t[i];
-                            if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], u.bl_d[i] < Dn[t]);
-                            Dn[t] = u.bl_d[i];
-                            u.snew[t] = u.bl_s[i];
-                        }
-                        Dr = Dn;
-                        Sr = u.snew;
-                    } else {
-                        int32_t *Dw = J.g.D + (size_t)s * n;
-                        uint64_t *Sw = J.g.S + (size_t)s * n;
-                        for (int32_t i = tid; i < nb; i += bs) {
-                            const int32_t t = u.bl_t[i];
-                            const int32_t d = u.bl_d[i];
-                            if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], d < (lds ? lds_row[t] : Dw[t]));
-                            Sw[t] = u.bl_s[i];
-                            Dw[t] = d;
-                            if (lds) lds_row[t] = d;
-                        }
-                    }
-                    __syncthreads();
-                }
-                // The old pass of a paired source tests its B vertices' E*
-                // in-arcs, so it never uses a stored predecessor that its new
-                // pass (another workgroup, at the same time) rewrites: its walk
-                // may load one ahead, but stops at the B vertex, which is in the
-                // sub-DAG from the start.  A source updated by one workgroup
-                // rewrites its predecessors only after the old pass, so that
-                // pass takes the B vertices' stored (old) predecessors.  The new
-                // pass of a one-arc update takes theirs from Alg 2 (written
-                // above); other updates test the B vertices' E* in-arcs and
-                // write the predecessors from the arc record
-                preds_done = restricted_pass<false, 2, 4>(
-                    s, n, Dr, Sr, ph ? J.g.yc_ptr : J.g.xc_ptr, ph ? J.g.yc_src : J.g.xc_src,
-                    ph ? J.g.yc_dst : J.g.xc_dst, ph ? J.g.yc_w : J.g.xc_w, u.bl_t, nb, full, u, ph ? 1.0 : -1.0,
-                    J.g.bc_delta, pred_row, ph && !edge ? pred_row : nullptr, ph ? edge : role == 2, sh, es);
-            }
-            // the new row of the new pass: in LDS, in the slot (role 1 without
-            // staging) or written back to D (role 2)
-            if (role != 0 && !preds_done && !edge)
-                refresh_preds<1>(lds ? lds_row : role == 1 ? u.dnew : Dg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, u.bl_t, nb,
-                                 pred_row, sh, es);
+        if (tid == 0) {
+            sh.nb = 0;
+            sh.nf = 0;
         }
+        // role 0: old pass, 1: new pass, 2: the whole update of the source
+        const int role = sh.role;
+        const int32_t region = sh.source;
+        const int32_t s = J.g.biglist[sh.item];
+        const SrcScal sc = J.g.scal[s];
+        int32_t *const pred_row = J.g.pred + (size_t)s * n;
+        const int32_t *Dg = J.g.D + (size_t)s * n;
+        const uint64_t *Sg = J.g.S + (size_t)s * n;
+        __syncthreads();
+        if (lds) {
+            copy_row<4>(lds_row, Dg, n);
+            __syncthreads();
+        }
+        scan_row<4>(J, R, sc, (sc.flags & 1) != 0, lds ? lds_row : Dg, Sg, use_tlist, t_count, u.q1, n, L, sh,
+                    ovf_s, ovf_d);
         if (ovf_s) atomicOr(&ctl->status, ST_SIGMA_OVF);
         if (ovf_d) atomicOr(&ctl->status, ST_DIST_OVF);
         __syncthreads();
-        if (tid == 0 && sh.counter) atomicAdd(&ctl->changed_pairs, sh.counter);
-        region0 += paired;
+        const int32_t nb = sh.nb;
+        if (role == 0) {
+            const ItemRegion ir = item_region_at(items + (size_t)region * region_bytes, n_layout);
+            for (int32_t i = tid; i < nb; i += bs) {
+                ir.t[i] = u.bl_t[i];
+                ir.d[i] = u.bl_d[i];
+                ir.s[i] = u.bl_s[i];
+            }
+            if (tid == 0) *ir.nb = nb;
+        }
+        if (nb == 0) continue;
+        if (role != 1 && tid == 0) atomicAdd(&ctl->changed_pairs, (unsigned long long)nb);
+        // a B of half the row or more makes the sub-DAG most of DAG(s):
+        // take every vertex's DAG in-arcs instead of walking back from B.
+        // Below that the walk is cheaper: a hub update's changed targets
+        // hang mostly below the hub, so their new ancestors are little
+        // more than B itself (a hub update with 19 000 deferred sources
+        // took 80 ms this way, 127 ms with whole-DAG passes from 1/16)
+        const bool full = (int64_t)nb * 2 >= (int64_t)n;
+        bool preds_done = false;
+        // phase 0: old pass (roles 0 and 2); phase 1: new pass (roles 1 and 2)
+        for (int ph = role == 1 ? 1 : 0; ph <= (role == 0 ? 0 : 1); ++ph) {
+            const int32_t *Dr = lds ? lds_row : Dg;
+            const uint64_t *Sr = Sg;
+            if (ph == 1) {
+                if (role == 1) {
+                    // the new row and counts: the old ones with the changed pairs in
+                    int32_t *Dn = lds ? lds_row : u.dnew;
+                    if (!lds)
+                        for (int32_t t = tid; t < n; t += bs) u.dnew[t] = Dg[t];
+                    for (int32_t t = tid; t < n; t += bs) u.snew[t] = Sg[t];
+                    __syncthreads();
+                    for (int32_t i = tid; i < nb; i += bs) {
+                        const int32_t t = u.bl_t[i];
+                        if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], u.bl_d[i] < Dn[t]);
+                        Dn[t] = u.bl_d[i];
+                        u.snew[t] = u.bl_s[i];
+                    }
+                    Dr = Dn;
+                    Sr = u.snew;
+                } else {
+                    int32_t *Dw = J.g.D + (size_t)s * n;
+                    uint64_t *Sw = J.g.S + (size_t)s * n;
+                    for (int32_t i = tid; i < nb; i += bs) {
+                        const int32_t t = u.bl_t[i];
+                        const int32_t d = u.bl_d[i];
+                        if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], d < (lds ? lds_row[t] : Dw[t]));
+                        Sw[t] = u.bl_s[i];
+                        Dw[t] = d;
+                        if (lds) lds_row[t] = d;
+                    }
+                }
+                __syncthreads();
+            }
+            // The old pass of a paired source tests its B vertices' E*
+            // in-arcs, so it never uses a stored predecessor that its new
+            // pass (another workgroup, at the same time) rewrites: its walk
+            // may load one ahead, but stops at the B vertex, which is in the
+            // sub-DAG from the start.  A source updated by one workgroup
+            // rewrites its predecessors only after the old pass, so that
+            // pass takes the B vertices' stored (old) predecessors.  The new
+            // pass of a one-arc update takes theirs from Alg 2 (written
+            // above); other updates test the B vertices' E* in-arcs and
+            // write the predecessors from the arc record
+            preds_done = restricted_pass<false, 2, 4>(
+                s, n, Dr, Sr, ph ? J.g.yc_ptr : J.g.xc_ptr, ph ? J.g.yc_src : J.g.xc_src,
+                ph ? J.g.yc_dst : J.g.xc_dst, ph ? J.g.yc_w : J.g.xc_w, u.bl_t, nb, full, u, ph ? 1.0 : -1.0,
+                J.g.bc_delta, pred_row, ph && !edge ? pred_row : nullptr, ph ? edge : role == 2, sh, es);
+        }
+        // the new row of the new pass: in LDS, in the slot (role 1 without
+        // staging) or written back to D (role 2)
+        if (role != 0 && !preds_done && !edge)
+            refresh_preds<1>(lds ? lds_row : role == 1 ? u.dnew : Dg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, u.bl_t, nb,
+                             pred_row, sh, es);
     }
 }
 
@@ -2957,10 +3037,7 @@ __global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jo
             c->a_count = 0;
             c->work_next = 0;
             c->big_count = 0;
-            c->big_next = 0;
             c->dag_count = 0;
-            c->dag_next = 0;
-            c->dag_next_light = 0;
             c->dag_back = 0;
         }
     }
@@ -2969,7 +3046,11 @@ __global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jo
 // Clears the statistics that accumulate during an update (before k_scan).
 __global__ void k_begin(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p, StepPool pool) {
     const int njobs = *njobs_p;
-    if (threadIdx.x == 0) *pool.next = 0;
+    if (threadIdx.x == 0) {
+        *pool.next = 0;
+        *pool.src_next = 0;
+        *pool.wide_next = 0;
+    }
     for (int j = threadIdx.x; j < njobs; j += blockDim.x) {
         GraphCtl *c = jobs[j].g.ctl;
         c->changed_pairs = 0;
@@ -2977,10 +3058,7 @@ __global__ void k_begin(const UpdateJob *__restrict__ jobs, const int32_t *__res
         c->work_next = 0;
         c->t_count = 0;
         c->big_count = 0;
-        c->big_next = 0;
         c->dag_count = 0;
-        c->dag_next = 0;
-        c->dag_next_light = 0;
         c->dag_back = 0;
     }
 }
