@@ -24,14 +24,6 @@ constexpr int KMAX = 64;
 // per-workgroup bookkeeping: 36864 * 4 = 144 KiB of the 160 KiB of gfx950.
 constexpr int32_t LDS_ROW_MAX = 36864;
 
-// E* rebuild modes (see the k_es_* kernels).
-//   ES_BUILD   all arcs (CSR by tail)  -> X  (arcs with w == d)
-//   ES_BUILD_C all arcs (CSR by head)  -> XC (arcs with w == d)
-//   ES_MERGE   XC plus the updated arcs -> YC (k_es_merge, elementwise)
-//   ES_FILTER  YC                       -> XC (arcs with w == d after the update;
-//              k_es_keep, k_es_wscan, k_es_place, arc-parallel)
-enum { ES_BUILD = 0, ES_BUILD_C = 1, ES_MERGE = 2, ES_FILTER = 3 };
-
 // Flags of the restricted dependency pass.  The LDS table keeps them apart;
 // the global-memory pass packs them with the successor count in one word.
 enum : int32_t { F_VIS = 1, F_B = 2 };
@@ -52,7 +44,6 @@ struct GraphCtl {
     int32_t status;     // sticky ST_* bits
     int32_t a_count;    // |A| of the update in flight (written by the scan)
     int32_t max_levels; // deepest Kahn level count seen (statistic)
-    int32_t es_m;       // arcs in X (E* by tail, built by the static pass)
     int32_t esc_m;      // arcs in XC (E* by head, kept current)
     int32_t esc_m_tmp;  // arcs in YC (E* by head plus the updated arcs)
     int32_t t_count;    // candidate targets of the update in flight
@@ -118,8 +109,8 @@ struct GraphPtrs {
     uint64_t *S;     // n x n path counts
     double *bc_hi, *bc_lo;  // BC as an unevaluated sum hi + lo
     double *bc_delta;       // per-update difference, folded into (hi, lo) at commit
-    // E* three ways: X by tail (static pass), XC by head (current), YC by
-    // head with the updated arcs merged in (during an update).
+    // E* by head: XC current, YC with the updated arcs merged in (during an
+    // update).  x_src and x_dst hold the filter's keep masks and their prefix.
     int32_t *x_ptr, *x_src, *x_dst, *x_w;
     int32_t *xc_ptr, *xc_src, *xc_dst, *xc_w;
     int32_t *yc_ptr, *yc_src, *yc_dst, *yc_w;
@@ -166,23 +157,6 @@ struct UpdateJob {
 };
 
 __host__ __device__ constexpr inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
-// Per-workgroup scratch of the static pass (Kahn levels over a whole DAG).
-struct StaticLayout {
-    size_t indeg, order, lvl, coef, queue2, total;
-};
-
-__host__ __device__ inline StaticLayout static_layout(int32_t n) {
-    StaticLayout L;
-    size_t off = 0;
-    L.indeg = off;  off += align256(sizeof(int32_t) * (size_t)n);
-    L.order = off;  off += align256(sizeof(int32_t) * (size_t)n);
-    L.lvl = off;    off += align256(sizeof(int32_t) * ((size_t)n + 1));
-    L.coef = off;   off += align256(sizeof(double) * (size_t)n);
-    L.queue2 = off; off += align256(sizeof(int32_t) * (size_t)n);
-    L.total = off;
-    return L;
-}
 
 // Per-workgroup scratch of the DAG kernel's global sub-DAG pass: outdeg /
 // acc / kcnt are kept all-zero between sources (each pass clears exactly the
@@ -270,10 +244,7 @@ __host__ __device__ inline ItemRegion item_region_at(char *base, int32_t n) {
 
 // Workgroup slots: the DAG kernel and the static pass share one region, the
 // wide kernel has its own.
-__host__ __device__ inline size_t slot_bytes_for(int32_t n) {
-    const size_t a = static_layout(n).total, b = update_layout(n).total;
-    return a > b ? a : b;
-}
+__host__ __device__ inline size_t slot_bytes_for(int32_t n) { return update_layout(n).total; }
 __host__ __device__ inline size_t wide_slot_bytes_for(int32_t n) { return wide_layout(n).total; }
 
 }  // namespace bcinc

@@ -214,6 +214,8 @@ struct bc_ctx {
     size_t sssp_lds_limit = 0;  // and the static search
     int rows_grid = 1024;       // workgroups of the row kernel (all resident)
     int32_t n_layout = 1;  // slot layout size: the largest graph ever loaded
+    int32_t zero_layout = 0;  // the layout whose slots were last cleared (zero_slots)
+    bool rezero = false;      // a graph has reported an error since
     bool full_search = false;  // BC_FLAG_FULL_SEARCH: the static pass relaxes every arc
     bool check = false;        // BC_FLAG_CHECK: state check after every load, recompute and step
     // schedules chosen by the autotuner per size bucket (ceil(log2 n) of a
@@ -966,6 +968,7 @@ void apply_pending(GraphRec *g, const Pending &p) {
 bc_status read_status(bc_ctx *ctx, GraphRec *g, int32_t *status) {
     HIPCHK(hipMemcpyAsync(status, &g->P.ctl->status, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (*status) ctx->rezero = true;
     return BC_OK;
 }
 
@@ -999,6 +1002,7 @@ bc_status read_status(bc_ctx *ctx, const std::vector<const int32_t *> &words, bo
         HIPCHK(hipStreamSynchronize(st));
         for (size_t k = 0; k < e - b; ++k) *acc |= ctx->h_status[k];
     }
+    if (*acc) ctx->rezero = true;
     return BC_OK;
 }
 
@@ -1218,6 +1222,38 @@ bc_status check_step(bc_ctx *ctx, const std::vector<UpdateJob> &jobs) {
 //     complete graphs with random weights E* has about n ln n arcs
 //     (Section 1), so H stays a small fraction of the n^2 arcs;
 //   otherwise (sparse graphs, or BC_FLAG_FULL_SEARCH): every arc.
+// The kernels keep the flags and sums of every work slot at zero between
+// uses.  The slots are cleared only when their layout has changed (n_layout
+// has grown, so they may hold another layout's lists) or a graph has reported
+// an error: clearing them twice per static pass took 0.8 ms at n = 16384.
+bc_status zero_slots(bc_ctx *ctx) {
+    if (ctx->zero_layout == ctx->n_layout && !ctx->rezero) return BC_OK;
+    const ScratchPlan sp = plan_scratch(ctx, ctx->n_layout);
+    HIPCHK(hipMemsetAsync(sp.src_base, 0, (size_t)sp.src * sp.src_bytes + (size_t)sp.wide * sp.wide_bytes, ctx->stream));
+    ctx->zero_layout = ctx->n_layout;
+    ctx->rezero = false;
+    return BC_OK;
+}
+
+void launch_static(bc_ctx *ctx, const GraphPtrs &P, int slots, const LaunchShape &L) {
+    const int32_t n = P.n;
+    // where the values live (see the kernel), and 8 to 16 vertices per thread:
+    // smaller workgroups for smaller graphs, so that several sources share a
+    // CU (20 waves by the kernel's registers, 160 KiB of LDS)
+    const int mode = n <= ST_VALS ? ST_VAL_LDS : n <= LDS_ROW_MAX ? ST_ROW_LDS : ST_GLOBAL;
+    const int block = n > 9216 ? 1024 : n > 4096 ? 512 : n > 2048 ? 256 : n > 512 ? 128 : 64;
+    const int lhist = std::min(n, ST_HIST);
+    const size_t lds = align256(4 * (size_t)lhist) + (mode == ST_VAL_LDS ? 8 : mode == ST_ROW_LDS ? 4 : 0) * (size_t)n;
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(1280 / block, 160 * 1024 / (lds + 1024)));
+    const dim3 grid(std::min(slots, per_cu * ctx->cu_count)), blk(block);
+    if (mode == ST_VAL_LDS)
+        hipLaunchKernelGGL(k_static<ST_VAL_LDS>, grid, blk, lds, ctx->stream, P, L.src_base, L.slot_bytes, lhist, L.n_layout);
+    else if (mode == ST_ROW_LDS)
+        hipLaunchKernelGGL(k_static<ST_ROW_LDS>, grid, blk, lds, ctx->stream, P, L.src_base, L.slot_bytes, lhist, L.n_layout);
+    else
+        hipLaunchKernelGGL(k_static<ST_GLOBAL>, grid, blk, lds, ctx->stream, P, L.src_base, L.slot_bytes, lhist, L.n_layout);
+}
+
 bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     const int32_t n = g->n;
     ArcCsr full;
@@ -1247,10 +1283,7 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     const UpdateJob *dj = ring_jobs_dev(ctx, r);
     const int32_t *nj = ring_njobs_dev(ctx, r);
     const int slots = std::min<int>(L.slots, n);
-    // slots may still hold another layout's lists (n_layout can just have grown)
-    const ScratchPlan sp = plan_scratch(ctx, ctx->n_layout);
-    const size_t slot_region = (size_t)sp.src * sp.src_bytes + (size_t)sp.wide * sp.wide_bytes;
-    HIPCHK(hipMemsetAsync(sp.src_base, 0, slot_region, ctx->stream));
+    if ((st = zero_slots(ctx))) return st;
     const int g_wave = (int)std::min<int64_t>(((int64_t)n * 64 + 255) / 256, 4096);
     hipStream_t s = ctx->stream;
     // the search stages the row in LDS when it fits beside its expansion
@@ -1321,19 +1354,13 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
         hipLaunchKernelGGL(k_sssp, dim3(slots), dim3(1024), source_lds_bytes(sssp_cap, 1024, 0), s, dj, L.src_base,
                            L.slot_bytes, sssp_cap, L.n_layout, g->P.arc_ptr, g->P.arc_dst, g->P.arc_w);
     }
-    hipLaunchKernelGGL(k_es_count<ES_BUILD>, dim3(g_wave), dim3(256), 0, s, dj, nj);
-    hipLaunchKernelGGL(k_es_scan<ES_BUILD>, dim3(1), dim3(1024), 0, s, dj, nj);
-    hipLaunchKernelGGL(k_es_scatter<ES_BUILD>, dim3(g_wave), dim3(256), 0, s, dj, nj);
-    hipLaunchKernelGGL(k_es_count<ES_BUILD_C>, dim3(g_wave), dim3(256), 0, s, dj, nj);
-    hipLaunchKernelGGL(k_es_scan<ES_BUILD_C>, dim3(1), dim3(1024), 0, s, dj, nj);
-    hipLaunchKernelGGL(k_es_scatter<ES_BUILD_C>, dim3(g_wave), dim3(256), 0, s, dj, nj);
+    hipLaunchKernelGGL(k_es_count, dim3(g_wave), dim3(256), 0, s, dj);
+    hipLaunchKernelGGL(k_es_scan, dim3(1), dim3(1024), 0, s, dj);
+    hipLaunchKernelGGL(k_es_scatter, dim3(g_wave), dim3(256), 0, s, dj);
     hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
-    hipLaunchKernelGGL(k_static, dim3(slots), dim3(1024), (size_t)L.lds_cap * 4, s, dj, L.src_base, L.slot_bytes,
-                       L.lds_cap, L.n_layout);
+    launch_static(ctx, g->P, slots, L);
     hipLaunchKernelGGL(k_commit, dim3((n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048), dim3(256), 0, s, dj, nj, 1);
     HIPCHK(hipGetLastError());
-    // the update kernels expect their per-workgroup flags and sums at zero
-    HIPCHK(hipMemsetAsync(sp.src_base, 0, slot_region, s));
     st = ring_release(ctx, r);
     if (st) return st;
     // the host vectors above are read by the copies: finish before they go
@@ -1384,7 +1411,8 @@ bc_status set_lds_limits(bc_ctx *ctx) {
     if ((st = set_lds_limit(ctx, (const void *)k_source<128>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_source_wide, &ctx->wide_lds_limit))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_sssp, &ctx->sssp_lds_limit))) return st;
-    if ((st = set_lds_limit(ctx, (const void *)k_static))) return st;
+    if ((st = set_lds_limit(ctx, (const void *)k_static<ST_VAL_LDS>))) return st;
+    if ((st = set_lds_limit(ctx, (const void *)k_static<ST_ROW_LDS>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_delta_row_byval))) return st;
     return set_lds_limit(ctx, (const void *)k_delta_row);
 }
