@@ -83,10 +83,10 @@ __global__ void __launch_bounds__(256) k_check_rows(const GraphPtrs G, CheckRec 
             bool carry = false;
             int32_t tight = 0, tail = PRED_NONE;
             for (int32_t e = G.arcin_ptr[t]; e < G.arcin_ptr[t + 1]; ++e) {
-                const int32_t a = G.arcin_src[e];
+                const int32_t a = G.arcin[e].v;
                 const int32_t da = G.D[row + a];
                 if (da == INF32) continue;
-                const int64_t c = (int64_t)da + G.arcin_w[e];
+                const int64_t c = (int64_t)da + G.arcin[e].w;
                 if (dt == INF32 || c < (int64_t)dt) {
                     kind = CK_RELAX;
                     break;
@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(256) k_check_estar(const GraphPtrs G, CheckRec
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n; b += (int64_t)gridDim.x * blockDim.x) {
         const int32_t p0 = G.arcin_ptr[b], p1 = G.arcin_ptr[b + 1];
         int32_t tight = 0;
-        for (int32_t e = p0; e < p1; ++e) tight += G.D[(size_t)G.arcin_src[e] * n + b] == G.arcin_w[e];
+        for (int32_t e = p0; e < p1; ++e) tight += G.D[(size_t)G.arcin[e].v * n + b] == G.arcin[e].w;
         const int32_t x0 = G.xc_ptr[b], x1 = G.xc_ptr[b + 1];
         int32_t bad_tail = -1;
         bool bad = x0 < 0 || x1 < x0 || (int64_t)x1 > G.es_cap || x1 - x0 != tight;
@@ -137,10 +137,10 @@ __global__ void __launch_bounds__(256) k_check_estar(const GraphPtrs G, CheckRec
                 int32_t lo = p0, hi = p1;
                 while (lo < hi) {
                     const int32_t mid = (lo + hi) >> 1;
-                    if (G.arcin_src[mid] < a) lo = mid + 1;
+                    if (G.arcin[mid].v < a) lo = mid + 1;
                     else hi = mid;
                 }
-                bad = lo == p1 || G.arcin_src[lo] != a || G.arcin_w[lo] != w;
+                bad = lo == p1 || G.arcin[lo].v != a || G.arcin[lo].w != w;
             }
             for (int32_t k = x0; k < i && !bad; ++k) bad = G.xc_src[k] == a;
             if (bad) bad_tail = a;

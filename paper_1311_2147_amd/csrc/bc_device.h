@@ -99,6 +99,11 @@ constexpr int32_t LCAP = 1024;
 // kernel (their sub-DAGs take longest; starting them first shortens the tail).
 constexpr int32_t HEAVY_NB = 32;
 
+// An arc of a list by tail or by head: its other end and its weight.
+struct alignas(8) ArcW {
+    int32_t v, w;
+};
+
 // Device pointers and sizes of one graph.  A copy rides in every job.
 struct GraphPtrs {
     int32_t n;
@@ -134,8 +139,8 @@ struct GraphPtrs {
     // Full arc set by tail and by head (static recompute and E* build).  No
     // update reads them; a state check puts the current arcs by head in
     // arcin_* before it runs.
-    int32_t *arc_ptr, *arc_dst, *arc_w;
-    int32_t *arcin_ptr, *arcin_src, *arcin_w;
+    int32_t *arc_ptr, *arcin_ptr;
+    ArcW *arc, *arcin;
     int64_t arc_m;
 };
 

@@ -390,8 +390,8 @@ GraphPtrs carve(char *base, int32_t n, int64_t arc_cap, int64_t es_cap, size_t *
     size_t orvvd = c.take(4 * (size_t)n), orvvs = c.take(8 * (size_t)n), orvvh = c.take(8 * (size_t)n);
     size_t otl = c.take(4 * (size_t)n), otlr = c.take(4 * (size_t)n), otlrr = c.take(4 * (size_t)n);
     size_t octl = c.take(sizeof(GraphCtl));
-    size_t oap = c.take(4 * ((size_t)n + 1)), oad = c.take(4 * (size_t)arc_cap), oaw = c.take(4 * (size_t)arc_cap);
-    size_t oip = c.take(4 * ((size_t)n + 1)), ois = c.take(4 * (size_t)arc_cap), oiw = c.take(4 * (size_t)arc_cap);
+    size_t oap = c.take(4 * ((size_t)n + 1)), oaa = c.take(sizeof(ArcW) * (size_t)arc_cap);
+    size_t oip = c.take(4 * ((size_t)n + 1)), oia = c.take(sizeof(ArcW) * (size_t)arc_cap);
     size_t ochk = c.take(sizeof(CheckRec));
     *total = c.off;
     GraphPtrs P{};
@@ -434,11 +434,9 @@ GraphPtrs carve(char *base, int32_t n, int64_t arc_cap, int64_t es_cap, size_t *
     P.tl_rvvD = (int32_t *)(base + otlrr);
     P.ctl = (GraphCtl *)(base + octl);
     P.arc_ptr = (int32_t *)(base + oap);
-    P.arc_dst = (int32_t *)(base + oad);
-    P.arc_w = (int32_t *)(base + oaw);
+    P.arc = (ArcW *)(base + oaa);
     P.arcin_ptr = (int32_t *)(base + oip);
-    P.arcin_src = (int32_t *)(base + ois);
-    P.arcin_w = (int32_t *)(base + oiw);
+    P.arcin = (ArcW *)(base + oia);
     return P;
 }
 
@@ -1006,11 +1004,24 @@ bc_status read_status(bc_ctx *ctx, const std::vector<const int32_t *> &words, bo
     return BC_OK;
 }
 
+// An arc set by tail (heads ascending within a tail).
+struct ArcCsr {
+    std::vector<int32_t> ptr;
+    std::vector<ArcW> arc;
+    int64_t size() const { return (int64_t)arc.size(); }
+    // from an arc list in CSR order kept as two arrays
+    template <typename P>
+    void assign(const std::vector<P> &p, const std::vector<int32_t> &v, const std::vector<int32_t> &w) {
+        ptr.assign(p.begin(), p.end());
+        arc.resize(v.size());
+        for (size_t i = 0; i < v.size(); ++i) arc[i] = {v[i], w[i]};
+    }
+};
+
 // The maintained E* as an arc list grouped by tail (heads ascending within a
 // tail), read from its by-head copy XC.  Refuses a graph with a sticky error:
 // its E* may be incomplete then.
-bc_status estar_by_tail(bc_ctx *ctx, GraphRec *g, std::vector<int32_t> &hp, std::vector<int32_t> &hd,
-                        std::vector<int32_t> &hw) {
+bc_status estar_by_tail(bc_ctx *ctx, GraphRec *g, ArcCsr &out) {
     const int32_t n = g->n;
     int32_t status = 0;
     bc_status st = read_status(ctx, g, &status);
@@ -1028,49 +1039,34 @@ bc_status estar_by_tail(bc_ctx *ctx, GraphRec *g, std::vector<int32_t> &hp, std:
     }
     // counting sort by tail; XC is grouped by ascending head, so heads stay
     // ascending within each tail
-    hp.assign(n + 1, 0);
-    for (int32_t e = 0; e < m; ++e) hp[a[e] + 1]++;
-    for (int32_t i = 0; i < n; ++i) hp[i + 1] += hp[i];
-    hd.resize((size_t)m);
-    hw.resize((size_t)m);
-    std::vector<int32_t> fill(hp.begin(), hp.end() - 1);
-    for (int32_t e = 0; e < m; ++e) {
-        const int32_t q = fill[a[e]]++;
-        hd[q] = b[e];
-        hw[q] = w[e];
-    }
+    out.ptr.assign(n + 1, 0);
+    for (int32_t e = 0; e < m; ++e) out.ptr[a[e] + 1]++;
+    for (int32_t i = 0; i < n; ++i) out.ptr[i + 1] += out.ptr[i];
+    out.arc.resize((size_t)m);
+    std::vector<int32_t> fill(out.ptr.begin(), out.ptr.end() - 1);
+    for (int32_t e = 0; e < m; ++e) out.arc[fill[a[e]]++] = {b[e], w[e]};
     return BC_OK;
 }
-
-// An arc set by tail (heads ascending within a tail).
-struct ArcCsr {
-    std::vector<int32_t> ptr, dst, w;
-    int64_t size() const { return (int64_t)dst.size(); }
-};
 
 // The same arcs grouped by head (counting sort; tails stay ascending).
 void by_head(int32_t n, const ArcCsr &t, ArcCsr &h) {
     const int64_t m = t.size();
     h.ptr.assign(n + 1, 0);
-    h.dst.resize((size_t)m);
-    h.w.resize((size_t)m);
-    for (int64_t e = 0; e < m; ++e) h.ptr[t.dst[e] + 1]++;
+    h.arc.resize((size_t)m);
+    for (int64_t e = 0; e < m; ++e) h.ptr[t.arc[e].v + 1]++;
     for (int32_t i = 0; i < n; ++i) h.ptr[i + 1] += h.ptr[i];
     std::vector<int32_t> fill(h.ptr.begin(), h.ptr.end() - 1);
     for (int32_t a = 0; a < n; ++a)
         for (int32_t e = t.ptr[a]; e < t.ptr[a + 1]; ++e) {
-            const int32_t q = fill[t.dst[e]]++;
-            h.dst[q] = a;
-            h.w[q] = t.w[e];
+            const int32_t q = fill[t.arc[e].v]++;
+            h.arc[q] = {a, t.arc[e].w};
         }
 }
 
-bc_status upload_csr(bc_ctx *ctx, int32_t n, const ArcCsr &c, int32_t *ptr, int32_t *other, int32_t *w) {
+bc_status upload_csr(bc_ctx *ctx, int32_t n, const ArcCsr &c, int32_t *ptr, ArcW *arc) {
     HIPCHK(hipMemcpyAsync(ptr, c.ptr.data(), 4 * (size_t)(n + 1), hipMemcpyHostToDevice, ctx->stream));
-    if (c.size()) {
-        HIPCHK(hipMemcpyAsync(other, c.dst.data(), 4 * (size_t)c.size(), hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(hipMemcpyAsync(w, c.w.data(), 4 * (size_t)c.size(), hipMemcpyHostToDevice, ctx->stream));
-    }
+    if (c.size())
+        HIPCHK(hipMemcpyAsync(arc, c.arc.data(), sizeof(ArcW) * (size_t)c.size(), hipMemcpyHostToDevice, ctx->stream));
     return BC_OK;
 }
 
@@ -1078,12 +1074,11 @@ bc_status upload_csr(bc_ctx *ctx, int32_t n, const ArcCsr &c, int32_t *ptr, int3
 // most k), heads ascending.
 void lightest_arcs(int32_t n, const ArcCsr &full, int32_t k, ArcCsr &out) {
     out.ptr.assign(n + 1, 0);
-    out.dst.clear();
-    out.w.clear();
+    out.arc.clear();
     std::vector<std::pair<int32_t, int32_t>> row;  // (w, head)
     for (int32_t a = 0; a < n; ++a) {
         row.clear();
-        for (int32_t e = full.ptr[a]; e < full.ptr[a + 1]; ++e) row.push_back({full.w[e], full.dst[e]});
+        for (int32_t e = full.ptr[a]; e < full.ptr[a + 1]; ++e) row.push_back({full.arc[e].w, full.arc[e].v});
         if ((int32_t)row.size() > k) {
             std::nth_element(row.begin(), row.begin() + k, row.end());
             row.resize(k);
@@ -1091,11 +1086,8 @@ void lightest_arcs(int32_t n, const ArcCsr &full, int32_t k, ArcCsr &out) {
         std::sort(row.begin(), row.end(), [](const std::pair<int32_t, int32_t> &x, const std::pair<int32_t, int32_t> &y) {
             return x.second < y.second;
         });
-        for (auto &p : row) {
-            out.dst.push_back(p.second);
-            out.w.push_back(p.first);
-        }
-        out.ptr[a + 1] = (int32_t)out.dst.size();
+        for (auto &p : row) out.arc.push_back({p.second, p.first});
+        out.ptr[a + 1] = (int32_t)out.arc.size();
     }
 }
 
@@ -1105,8 +1097,9 @@ int64_t add_missing(int32_t n, ArcCsr &set, const std::vector<int32_t> &a, const
     std::vector<std::vector<std::pair<int32_t, int32_t>>> extra;
     int64_t added = 0;
     for (size_t i = 0; i < a.size(); ++i) {
-        auto first = set.dst.begin() + set.ptr[a[i]], last = set.dst.begin() + set.ptr[a[i] + 1];
-        if (std::binary_search(first, last, b[i])) continue;
+        auto first = set.arc.begin() + set.ptr[a[i]], last = set.arc.begin() + set.ptr[a[i] + 1];
+        auto at = std::lower_bound(first, last, b[i], [](const ArcW &x, int32_t v) { return x.v < v; });
+        if (at != last && at->v == b[i]) continue;
         if (extra.empty()) extra.resize(n);
         extra[a[i]].push_back({b[i], w[i]});
         ++added;
@@ -1117,14 +1110,11 @@ int64_t add_missing(int32_t n, ArcCsr &set, const std::vector<int32_t> &a, const
     std::vector<std::pair<int32_t, int32_t>> row;
     for (int32_t t = 0; t < n; ++t) {
         row.clear();
-        for (int32_t e = set.ptr[t]; e < set.ptr[t + 1]; ++e) row.push_back({set.dst[e], set.w[e]});
+        for (int32_t e = set.ptr[t]; e < set.ptr[t + 1]; ++e) row.push_back({set.arc[e].v, set.arc[e].w});
         row.insert(row.end(), extra[t].begin(), extra[t].end());
         std::sort(row.begin(), row.end());
-        for (auto &p : row) {
-            out.dst.push_back(p.first);
-            out.w.push_back(p.second);
-        }
-        out.ptr[t + 1] = (int32_t)out.dst.size();
+        for (auto &p : row) out.arc.push_back({p.first, p.second});
+        out.ptr[t + 1] = (int32_t)out.arc.size();
     }
     set = std::move(out);
     return added;
@@ -1165,13 +1155,10 @@ bc_status run_check(bc_ctx *ctx, GraphRec *g, const Mirror &arcs, bool all, int3
     Mirror m = arcs;
     m.compact();
     ArcCsr tail, head;
-    tail.ptr.resize((size_t)n + 1);
-    for (int32_t i = 0; i <= n; ++i) tail.ptr[i] = (int32_t)m.ptr[i];
-    tail.dst = std::move(m.dst);
-    tail.w = std::move(m.w);
+    tail.assign(m.ptr, m.dst, m.w);
     if (tail.size() > g->arc_cap) return fail(ctx, BC_ERR_CAPACITY, "arc capacity exceeded");
     by_head(n, tail, head);
-    bc_status st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin_src, g->P.arcin_w);
+    bc_status st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin);
     if (st) return st;
     hipLaunchKernelGGL(k_check_rows, dim3(2048), dim3(256), 0, ctx->stream, g->P, g->chk, all ? 1 : 0);
     hipLaunchKernelGGL(k_check_estar, dim3((int)std::min<int64_t>(((int64_t)n + 255) / 256, 1024)), dim3(256), 0,
@@ -1235,6 +1222,29 @@ bc_status zero_slots(bc_ctx *ctx) {
     return BC_OK;
 }
 
+// The distance search over a set of arcs by tail.  Width of a step: three
+// quarters of the mean weight (at half and at twice that, the rounds and the
+// relaxations on Chung-Lu graphs multiply to more).
+void launch_search(bc_ctx *ctx, const GraphPtrs &P, const ArcCsr &set, const int32_t *ptr, const ArcW *arc) {
+    const int32_t n = P.n;
+    int64_t sum = 0;
+    for (const ArcW &a : set.arc) sum += a.w;
+    const int64_t mean34 = set.size() ? sum / set.size() * 3 / 4 : 1;
+    const int32_t delta = (int32_t)std::max<int64_t>(1, std::min<int64_t>(mean34, INF32 - 1));
+    // the row in LDS where it fits beside the marks and a queue; 8 to 24
+    // vertices per thread, so that several sources share a CU (24 waves by
+    // the kernel's registers)
+    const size_t marks = 8 * (((size_t)n + 63) / 64);
+    const int32_t qcap = std::max(256, std::min(n / 4, 2048));
+    const bool lds = marks + 4 * (size_t)n + 4 * (size_t)qcap <= ctx->sssp_lds_limit;
+    const size_t bytes = marks + 4 * (size_t)qcap + (lds ? 4 * (size_t)n : 0);
+    const int block = n > 17000 ? 1024 : n > 9216 ? 768 : n > 4096 ? 512 : n > 2048 ? 256 : n > 512 ? 128 : 64;
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(1536 / block, 160 * 1024 / (bytes + 2048)));
+    const dim3 grid(std::min(n, per_cu * ctx->cu_count)), blk(block);
+    if (lds) hipLaunchKernelGGL(k_sssp<true>, grid, blk, bytes, ctx->stream, P, ptr, arc, delta, qcap);
+    else hipLaunchKernelGGL(k_sssp<false>, grid, blk, bytes, ctx->stream, P, ptr, arc, delta, qcap);
+}
+
 void launch_static(bc_ctx *ctx, const GraphPtrs &P, int slots, const LaunchShape &L) {
     const int32_t n = P.n;
     // where the values live (see the kernel), and 8 to 16 vertices per thread:
@@ -1258,14 +1268,11 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     const int32_t n = g->n;
     ArcCsr full;
     if (over_estar) {
-        bc_status st = estar_by_tail(ctx, g, full.ptr, full.dst, full.w);
+        bc_status st = estar_by_tail(ctx, g, full);
         if (st) return st;
     } else {
         g->mirror.compact();
-        full.ptr.resize(n + 1);
-        full.dst = g->mirror.dst;
-        full.w = g->mirror.w;
-        for (int32_t i = 0; i <= n; ++i) full.ptr[i] = (int32_t)g->mirror.ptr[i];
+        full.assign(g->mirror.ptr, g->mirror.dst, g->mirror.w);
     }
     const int64_t m = full.size();
     if (m > g->arc_cap) return fail(ctx, BC_ERR_CAPACITY, "arc capacity exceeded");
@@ -1286,26 +1293,21 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     if ((st = zero_slots(ctx))) return st;
     const int g_wave = (int)std::min<int64_t>(((int64_t)n * 64 + 255) / 256, 4096);
     hipStream_t s = ctx->stream;
-    // the search stages the row in LDS when it fits beside its expansion
-    // arrays (for n up to about 34 800), else works on the row in place
-    const int32_t sssp_cap = source_lds_bytes(L.lds_cap, 1024, 0) <= ctx->sssp_lds_limit ? L.lds_cap : 0;
     ArcCsr search;  // the arcs the distance search relaxes
     bool have_dist = false;
     int32_t rounds = 0;
     if (checked) {
         // every arc by tail stays in arc_* for the check; the searched set
         // goes by tail into the by-head arrays, unused until the E* build
-        if ((st = upload_csr(ctx, n, full, g->P.arc_ptr, g->P.arc_dst, g->P.arc_w))) return st;
+        if ((st = upload_csr(ctx, n, full, g->P.arc_ptr, g->P.arc))) return st;
         lightest_arcs(n, full, search_k(n), search);
         unsigned long long *cnt = (unsigned long long *)misc_dev(ctx);
         std::vector<int32_t> ca, cb, cw;
         for (;;) {
             ++rounds;
-            if ((st = upload_csr(ctx, n, search, g->P.arcin_ptr, g->P.arcin_src, g->P.arcin_w))) return st;
+            if ((st = upload_csr(ctx, n, search, g->P.arcin_ptr, g->P.arcin))) return st;
             hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
-            hipLaunchKernelGGL(k_sssp, dim3(slots), dim3(1024), source_lds_bytes(sssp_cap, 1024, 0), s, dj,
-                               L.src_base, L.slot_bytes, sssp_cap, L.n_layout, g->P.arcin_ptr, g->P.arcin_src,
-                               g->P.arcin_w);
+            launch_search(ctx, g->P, search, g->P.arcin_ptr, g->P.arcin);
             HIPCHK(hipMemsetAsync(cnt, 0, 8, s));
             hipLaunchKernelGGL(k_search_check, dim3(std::max(1, std::min(g_wave, 4096))), dim3(256), 0, s, dj,
                                g->P.yc_src, g->P.yc_dst, g->P.yc_w, g->es_cap, cnt);
@@ -1346,13 +1348,12 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     // the final arc set, by tail and by head, for the E* build
     ArcCsr head;
     by_head(n, search, head);
-    if ((st = upload_csr(ctx, n, search, g->P.arc_ptr, g->P.arc_dst, g->P.arc_w))) return st;
-    if ((st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin_src, g->P.arcin_w))) return st;
+    if ((st = upload_csr(ctx, n, search, g->P.arc_ptr, g->P.arc))) return st;
+    if ((st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin))) return st;
     g->P.arc_m = search.size();
     if (!have_dist) {
         hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
-        hipLaunchKernelGGL(k_sssp, dim3(slots), dim3(1024), source_lds_bytes(sssp_cap, 1024, 0), s, dj, L.src_base,
-                           L.slot_bytes, sssp_cap, L.n_layout, g->P.arc_ptr, g->P.arc_dst, g->P.arc_w);
+        launch_search(ctx, g->P, search, g->P.arc_ptr, g->P.arc);
     }
     hipLaunchKernelGGL(k_es_count, dim3(g_wave), dim3(256), 0, s, dj);
     hipLaunchKernelGGL(k_es_scan, dim3(1), dim3(1024), 0, s, dj);
@@ -1410,7 +1411,7 @@ bc_status set_lds_limits(bc_ctx *ctx) {
     if ((st = set_lds_limit(ctx, (const void *)k_source<256>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_source<128>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_source_wide, &ctx->wide_lds_limit))) return st;
-    if ((st = set_lds_limit(ctx, (const void *)k_sssp, &ctx->sssp_lds_limit))) return st;
+    if ((st = set_lds_limit(ctx, (const void *)k_sssp<true>, &ctx->sssp_lds_limit))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_static<ST_VAL_LDS>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_static<ST_ROW_LDS>))) return st;
     if ((st = set_lds_limit(ctx, (const void *)k_delta_row_byval))) return st;

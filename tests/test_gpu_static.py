@@ -2,7 +2,8 @@
 
 Values in LDS (up to 18432 vertices), the distance row only (up to 36864) or
 nothing; the list of DAG arcs against sweeps over E* (more than three DAG arcs
-per vertex); level counts in LDS (below 2048 levels) or in the slot.  Small
+per vertex); level counts in LDS (below 2048 levels) or in the slot; the search's
+queue and its list of heavy vertices full.  Small
 graphs are compared with the oracle in full.  Large ones are many small
 components, so that the oracle can give a component's betweenness by itself,
 and the device's state check covers distances, counts and predecessors.
@@ -27,6 +28,22 @@ def layered(layers: int, width: int) -> W.Graph:
     return W.Graph(layers * width, True, src, dst, np.ones(src.size, np.int64))
 
 
+def hub_row(hubs: int, degree: int, n: int) -> W.Graph:
+    """Vertex 0 reaches `hubs` vertices at distance 1, each with `degree` out-arcs: the
+    search expands them all at once (queue of 256 at these sizes, 256 chunks of heavy
+    vertices, 256 arcs per chunk)."""
+    rs = np.random.default_rng(hubs * 1000 + degree)
+    src, dst = [np.zeros(hubs, np.int64)], [np.arange(1, hubs + 1)]
+    for h in range(1, hubs + 1):
+        others = rs.permutation(np.delete(np.arange(1, n), h - 1))[:degree]
+        src.append(np.full(others.size, h))
+        dst.append(others)
+    src, dst = np.concatenate(src), np.concatenate(dst)
+    w = rs.integers(1, 60, src.size)
+    w[:hubs] = 1
+    return W.Graph(n, True, src.astype(np.int32), dst.astype(np.int32), w.astype(np.int64))
+
+
 SMALL = {
     "one vertex": lambda: W.Graph(1, True, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros(0, np.int64)),
     "two": lambda: W.path_graph(2),
@@ -37,6 +54,12 @@ SMALL = {
     "2048 levels": lambda: W.path_graph(2048),
     "2049 levels": lambda: W.path_graph(2049, directed=True),
     "2500 levels": lambda: W.path_graph(2500),
+    "more hubs than the queue holds": lambda: hub_row(300, 64, 700),
+    "more hubs than the heavy list holds": lambda: hub_row(300, 65, 700),
+    "more chunks than the heavy list holds": lambda: hub_row(200, 400, 700),
+    "no arc at all": lambda: W.Graph(130, True, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros(0, np.int64)),
+    "one heavy weight": lambda: W.Graph(3, True, np.array([0, 1, 0], np.int32), np.array([1, 2, 2], np.int32),
+                                        np.array([1, 2, 2 ** 31 - 2], np.int64)),
     "unit weights": lambda: W.chung_lu_directed(1201, 2.5, 16.0, 1, 9),
 }
 
