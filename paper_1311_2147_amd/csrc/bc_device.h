@@ -49,6 +49,7 @@ struct GraphCtl {
     int32_t t_count;    // candidate targets of the update in flight
     int32_t big_last;   // deferred sources of the last update (statistic)
     unsigned long long affected_last;  // |A| of the last update
+    unsigned long long changed_last;   // and its changed pairs
     unsigned long long updates;        // updates applied since load
     unsigned long long affected_total; // sums over all updates since load
     unsigned long long changed_total;
@@ -58,7 +59,7 @@ struct GraphCtl {
     alignas(256) int32_t dag_count;    // listed sources with many changed targets: dlist[0 .. dag_count)
     alignas(256) int32_t dag_back;     // listed sources with few: dlist[n - dag_back .. n)
     alignas(256) int32_t big_count;    // deferred (large) sources of the update in flight
-    alignas(256) unsigned long long changed_pairs;  // statistic of the last update
+    alignas(256) unsigned long long changed_pairs;  // of the update in flight
 };
 
 // Per-source scalars of the update in flight (Alg 4 output).
@@ -92,6 +93,10 @@ struct StepPool {
     int32_t *wide_next;  // units of the wide kernel handed out past the first per workgroup
     int64_t cap;
 };
+
+// An E* that may hold more arcs than this has the filter's keep masks scanned
+// by a launch of their own.
+constexpr int64_t ES_LONG = int64_t(1) << 20;
 
 // Most changed targets the row kernel lists for one source (in LDS).
 constexpr int32_t LCAP = 1024;

@@ -512,23 +512,27 @@ struct LaunchShape {
     int item_regions;
     int wide_lds_cap; // and its LDS staging limit
     int32_t n_layout;
+    bool may_defer;      // some source may go to the wide kernel
+    bool es_long;        // some E* may hold more than ES_LONG arcs
+    int64_t es_cap_max;  // most arcs an E* of the step may hold
 };
 
 // The update kernel sequence for the jobs staged in ring slot r, in four
-// parts: 0 = begin, scan, row v'', E* merge; 1 = the row kernel; 2 = the DAG
-// and wide kernels; 3 = E* filter and commit.
-bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part) {
-    const UpdateJob *jobs = ring_jobs_dev(ctx, r);
-    const int32_t *nj = ring_njobs_dev(ctx, r);
+// parts: 0 = scan, row v'', E* merge (with `one`, the step's only job, which
+// then comes with the launch instead of the ring's copy); 1 = the row kernel;
+// 2 = the DAG and wide kernels; 3 = E* filter and commit.
+bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part, const UpdateJob *one = nullptr) {
+    UpdateJob *jobs = ring_jobs_dev(ctx, r);
+    int32_t *nj = ring_njobs_dev(ctx, r);
     hipStream_t st = ctx->stream;
     const int g_elem = (int)std::min<int64_t>(((int64_t)L.n_max + 255) / 256, 2048);
     const int g_wave = (int)std::min<int64_t>(((int64_t)L.n_max * 64 + 255) / 256, 4096);
     const StepPool pool = step_pool(ctx);
     if (part == 0) {
-        hipLaunchKernelGGL(k_begin, dim3(1), dim3(64), 0, st, jobs, nj, pool);
-        hipLaunchKernelGGL(k_scan, dim3(g_elem, L.njobs), dim3(256), 0, st, jobs, nj);
-        hipLaunchKernelGGL(k_targets, dim3(g_elem, L.njobs), dim3(256), 0, st, jobs, nj);
-        hipLaunchKernelGGL(k_es_merge, dim3(g_wave, L.njobs), dim3(256), 0, st, jobs, nj);
+        if (one)
+            hipLaunchKernelGGL(k_prep_one, dim3(2 * g_elem + g_wave), dim3(256), 0, st, *one, jobs, nj, g_elem);
+        else
+            hipLaunchKernelGGL(k_prep, dim3(2 * g_elem + g_wave, L.njobs), dim3(256), 0, st, jobs, nj, g_elem);
     } else if (part == 1) {
         hipLaunchKernelGGL(k_rows, dim3(ctx->rows_grid), dim3(256), 0, st, jobs, nj, ctx->big_b, pool);
     } else if (part == 2) {
@@ -536,28 +540,34 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part)
         // sources) touch disjoint rows and run side by side: the wide one
         // directly behind the row kernel on the main stream, so its few long
         // workgroups (a whole CU each) start first, the DAG kernel on the
-        // side stream, filling the remaining CUs
-        HIPCHK(hipEventRecord(ctx->fork_ev, st));
-        HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
-        hipLaunchKernelGGL(k_source_wide, dim3(L.wide_slots), dim3(ctx->wide_block),
-                           source_lds_bytes(L.wide_lds_cap, ctx->wide_block, 0), st, jobs, nj, L.wide_base,
-                           L.wide_bytes, L.wide_lds_cap, L.n_layout, L.items_base, L.item_regions, pool);
+        // side stream, filling the remaining CUs; the DAG kernel alone where
+        // no source can be deferred
+        hipStream_t dag = L.may_defer ? ctx->side : st;
+        if (L.may_defer) {
+            HIPCHK(hipEventRecord(ctx->fork_ev, st));
+            HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
+            hipLaunchKernelGGL(k_source_wide, dim3(L.wide_slots), dim3(ctx->wide_block),
+                               source_lds_bytes(L.wide_lds_cap, ctx->wide_block, 0), st, jobs, nj, L.wide_base,
+                               L.wide_bytes, L.wide_lds_cap, L.n_layout, L.items_base, L.item_regions, pool);
+        }
         const size_t lds = source_lds_bytes(L.src_lds_cap, ctx->block, ctx->table);
         if (ctx->table == 128)
-            hipLaunchKernelGGL(k_source<128>, dim3(L.slots), dim3(ctx->block), lds, ctx->side, jobs, nj, L.src_base,
+            hipLaunchKernelGGL(k_source<128>, dim3(L.slots), dim3(ctx->block), lds, dag, jobs, nj, L.src_base,
                                L.slot_bytes, L.src_lds_cap, L.n_layout, pool);
         else
-            hipLaunchKernelGGL(k_source<256>, dim3(L.slots), dim3(ctx->block), lds, ctx->side, jobs, nj, L.src_base,
+            hipLaunchKernelGGL(k_source<256>, dim3(L.slots), dim3(ctx->block), lds, dag, jobs, nj, L.src_base,
                                L.slot_bytes, L.src_lds_cap, L.n_layout, pool);
-        HIPCHK(hipEventRecord(ctx->join_ev, ctx->side));
-        hipLaunchKernelGGL(k_wide_apply, dim3(256), dim3(256), 0, st, jobs, nj, L.items_base, L.item_regions,
-                           L.n_layout);
-        HIPCHK(hipStreamWaitEvent(st, ctx->join_ev, 0));
+        if (L.may_defer) {
+            HIPCHK(hipEventRecord(ctx->join_ev, ctx->side));
+            hipLaunchKernelGGL(k_wide_apply, dim3(256), dim3(256), 0, st, jobs, nj, L.items_base, L.item_regions,
+                               L.n_layout);
+            HIPCHK(hipStreamWaitEvent(st, ctx->join_ev, 0));
+        }
     } else {
         hipLaunchKernelGGL(k_es_keep, dim3(g_wave, L.njobs), dim3(256), 0, st, jobs, nj);
-        hipLaunchKernelGGL(k_es_wscan, dim3(L.njobs), dim3(1024), 0, st, jobs, nj);
-        hipLaunchKernelGGL(k_es_place, dim3(g_wave, L.njobs), dim3(256), 0, st, jobs, nj);
-        hipLaunchKernelGGL(k_commit, dim3(g_elem, L.njobs), dim3(256), 0, st, jobs, nj, 0);
+        if (L.es_long) hipLaunchKernelGGL(k_es_wscan, dim3(L.njobs), dim3(1024), 0, st, jobs, nj);
+        const int g_place = (int)std::min<int64_t>(std::max<int64_t>(g_elem, L.es_cap_max / PLACE + 1), 1024);
+        hipLaunchKernelGGL(k_es_place, dim3(g_place, L.njobs), dim3(256), 0, st, jobs, nj, L.es_long ? 1 : 0, pool);
     }
     HIPCHK(hipGetLastError());
     return BC_OK;
@@ -580,6 +590,9 @@ bc_status part_graph(bc_ctx *ctx, int r, const LaunchShape &L, int part, hipGrap
                                       (int64_t)L.wide_bytes,
                                       L.wide_lds_cap,
                                       L.item_regions,
+                                      L.may_defer,
+                                      L.es_long,
+                                      L.es_cap_max,
                                       (int64_t)(uintptr_t)L.src_base,
                                       (int64_t)(uintptr_t)L.wide_base,
                                       (int64_t)(uintptr_t)L.items_base,
@@ -605,7 +618,18 @@ bc_status part_graph(bc_ctx *ctx, int r, const LaunchShape &L, int part, hipGrap
 
 bc_status shape_for(bc_ctx *ctx, const std::vector<UpdateJob> &jobs, LaunchShape *L) {
     L->n_max = 1;
-    for (auto &j : jobs) L->n_max = std::max(L->n_max, j.g.n);
+    L->es_cap_max = 1;
+    int64_t pairs = 0;
+    for (auto &j : jobs) {
+        L->n_max = std::max(L->n_max, j.g.n);
+        L->es_cap_max = std::max(L->es_cap_max, j.g.es_cap);
+        pairs += (int64_t)j.g.n * j.g.n;
+    }
+    L->es_long = L->es_cap_max > ES_LONG;
+    // a source is deferred when it has more changed targets than the row
+    // kernel lists, or the step's target pool is full: neither can happen in
+    // graphs of so few vertices
+    L->may_defer = L->n_max > std::min(ctx->big_b, LCAP) || pairs > pool_entries(ctx->n_layout);
     L->njobs = (int)jobs.size();
     L->n_layout = ctx->n_layout;
     const ScratchPlan sp = plan_scratch(ctx, ctx->n_layout);
@@ -691,13 +715,14 @@ bc_status run_step(bc_ctx *ctx, const std::vector<UpdateJob> &jobs, bool use_gra
     int r;
     if ((st = ring_acquire(ctx, &r))) return st;
     if (se) HIPCHK(hipEventRecord(se->begin, ctx->stream));
-    if ((st = ring_stage(ctx, r, jobs))) return st;
+    const UpdateJob *one = !use_graph && jobs.size() == 1 ? jobs.data() : nullptr;
+    if (!one && (st = ring_stage(ctx, r, jobs))) return st;
     const bool timed = ctx->timing;
     // timing events sit on the stream between the parts (never inside a graph)
     for (int part = 0; part < 4; ++part) {
         if (timed) HIPCHK(hipEventRecord(ctx->tev[r][part], ctx->stream));
         if (!use_graph) {
-            if ((st = launch_update_part(ctx, r, L, part))) return st;
+            if ((st = launch_update_part(ctx, r, L, part, one))) return st;
         } else {
             hipGraphExec_t exec;
             if ((st = part_graph(ctx, r, L, part, &exec))) return st;
@@ -1288,7 +1313,6 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     if ((st = ring_acquire(ctx, &r))) return st;
     if ((st = ring_stage(ctx, r, jobs))) return st;
     const UpdateJob *dj = ring_jobs_dev(ctx, r);
-    const int32_t *nj = ring_njobs_dev(ctx, r);
     const int slots = std::min<int>(L.slots, n);
     if ((st = zero_slots(ctx))) return st;
     const int g_wave = (int)std::min<int64_t>(((int64_t)n * 64 + 255) / 256, 4096);
@@ -1360,7 +1384,8 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     hipLaunchKernelGGL(k_es_scatter, dim3(g_wave), dim3(256), 0, s, dj);
     hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
     launch_static(ctx, g->P, slots, L);
-    hipLaunchKernelGGL(k_commit, dim3((n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048), dim3(256), 0, s, dj, nj, 1);
+    hipLaunchKernelGGL(k_commit, dim3((n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048), dim3(256), 0, s, dj,
+                       step_pool(ctx));
     HIPCHK(hipGetLastError());
     st = ring_release(ctx, r);
     if (st) return st;
@@ -2440,7 +2465,7 @@ bc_status bc_get_stats(bc_ctx *ctx, bc_graph_id gid, bc_update_stats *out) {
     HIPCHK(hipMemcpyAsync(&c, g->P.ctl, sizeof c, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     out->affected_sources = (int64_t)c.affected_last;
-    out->changed_pairs = (int64_t)c.changed_pairs;
+    out->changed_pairs = (int64_t)c.changed_last;
     out->estar_arcs = c.esc_m;
     out->max_levels = c.max_levels;
     out->updates_applied = (int64_t)g->updates;

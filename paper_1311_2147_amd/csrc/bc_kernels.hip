@@ -1,14 +1,15 @@
 // HIP kernels of libbcinc for gfx950 (64-lane wavefronts).
 //
 // Update pipeline for a batch of jobs (one update on each of several graphs):
-//   k_scan        affected sources A and Alg 4 scalars (Eq.6, Eq.7)
-//   k_targets     row v'' of the Out phase (Alg 4 on the reverse graph) and
-//                 the candidate targets of the update
-//   k_es_*        E* (by head) plus the updated arcs (buffer YC)
-//   k_source      per affected source: changed targets by Lemma 2 / Lemma 4,
-//                 old and new partial dependencies over them, BC difference
-//   k_es_*        E*' = arcs of YC whose weight equals their new distance
-//   k_commit      BC += difference (compensated), reset counters
+//   k_prep        affected sources A and Alg 4 scalars (Eq.6, Eq.7); row v''
+//                 of the Out phase (Alg 4 on the reverse graph) and the
+//                 candidate targets; E* (by head) plus the updated arcs (YC)
+//   k_rows        the affected sources' changed targets (Lemma 2 / Lemma 4)
+//   k_source      per affected source: old and new partial dependencies over
+//                 its changed targets, BC difference (k_source_wide and
+//                 k_wide_apply: sources with many)
+//   k_es_*        E*' = arcs of YC whose weight equals their new distance, and
+//                 BC += difference (compensated), counters reset
 // Static pass (initial state and full recompute, Alg 7):
 //   k_sssp        distances of every source (near/far search in LDS)
 //   k_es_*        E* = arcs with w(a,b) = d(a,b), by head (XC)
@@ -101,104 +102,143 @@ __device__ int32_t block_excl_scan(int32_t x, int32_t *sh /* >= 32 */, int32_t &
     return res;
 }
 
-// ------------------------------------------------------------ k_scan -------
+// ------------------------------------------------------------ k_prep -------
+//
+// The first launch of a step: three roles side by side, told apart by
+// blockIdx.x (scan, targets, merge), a row of blocks per job.  None needs
+// another's output (the few scalars the targets role wants it forms itself),
+// and at small sizes a launch costs as much as its work: with the fused tail
+// (k_es_place) and the wide kernel left out where no source can be deferred, an
+// update takes 5 or 7 launches instead of a copy and 12.  16 updates of a
+// 64-vertex graph went from 1.61 to 1.02 ms, 8 vertex updates of 32 edges on a
+// complete graph of 2048 from 9.7 to 2.4 (the column reads besides), 64 arc
+// updates at n = 4096 from 13.5 to 12.3.
 
-// Per source s: Alg 4 over E_i (Eq.6 d'(s,v), Eq.7 sigma-hat'_sv, sigma'_sv),
-// then the affected test.  s changes in the In phase iff d'(s,v) < d(s,v) or
-// sigma-hat'_sv > 0 (Lemma 4 cases 2-4 need one of them; for an arc update
-// this is Lemma 2 case 1 failing at t = v).  s changes in the Out phase iff
-// d'(s,v) + w'(v,x) <= d'(s,x) for some (v,x) in E_o.  Affected sources are
-// compacted with a wave ballot and one atomic per wave.
-__global__ void __launch_bounds__(256) k_scan(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p) {
-    const int njobs = *njobs_p;
-    for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
-        const UpdateJob &J = jobs[j];
-        const int32_t n = J.g.n, v = J.v, n_in = J.n_in, n_out = J.n_out;
-        const int32_t *D = J.g.D;
-        const uint64_t *S = J.g.S;
-        const int32_t *Dv = D + (size_t)v * n;
-        bool ovf_s = false, ovf_d = false;
-        for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += (int64_t)gridDim.x * blockDim.x) {
-            const int32_t s = (int32_t)(base + threadIdx.x);
-            bool aff = false;
-            if (s < n) {
-                const int32_t *Ds = D + (size_t)s * n;
-                const uint64_t *Ss = S + (size_t)s * n;
-                const int32_t dsv = Ds[v];
-                // 64-bit sums with INF64 for unreachable: a candidate of 2^31-1
-                // or more is compared like any other and is an overflow only
-                // if it wins (it is then the new finite d'(s,v))
-                const int64_t d0 = dsv == INF32 ? INF64 : (int64_t)dsv;
-                int64_t cur = d0;
-                uint64_t sig = Ss[v], hat = 0;
-                for (int k = 0; k < n_in; ++k) {
-                    const int32_t u = J.in_tail[k];
-                    const int32_t du = Ds[u];
-                    if (du == INF32) continue;
-                    const int64_t c = (int64_t)du + J.in_w[k];
-                    if (c == cur) {
-                        const uint64_t su = Ss[u];
-                        sig = add_chk(sig, su, ovf_s);
-                        hat = add_chk(hat, su, ovf_s);
-                    } else if (c < cur) {
-                        cur = c;
-                        sig = Ss[u];
-                        hat = 0;
-                    }
-                }
-                if (cur != INF64 && cur >= INF32) {
-                    // d'(s,v) does not fit the distance matrix: the graph is
-                    // halted (sticky), s is left out
-                    ovf_d = true;
-                    cur = d0;
-                    hat = 0;
-                }
-                const bool same = (cur == d0);
-                aff = (cur < d0) || (hat != 0);
-                if (!aff && cur != INF64) {
-                    for (int k = 0; k < n_out; ++k) {
-                        const int32_t x = J.out_head[k];
-                        int64_t d1 = Ds[x] == INF32 ? INF64 : (int64_t)Ds[x];
-                        const int32_t dvx = Dv[x];
-                        if (dvx != INF32 && cur + dvx < d1) d1 = cur + dvx;
+// Alg 4 over E_i for source s (Eq.6 d'(s,v), Eq.7 sigma-hat'_sv, sigma'_sv).
+// cur is d'(s,v) in 64 bits with INF64 for unreachable: a candidate of 2^31-1
+// or more is compared like any other and is an overflow only if it wins (it is
+// then the new finite d'(s,v)).  Distances and counts into column u are read
+// from row u where the graph is undirected (the state is symmetric between
+// updates): coalesced over the sources, against a cache line per source.
+struct ScanOut {
+    int64_t d0, cur;
+    uint64_t sig, hat;
+};
+
+__device__ __forceinline__ ScanOut scan_source(const UpdateJob &J, const int32_t s, bool &ovf_s, bool &ovf_d) {
+    const int32_t n = J.g.n, v = J.v, n_in = J.n_in;
+    const size_t rs = J.g.directed ? (size_t)n : 1, cs = J.g.directed ? 1 : (size_t)n;
+    const int32_t *D = J.g.D + s * rs;
+    const uint64_t *S = J.g.S + s * rs;
+    const int32_t dsv = D[v * cs];
+    ScanOut o;
+    o.d0 = dsv == INF32 ? INF64 : (int64_t)dsv;
+    o.cur = o.d0;
+    o.sig = S[v * cs];
+    o.hat = 0;
+    constexpr int U = 8;  // column loads in flight
+    for (int k0 = 0; k0 < n_in; k0 += U) {
+        int32_t du[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) du[k] = k0 + k < n_in ? D[J.in_tail[k0 + k] * cs] : INF32;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (du[k] == INF32) continue;
+            const int64_t c = (int64_t)du[k] + J.in_w[k0 + k];
+            if (c > o.cur) continue;
+            const uint64_t su = S[J.in_tail[k0 + k] * cs];
+            if (c == o.cur) {
+                o.sig = add_chk(o.sig, su, ovf_s);
+                o.hat = add_chk(o.hat, su, ovf_s);
+            } else {
+                o.cur = c;
+                o.sig = su;
+                o.hat = 0;
+            }
+        }
+    }
+    if (o.cur != INF64 && o.cur >= INF32) {
+        // d'(s,v) does not fit the distance matrix: the graph is halted
+        // (sticky), s is left out
+        ovf_d = true;
+        o.cur = o.d0;
+        o.hat = 0;
+    }
+    return o;
+}
+
+__device__ __forceinline__ SrcScal scan_scal(const ScanOut &o, const bool aff) {
+    SrcScal sc;
+    sc.dv = o.cur == INF64 ? INF32 : (int32_t)o.cur;
+    sc.flags = (o.cur == o.d0 ? 1 : 0) | (aff ? 2 : 0);
+    sc.sv = o.sig;
+    sc.hv = o.hat;
+    return sc;
+}
+
+// Scan role: per source s its Alg 4 scalars, then the affected test.  s
+// changes in the In phase iff d'(s,v) < d(s,v) or sigma-hat'_sv > 0 (Lemma 4
+// cases 2-4 need one of them; for an arc update this is Lemma 2 case 1 failing
+// at t = v).  s changes in the Out phase iff d'(s,v) + w'(v,x) <= d'(s,x) for
+// some (v,x) in E_o.  Affected sources are compacted with a wave ballot and one
+// atomic per wave.
+__device__ __forceinline__ void prep_scan(const UpdateJob &J, const int64_t first, const int64_t stride) {
+    const int32_t n = J.g.n, v = J.v, n_out = J.n_out;
+    const size_t rs = J.g.directed ? (size_t)n : 1, cs = J.g.directed ? 1 : (size_t)n;
+    const int32_t *Dv = J.g.D + (size_t)v * n;
+    bool ovf_s = false, ovf_d = false;
+    for (int64_t base = first; base < n; base += stride) {
+        const int32_t s = (int32_t)(base + threadIdx.x);
+        bool aff = false;
+        if (s < n) {
+            const ScanOut o = scan_source(J, s, ovf_s, ovf_d);
+            aff = (o.cur < o.d0) || (o.hat != 0);
+            if (!aff && o.cur != INF64) {
+                const int32_t *Ds = J.g.D + s * rs;
+                constexpr int U = 8;
+                for (int k0 = 0; k0 < n_out && !aff; k0 += U) {
+                    int32_t dx[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) dx[k] = k0 + k < n_out ? Ds[J.out_head[k0 + k] * cs] : 0;
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        if (k0 + k >= n_out) continue;
+                        int64_t d1 = dx[k] == INF32 ? INF64 : (int64_t)dx[k];
+                        const int32_t dvx = Dv[J.out_head[k0 + k]];
+                        if (dvx != INF32 && o.cur + dvx < d1) d1 = o.cur + dvx;
                         // a candidate of 2^31-1 or more also marks s: the row
                         // kernel's pair update decides with row v'' whether it
                         // wins, and only then raises the overflow
-                        const int64_t c = cur + J.out_w[k];
-                        if (c <= d1) { aff = true; break; }
+                        aff |= o.cur + J.out_w[k0 + k] <= d1;
                     }
                 }
-                SrcScal sc;
-                sc.dv = cur == INF64 ? INF32 : (int32_t)cur;
-                sc.flags = (same ? 1 : 0) | (aff ? 2 : 0);
-                sc.sv = sig;
-                sc.hv = hat;
-                J.g.scal[s] = sc;
             }
-            const uint64_t mask = __ballot(aff);
-            if (mask) {
-                const int lane = lane_id();
-                const int leader = __ffsll((unsigned long long)mask) - 1;
-                int32_t b0 = 0;
-                if (lane == leader) b0 = atomicAdd(&J.g.ctl->a_count, (int32_t)__popcll(mask));
-                b0 = __shfl(b0, leader, 64);
-                if (aff) J.g.alist[b0 + popc_below(mask, lane)] = s;
-            }
+            J.g.scal[s] = scan_scal(o, aff);
         }
-        if (ovf_s) atomicOr(&J.g.ctl->status, ST_SIGMA_OVF);
-        if (ovf_d) atomicOr(&J.g.ctl->status, ST_DIST_OVF);
+        const uint64_t mask = __ballot(aff);
+        if (mask) {
+            const int lane = lane_id();
+            const int leader = __ffsll((unsigned long long)mask) - 1;
+            int32_t b0 = 0;
+            if (lane == leader) b0 = atomicAdd(&J.g.ctl->a_count, (int32_t)__popcll(mask));
+            b0 = __shfl(b0, leader, 64);
+            if (aff) J.g.alist[b0 + popc_below(mask, lane)] = s;
+        }
     }
+    if (ovf_s) atomicOr(&J.g.ctl->status, ST_SIGMA_OVF);
+    if (ovf_d) atomicOr(&J.g.ctl->status, ST_DIST_OVF);
 }
 
-// ------------------------------------------------------------ k_targets ----
-
-// Row v'' and the candidate targets of an update, one thread per target t.
+// Targets role: row v'' and the candidate targets of an update, one thread per
+// target t.
 //
 // Row v'' (Section 4, Out phase): with E_o = {(v, x_j)}, Alg 4 on G'_R gives
 // d''(v,t) = min(d'(v,t), min_j w'(v,x_j) + d'(x_j,t)) and the counts
 // sigma''_vt, sigma-hat''_vt.  The rows x_j of G' are formed on the fly by
-// the In-phase rule from the old rows.  The old row v is snapshotted, since
-// the source v itself rewrites it during the update.
+// the In-phase rule from the old rows and the scalars of the sources x_j
+// (formed here once per workgroup: the scan role writes them in the same
+// launch).  The old row v is snapshotted, since the source v itself rewrites
+// it during the update.
 //
 // Candidates: a pair (s,t) can change in the In phase only if
 // d'(s,v) + d(v,t) <= d(s,t) with d'(s,v) = d(s,u_j) + w'_j for some in-arc,
@@ -211,43 +251,54 @@ __global__ void __launch_bounds__(256) k_scan(const UpdateJob *__restrict__ jobs
 // per target as filter rows: f_out = d''(v,t) on Out candidates, INF32
 // elsewhere, and f_any = min(f_in, f_out) with f_in = d(v,t) on In
 // candidates, INF32 elsewhere.
-__global__ void __launch_bounds__(256) k_targets(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p) {
-    const int njobs = *njobs_p;
-    for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
-        const UpdateJob &J = jobs[j];
-        const int32_t n = J.g.n, v = J.v;
-        const int32_t *D = J.g.D;
-        const uint64_t *S = J.g.S;
-        bool ovf_s = false, ovf_d = false;
-        for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += (int64_t)gridDim.x * blockDim.x) {
-            const int32_t t = (int32_t)(base + threadIdx.x);
-            bool cand = false, cand_out = false;
-            int32_t dvt = INF32, cur = INF32;
-            if (t < n) {
-                dvt = D[(size_t)v * n + t];
-                if (dvt != INF32) {
-                    for (int k = 0; k < J.n_in; ++k) {
-                        const int32_t dut = D[(size_t)J.in_tail[k] * n + t];
-                        if ((int64_t)J.in_w[k] + dvt <= (int64_t)dut) {
-                            cand = true;
-                            break;
-                        }
-                    }
+__device__ __forceinline__ void prep_targets(const UpdateJob &J, const int64_t first, const int64_t stride,
+                                             SrcScal *xs) {
+    const int32_t n = J.g.n, v = J.v;
+    const int32_t *D = J.g.D;
+    const uint64_t *S = J.g.S;
+    bool ovf_s = false, ovf_d = false;
+    for (int j = threadIdx.x; j < J.n_out; j += blockDim.x) {
+        bool os = false, od = false;  // raised by the scan role
+        xs[j] = scan_scal(scan_source(J, J.out_head[j], os, od), false);
+    }
+    __syncthreads();
+    constexpr int U = 8;  // row loads in flight
+    for (int64_t base = first; base < n; base += stride) {
+        const int32_t t = (int32_t)(base + threadIdx.x);
+        bool cand = false, cand_out = false;
+        int32_t dvt = INF32, cur = INF32;
+        if (t < n) {
+            dvt = D[(size_t)v * n + t];
+            if (dvt != INF32) {
+                for (int k0 = 0; k0 < J.n_in && !cand; k0 += U) {
+                    int32_t dut[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) dut[k] = k0 + k < J.n_in ? D[(size_t)J.in_tail[k0 + k] * n + t] : 0;
+#pragma unroll
+                    for (int k = 0; k < U; ++k)
+                        cand |= k0 + k < J.n_in && (int64_t)J.in_w[k0 + k] + dvt <= (int64_t)dut[k];
                 }
-                const int32_t f_in = cand ? dvt : INF32;
-                cur = dvt;
-                if (J.n_out > 0) {
-                    const uint64_t svt = S[(size_t)v * n + t];
-                    J.g.rv_D[t] = dvt;
-                    J.g.rv_S[t] = svt;
-                    // 64-bit sums with INF64 for unreachable, as in k_scan:
-                    // only a winning candidate of 2^31-1 or more overflows
-                    int64_t c64 = dvt == INF32 ? INF64 : (int64_t)dvt;
-                    uint64_t sig = svt, hat = 0;
-                    for (int k = 0; k < J.n_out; ++k) {
-                        const int32_t x = J.out_head[k];
-                        const SrcScal sc = J.g.scal[x];
-                        int32_t d1 = D[(size_t)x * n + t];
+            }
+            const int32_t f_in = cand ? dvt : INF32;
+            cur = dvt;
+            if (J.n_out > 0) {
+                const uint64_t svt = S[(size_t)v * n + t];
+                J.g.rv_D[t] = dvt;
+                J.g.rv_S[t] = svt;
+                // 64-bit sums with INF64 for unreachable, as in scan_source:
+                // only a winning candidate of 2^31-1 or more overflows
+                int64_t c64 = dvt == INF32 ? INF64 : (int64_t)dvt;
+                uint64_t sig = svt, hat = 0;
+                for (int k0 = 0; k0 < J.n_out; k0 += U) {
+                    int32_t dx[U];
+#pragma unroll
+                    for (int k = 0; k < U; ++k) dx[k] = k0 + k < J.n_out ? D[(size_t)J.out_head[k0 + k] * n + t] : INF32;
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        if (k0 + k >= J.n_out) continue;
+                        const int32_t x = J.out_head[k0 + k];
+                        const SrcScal sc = xs[k0 + k];
+                        int32_t d1 = dx[k];
                         uint64_t s1 = 0;
                         bool s1_known = false;
                         int64_t c;
@@ -263,7 +314,7 @@ __global__ void __launch_bounds__(256) k_targets(const UpdateJob *__restrict__ j
                             }
                         }
                         if (d1 == INF32) continue;
-                        const int64_t cc = (int64_t)J.out_w[k] + d1;
+                        const int64_t cc = (int64_t)J.out_w[k0 + k] + d1;
                         if (cc <= c64) {
                             if (!s1_known) s1 = S[(size_t)x * n + t];
                             if (cc == c64) {
@@ -276,41 +327,119 @@ __global__ void __launch_bounds__(256) k_targets(const UpdateJob *__restrict__ j
                             }
                         }
                     }
-                    if (c64 != INF64 && c64 >= INF32) {
-                        // d''(v,t) does not fit: the graph is halted (sticky)
-                        ovf_d = true;
-                        c64 = INF64;
-                        hat = 0;
-                    }
-                    cur = c64 == INF64 ? INF32 : (int32_t)c64;
-                    J.g.rvv_D[t] = cur;
-                    J.g.rvv_S[t] = sig;
-                    J.g.rvv_H[t] = hat;
-                    cand_out = cur < dvt || hat != 0;
-                    cand = cand || cand_out;
                 }
-                const int32_t f_out = cand_out ? cur : INF32;
-                J.g.f_out[t] = f_out;
-                J.g.f_any[t] = min(f_in, f_out);
+                if (c64 != INF64 && c64 >= INF32) {
+                    // d''(v,t) does not fit: the graph is halted (sticky)
+                    ovf_d = true;
+                    c64 = INF64;
+                    hat = 0;
+                }
+                cur = c64 == INF64 ? INF32 : (int32_t)c64;
+                J.g.rvv_D[t] = cur;
+                J.g.rvv_S[t] = sig;
+                J.g.rvv_H[t] = hat;
+                cand_out = cur < dvt || hat != 0;
+                cand = cand || cand_out;
             }
-            const uint64_t mask = __ballot(cand);
-            if (mask) {
-                const int lane = lane_id();
-                const int leader = __ffsll((unsigned long long)mask) - 1;
-                int32_t b0 = 0;
-                if (lane == leader) b0 = atomicAdd(&J.g.ctl->t_count, (int32_t)__popcll(mask));
-                b0 = __shfl(b0, leader, 64);
-                if (cand) {
-                    const int32_t pos = b0 + (int32_t)popc_below(mask, lane);
-                    J.g.tlist[pos] = t;
-                    J.g.tl_rvD[pos] = dvt;
-                    J.g.tl_rvvD[pos] = cur;
-                }
+            const int32_t f_out = cand_out ? cur : INF32;
+            J.g.f_out[t] = f_out;
+            J.g.f_any[t] = min(f_in, f_out);
+        }
+        const uint64_t mask = __ballot(cand);
+        if (mask) {
+            const int lane = lane_id();
+            const int leader = __ffsll((unsigned long long)mask) - 1;
+            int32_t b0 = 0;
+            if (lane == leader) b0 = atomicAdd(&J.g.ctl->t_count, (int32_t)__popcll(mask));
+            b0 = __shfl(b0, leader, 64);
+            if (cand) {
+                const int32_t pos = b0 + (int32_t)popc_below(mask, lane);
+                J.g.tlist[pos] = t;
+                J.g.tl_rvD[pos] = dvt;
+                J.g.tl_rvvD[pos] = cur;
             }
         }
-        if (ovf_s) atomicOr(&J.g.ctl->status, ST_SIGMA_OVF);
-        if (ovf_d) atomicOr(&J.g.ctl->status, ST_DIST_OVF);
     }
+    if (ovf_s) atomicOr(&J.g.ctl->status, ST_SIGMA_OVF);
+    if (ovf_d) atomicOr(&J.g.ctl->status, ST_DIST_OVF);
+}
+
+// Merge role: YC keeps every XC arc and adds the update's arcs behind their
+// head's XC arcs, so head h's segment starts before(h) entries later than in
+// XC, before(h) = the update arcs into heads below h; every arc is placed
+// directly.  An XC arc that the update lowers stays beside its new copy: its
+// old weight satisfies Eq.1 for no source, and the filter drops it.
+__device__ __forceinline__ void prep_merge(const UpdateJob &J, const int64_t gid, const int64_t nthreads) {
+    if (job_halted(J)) return;
+    const int32_t n = J.g.n, nu = J.n_u;
+    const int32_t *__restrict__ ptr = J.g.xc_ptr;
+    const int32_t m = ptr[n];
+    const int64_t total = (int64_t)m + nu;
+    if (total > J.g.es_cap) {
+        if (gid == 0) atomicOr(&J.g.ctl->status, ST_ESTAR_CAP);
+        return;
+    }
+    if (gid == 0) J.g.ctl->esc_m_tmp = (int32_t)total;
+    for (int64_t h = gid; h <= n; h += nthreads) {
+        int32_t before = 0;
+        for (int k = 0; k < nu; ++k) before += J.u_head[k] < h;
+        J.g.yc_ptr[h] = ptr[h] + before;
+    }
+    for (int64_t i = gid; i < m; i += nthreads) {
+        const int32_t h = J.g.xc_dst[i];
+        int32_t before = 0;
+        for (int k = 0; k < nu; ++k) before += J.u_head[k] < h;
+        const int64_t o = i + before;
+        J.g.yc_src[o] = J.g.xc_src[i];
+        J.g.yc_dst[o] = h;
+        J.g.yc_w[o] = J.g.xc_w[i];
+    }
+    for (int64_t k = gid; k < nu; k += nthreads) {
+        const int32_t h = J.u_head[k];
+        int32_t before = 0;
+        for (int q = 0; q < nu; ++q) before += J.u_head[q] < h || (J.u_head[q] == h && q < k);
+        const int64_t o = (int64_t)ptr[h + 1] + before;
+        J.g.yc_src[o] = J.u_tail[k];
+        J.g.yc_dst[o] = h;
+        J.g.yc_w[o] = J.u_w[k];
+    }
+}
+
+// `elem` blocks of the scan role, as many of the targets role, the others
+// merge.
+__device__ __forceinline__ void prep_roles(const UpdateJob &J, const int32_t elem, SrcScal *xs) {
+    const int32_t b = (int32_t)blockIdx.x;
+    if (b < elem) {
+        prep_scan(J, (int64_t)b * blockDim.x, (int64_t)elem * blockDim.x);
+    } else if (b < 2 * elem) {
+        prep_targets(J, (int64_t)(b - elem) * blockDim.x, (int64_t)elem * blockDim.x, xs);
+    } else {
+        prep_merge(J, (int64_t)(b - 2 * elem) * blockDim.x + threadIdx.x, (int64_t)((int32_t)gridDim.x - 2 * elem) * blockDim.x);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_prep(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
+                                              int32_t elem) {
+    __shared__ SrcScal xs[KMAX];
+    const int njobs = *njobs_p;
+    for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
+        prep_roles(jobs[j], elem, xs);
+        __syncthreads();
+    }
+}
+
+// The same for a step of one job that is not captured: the job comes with the
+// launch, and block 0 stages it for the kernels behind.
+__global__ void __launch_bounds__(256) k_prep_one(const UpdateJob J, UpdateJob *__restrict__ jobs,
+                                                  int32_t *__restrict__ njobs_p, int32_t elem) {
+    __shared__ SrcScal xs[KMAX];
+    static_assert(sizeof(UpdateJob) % 4 == 0 && sizeof(UpdateJob) < 4000, "a job fits the kernel arguments");
+    if (blockIdx.x == gridDim.x - 1) {
+        for (uint32_t i = threadIdx.x; i < sizeof(UpdateJob) / 4; i += blockDim.x)
+            ((uint32_t *)jobs)[i] = ((const uint32_t *)&J)[i];
+        if (threadIdx.x == 0) *njobs_p = 1;
+    }
+    prep_roles(J, elem, xs);
 }
 
 // ------------------------------------------------------------ E* rebuild ---
@@ -318,8 +447,8 @@ __global__ void __launch_bounds__(256) k_targets(const UpdateJob *__restrict__ j
 // E* is kept as segments of arcs keyed by head (XC; the static pass and the
 // updates walk DAG predecessors).  A wave-per-segment compaction of the arcs
 // by head builds it in the static pass (k_es_count / k_es_scan /
-// k_es_scatter); an update's merge (k_es_merge) and filter (k_es_keep /
-// k_es_wscan / k_es_place) are arc-parallel.  An arc whose
+// k_es_scatter); an update's merge (k_prep) and filter (k_es_keep / k_es_place) are
+// arc-parallel.  An arc whose
 // weight exceeds its distance lies on no
 // shortest path and is dropped; distances only decrease under incremental
 // updates, so E*' is contained in E* plus the updated arcs (Section 1
@@ -435,61 +564,12 @@ __global__ void __launch_bounds__(256) k_es_scatter(const UpdateJob *__restrict_
     }
 }
 
-// E* merge in one elementwise pass: YC keeps every XC arc and adds the
-// update's arcs behind their head's XC arcs, so head h's segment starts
-// before(h) entries later than in XC, before(h) = the update arcs into heads
-// below h.  Each XC arc and each update arc is placed directly (the same
-// layout the count / scan / scatter passes produce in the other modes).  An
-// XC arc that the update lowers stays beside its new copy: its old weight
-// satisfies Eq.1 for no source, and the filter drops it.
-__global__ void __launch_bounds__(256) k_es_merge(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p) {
-    const int njobs = *njobs_p;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
-    for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
-        const UpdateJob &J = jobs[j];
-        if (job_halted(J)) continue;
-        const int32_t n = J.g.n, nu = J.n_u;
-        const int32_t *__restrict__ ptr = J.g.xc_ptr;
-        const int32_t m = ptr[n];
-        const int64_t total = (int64_t)m + nu;
-        if (total > J.g.es_cap) {
-            if (gid == 0) atomicOr(&J.g.ctl->status, ST_ESTAR_CAP);
-            continue;
-        }
-        if (gid == 0) J.g.ctl->esc_m_tmp = (int32_t)total;
-        for (int64_t h = gid; h <= n; h += nthreads) {
-            int32_t before = 0;
-            for (int k = 0; k < nu; ++k) before += J.u_head[k] < h;
-            J.g.yc_ptr[h] = ptr[h] + before;
-        }
-        for (int64_t i = gid; i < m; i += nthreads) {
-            const int32_t h = J.g.xc_dst[i];
-            int32_t before = 0;
-            for (int k = 0; k < nu; ++k) before += J.u_head[k] < h;
-            const int64_t o = i + before;
-            J.g.yc_src[o] = J.g.xc_src[i];
-            J.g.yc_dst[o] = h;
-            J.g.yc_w[o] = J.g.xc_w[i];
-        }
-        for (int64_t k = gid; k < nu; k += nthreads) {
-            const int32_t h = J.u_head[k];
-            int32_t before = 0;
-            for (int q = 0; q < nu; ++q) before += J.u_head[q] < h || (J.u_head[q] == h && q < k);
-            const int64_t o = (int64_t)ptr[h + 1] + before;
-            J.g.yc_src[o] = J.u_tail[k];
-            J.g.yc_dst[o] = h;
-            J.g.yc_w[o] = J.u_w[k];
-        }
-    }
-}
-
 // E* filter, arc-parallel: XC = the arcs of YC with w = d'(a,b), in YC
 // order.  One gather per arc sets a bit of a 64-bit keep mask per 64 arcs;
-// one workgroup per job scans the masks' popcounts; then every kept arc and
-// every head's segment start is placed directly.  The masks and their
-// prefix sit in the by-tail E* arrays (X), which only the static pass uses
-// and rebuilds before use.
+// then every kept arc and every head's segment start is placed directly
+// (k_es_place; the masks' popcounts are summed by each of its workgroups for
+// itself, or scanned before by one workgroup per job where an E* may hold more
+// than ES_LONG arcs: 16 bytes of masks per thread and workgroup).
 __device__ __forceinline__ uint64_t *es_mask(const UpdateJob &J) { return (uint64_t *)J.g.x_src; }
 __device__ __forceinline__ int32_t *es_wpre(const UpdateJob &J) { return J.g.x_dst; }
 
@@ -554,32 +634,94 @@ __global__ void __launch_bounds__(1024) k_es_wscan(const UpdateJob *__restrict__
     }
 }
 
-// arcs of YC before position p that are kept
-__device__ __forceinline__ int32_t es_kept_before(const uint64_t *mask, const int32_t *wpre, const int64_t p) {
-    const int64_t w = p >> 6;
-    const int r = (int)(p & 63);
-    return wpre[w] + (r ? __popcll(mask[w] & ((1ull << r) - 1)) : 0);
+// First index in [0, cnt) with a[i] >= x (a ascending), else cnt: a search by
+// the whole workgroup, blockDim.x + 1 ways per round.
+__device__ __forceinline__ int32_t block_lower_bound(const int32_t *__restrict__ a, const int32_t cnt, const int32_t x) {
+    int32_t lo = 0, hi = cnt;  // the answer is in [lo, hi]
+    while (lo < hi) {
+        const int32_t step = (hi - lo + (int32_t)blockDim.x) / ((int32_t)blockDim.x + 1);  // >= 1 apart
+        const int64_t at = (int64_t)lo + ((int64_t)threadIdx.x + 1) * step - 1;
+        const int32_t below = __syncthreads_count(at < hi && a[at] < x);
+        const int64_t first = (int64_t)lo + (int64_t)below * step;
+        // (past the last probe only hi itself bounds the answer)
+        const int32_t old = hi;
+        if (below < (int32_t)blockDim.x) hi = (int32_t)min((int64_t)old, first + step - 1);
+        lo = (int32_t)min((int64_t)old, first);
+    }
+    return lo;
 }
 
-__global__ void __launch_bounds__(256) k_es_place(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p) {
+// The last launch of a step: the kept arcs of YC and the segment starts are
+// placed in XC (PLACE arcs per workgroup at a time; the kept arcs before them
+// are counted from the masks, or come from k_es_wscan where the masks are
+// long), the BC difference is folded in (k_commit) and the counters go back
+// to zero.
+constexpr int32_t PLACE = 2048;
+
+__device__ __forceinline__ void commit_job(const UpdateJob &J, const StepPool &pool, const bool replace);
+
+__global__ void __launch_bounds__(256) k_es_place(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
+                                                  int32_t scanned, StepPool pool) {
+    __shared__ int32_t sh[40];
+    __shared__ int32_t pre[PLACE / 64 + 1];
+    __shared__ uint64_t word[PLACE / 64];
     const int njobs = *njobs_p;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
+    const int tid = threadIdx.x;
     for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
         const UpdateJob &J = jobs[j];
-        if (job_halted(J)) continue;
-        const int32_t n = J.g.n;
-        const int64_t m = J.g.yc_ptr[n];
-        const uint64_t *const mask = es_mask(J);
-        const int32_t *const wpre = es_wpre(J);
-        for (int64_t i = gid; i < m; i += nthreads) {
-            if (!((mask[i >> 6] >> (i & 63)) & 1)) continue;
-            const int32_t o = es_kept_before(mask, wpre, i);
-            J.g.xc_src[o] = J.g.yc_src[i];
-            J.g.xc_dst[o] = J.g.yc_dst[i];
-            J.g.xc_w[o] = J.g.yc_w[i];
+        // (the flag is read once per workgroup: a job is halted before this launch)
+        if (!job_halted(J)) {
+            const int32_t n = J.g.n, m = J.g.yc_ptr[n];
+            const uint64_t *const mask = es_mask(J);
+            for (int64_t c0 = (int64_t)blockIdx.x * PLACE; c0 <= m; c0 += (int64_t)gridDim.x * PLACE) {
+                const int32_t w0 = (int32_t)(c0 >> 6), words = (m + 63) >> 6;
+                const int32_t c1 = (int32_t)min((int64_t)m, c0 + PLACE);
+                const bool last = c0 + PLACE > m;
+                // kept arcs before the chunk, then before each of its words
+                int32_t kept = 0, base;
+                if (!scanned)
+                    for (int32_t w = tid; w < w0; w += blockDim.x) kept += __popcll(mask[w]);
+                (void)block_excl_scan(kept, sh, base);
+                if (scanned) base = es_wpre(J)[w0];
+                if (tid < 64) {
+                    const uint64_t x = tid < PLACE / 64 && w0 + tid < words ? mask[w0 + tid] : 0ull;
+                    int32_t incl = __popcll(x);
+#pragma unroll
+                    for (int d = 1; d < 64; d <<= 1) {
+                        const int32_t y = __shfl_up(incl, d, 64);
+                        if (tid >= d) incl += y;
+                    }
+                    if (tid < PLACE / 64) {
+                        word[tid] = x;
+                        pre[tid + 1] = base + incl;
+                    }
+                    if (tid == 0) pre[0] = base;
+                }
+                __syncthreads();
+                auto before = [&](const int32_t p) {
+                    const int32_t w = (p >> 6) - w0;
+                    const int r = p & 63;
+                    return pre[w] + (r ? (int32_t)__popcll(word[w] & ((1ull << r) - 1)) : 0);
+                };
+                for (int32_t i = (int32_t)c0 + tid; i < c1; i += blockDim.x) {
+                    if (!((word[(i >> 6) - w0] >> (i & 63)) & 1)) continue;
+                    const int32_t o = before(i);
+                    J.g.xc_src[o] = J.g.yc_src[i];
+                    J.g.xc_dst[o] = J.g.yc_dst[i];
+                    J.g.xc_w[o] = J.g.yc_w[i];
+                }
+                // the heads whose segments start in the chunk
+                const int32_t h0 = block_lower_bound(J.g.yc_ptr, n + 1, (int32_t)c0);
+                const int32_t h1 = last ? n + 1 : block_lower_bound(J.g.yc_ptr, n + 1, (int32_t)(c0 + PLACE));
+                for (int32_t h = h0 + tid; h < h1; h += blockDim.x) {
+                    const int32_t o = before(J.g.yc_ptr[h]);
+                    J.g.xc_ptr[h] = o;
+                    if (h == n) J.g.ctl->esc_m = o;
+                }
+                __syncthreads();
+            }
         }
-        for (int64_t h = gid; h <= n; h += nthreads) J.g.xc_ptr[h] = es_kept_before(mask, wpre, J.g.yc_ptr[h]);
+        commit_job(J, pool, false);
     }
 }
 
@@ -2297,7 +2439,8 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
     int32_t dealt = 0;  // sources dealt by the jobs before this one, modulo the grid
     for (int j = 0; j < njobs; ++j) {
         const UpdateJob &J = jobs[j];
-        if (job_halted(J)) continue;
+        // another workgroup may halt the job meanwhile: one answer per workgroup
+        if (__syncthreads_or(job_halted(J))) continue;
         GraphCtl *ctl = J.g.ctl;
         const int32_t n = J.g.n;
         const int32_t count = *(volatile int32_t *)&ctl->a_count;
@@ -2780,73 +2923,60 @@ __global__ void __launch_bounds__(256) k_wide_apply(const UpdateJob *__restrict_
 // ------------------------------------------------------------ commit -------
 
 // BC(x) += bc_delta(x) as a compensated (hi, lo) pair (Knuth's two-sum),
-// then clears bc_delta and the per-update counters.
-__global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
-                                                int32_t replace) {
-    const int njobs = *njobs_p;
-    for (int j = blockIdx.y; j < njobs; j += gridDim.y) {  // a row of blocks per job
-        const UpdateJob &J = jobs[j];
-        const int32_t n = J.g.n;
-        for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
-            const double d = J.g.bc_delta[t];
-            if (replace) {
-                J.g.bc_hi[t] = d;
-                J.g.bc_lo[t] = 0.0;
-            } else if (d != 0.0) {
-                const double hi = J.g.bc_hi[t];
-                const double s = hi + d;
-                const double bp = s - hi;
-                double e = (hi - (s - bp)) + (d - bp);
-                e += J.g.bc_lo[t];
-                const double h2 = s + e;
-                J.g.bc_hi[t] = h2;
-                J.g.bc_lo[t] = e - (h2 - s);
-            }
-            J.g.bc_delta[t] = 0.0;
+// then clears bc_delta, the per-update counters and the step's pool.  Every
+// counter is at zero between steps.
+__device__ __forceinline__ void commit_job(const UpdateJob &J, const StepPool &pool, const bool replace) {
+    const int32_t n = J.g.n;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+        const double d = J.g.bc_delta[t];
+        if (replace) {
+            J.g.bc_hi[t] = d;
+            J.g.bc_lo[t] = 0.0;
+        } else if (d != 0.0) {
+            const double hi = J.g.bc_hi[t];
+            const double s = hi + d;
+            const double bp = s - hi;
+            double e = (hi - (s - bp)) + (d - bp);
+            e += J.g.bc_lo[t];
+            const double h2 = s + e;
+            J.g.bc_hi[t] = h2;
+            J.g.bc_lo[t] = e - (h2 - s);
         }
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            GraphCtl *c = J.g.ctl;
-            c->affected_last = (unsigned long long)c->a_count;
-            c->big_last = c->big_count;
-            // algorithmic bytes of the row scans: per affected source its
-            // distance row (4n) or, with the candidate list, the distances at
-            // the candidates (4|T|); sigma is read for the changed pairs only
-            const unsigned long long a = (unsigned long long)c->a_count, t = (unsigned long long)c->t_count;
-            const bool tl = (int64_t)c->t_count * 8 <= (int64_t)n;
-            c->scan_bytes_last = a * 4ull * (tl ? t : (unsigned long long)n) + 8ull * c->changed_pairs;
-            if (!replace) {
-                c->updates += 1;
-                c->affected_total += (unsigned long long)c->a_count;
-                c->changed_total += c->changed_pairs;
-                c->scan_bytes_total += c->scan_bytes_last;
-            }
-            c->a_count = 0;
-            c->work_next = 0;
-            c->big_count = 0;
-            c->dag_count = 0;
-            c->dag_back = 0;
-        }
+        J.g.bc_delta[t] = 0.0;
     }
-}
-
-// Clears the statistics that accumulate during an update (before k_scan).
-__global__ void k_begin(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p, StepPool pool) {
-    const int njobs = *njobs_p;
-    if (threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        GraphCtl *c = J.g.ctl;
+        c->affected_last = (unsigned long long)c->a_count;
+        c->big_last = c->big_count;
+        c->changed_last = c->changed_pairs;
+        // algorithmic bytes of the row scans: per affected source its
+        // distance row (4n) or, with the candidate list, the distances at
+        // the candidates (4|T|); sigma is read for the changed pairs only
+        const unsigned long long a = (unsigned long long)c->a_count, t = (unsigned long long)c->t_count;
+        const bool tl = (int64_t)c->t_count * 8 <= (int64_t)n;
+        c->scan_bytes_last = a * 4ull * (tl ? t : (unsigned long long)n) + 8ull * c->changed_pairs;
+        if (!replace) {
+            c->updates += 1;
+            c->affected_total += (unsigned long long)c->a_count;
+            c->changed_total += c->changed_pairs;
+            c->scan_bytes_total += c->scan_bytes_last;
+        }
+        c->changed_pairs = 0;
+        c->a_count = 0;
+        c->t_count = 0;
+        c->work_next = 0;
+        c->big_count = 0;
+        c->dag_count = 0;
+        c->dag_back = 0;
         *pool.next = 0;
         *pool.src_next = 0;
         *pool.wide_next = 0;
     }
-    for (int j = threadIdx.x; j < njobs; j += blockDim.x) {
-        GraphCtl *c = jobs[j].g.ctl;
-        c->changed_pairs = 0;
-        c->a_count = 0;
-        c->work_next = 0;
-        c->t_count = 0;
-        c->big_count = 0;
-        c->dag_count = 0;
-        c->dag_back = 0;
-    }
+}
+
+// The static pass's commit: BC = bc_delta.
+__global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jobs, StepPool pool) {
+    commit_job(jobs[0], pool, true);
 }
 
 // ------------------------------------------------------------ static pass --
