@@ -15,6 +15,7 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <memory>
 #include <set>
 #include <mutex>
 #include <tuple>
@@ -68,67 +69,82 @@ void *fixed_addr[FIXED_MAX_DEVICES] = {};  // per device, resolved once
 size_t ring_slot_bytes() { return align256(256 + sizeof(UpdateJob) * JCAP); }
 size_t ring_bytes() { return RING * ring_slot_bytes(); }
 
+// An arc set by tail (heads ascending within a tail).
+struct ArcCsr {
+    std::vector<int32_t> ptr;
+    std::vector<ArcW> arc;
+    int64_t size() const { return (int64_t)arc.size(); }
+    // place of (a,b), or -1
+    int64_t find(int32_t a, int32_t b) const {
+        auto first = arc.begin() + ptr[a], last = arc.begin() + ptr[a + 1];
+        auto it = std::lower_bound(first, last, b, [](const ArcW &x, int32_t v) { return x.v < v; });
+        return it != last && it->v == b ? it - arc.begin() : -1;
+    }
+};
+
+// Arcs of G (G_D when undirected): a CSR, which a graph and its clones share
+// (a clone of a complete graph of 2048 vertices would copy 33 MB), the new
+// weights of its arcs while it is shared, and the arcs inserted since the last
+// rebuild.
 struct Mirror {
-    // Arcs of G (G_D when undirected) as a CSR by tail, heads sorted, plus an
-    // overlay of arcs inserted since the last rebuild.
     int32_t n = 0;
-    std::vector<int64_t> ptr;
-    std::vector<int32_t> dst;
-    std::vector<int32_t> w;
-    std::unordered_map<uint64_t, int32_t> extra;
+    std::shared_ptr<ArcCsr> base;
+    std::unordered_map<uint64_t, int32_t> over;   // arcs of base with another weight
+    std::unordered_map<uint64_t, int32_t> extra;  // arcs not in base
     int64_t arcs = 0;
 
     uint64_t key(int32_t a, int32_t b) const { return (uint64_t)a * (uint64_t)n + (uint64_t)b; }
 
     // current weight of (a,b), or -1 when absent
     int64_t find(int32_t a, int32_t b) const {
-        auto first = dst.begin() + ptr[a], last = dst.begin() + ptr[a + 1];
-        auto it = std::lower_bound(first, last, b);
-        if (it != last && *it == b) return w[it - dst.begin()];
-        auto e = extra.find(key(a, b));
-        return e == extra.end() ? -1 : e->second;
+        const int64_t at = base->find(a, b);
+        const auto &map = at >= 0 ? over : extra;
+        if (!map.empty()) {
+            auto e = map.find(key(a, b));
+            if (e != map.end()) return e->second;
+        }
+        return at >= 0 ? base->arc[at].w : -1;
     }
 
     void set(int32_t a, int32_t b, int32_t wt) {
-        auto first = dst.begin() + ptr[a], last = dst.begin() + ptr[a + 1];
-        auto it = std::lower_bound(first, last, b);
-        if (it != last && *it == b) {
-            w[it - dst.begin()] = wt;
+        const int64_t at = base->find(a, b);
+        if (at >= 0) {
+            if (base.use_count() > 1) {
+                over[key(a, b)] = wt;
+            } else {
+                base->arc[at].w = wt;
+                if (!over.empty()) over.erase(key(a, b));
+            }
             return;
         }
-        auto e = extra.find(key(a, b));
-        if (e == extra.end()) {
-            extra.emplace(key(a, b), wt);
-            ++arcs;
-        } else {
-            e->second = wt;
-        }
+        if (extra.insert_or_assign(key(a, b), wt).second) ++arcs;
     }
 
-    // Folds the overlay into the CSR.
+    // Folds the overlays into the CSR.
     void compact() {
-        if (extra.empty()) return;
-        std::vector<std::vector<std::pair<int32_t, int32_t>>> add(n);
-        for (auto &kv : extra) add[kv.first / n].push_back({(int32_t)(kv.first % n), kv.second});
-        std::vector<int64_t> np(n + 1, 0);
-        std::vector<int32_t> nd, nw;
-        nd.reserve(arcs);
-        nw.reserve(arcs);
-        for (int32_t a = 0; a < n; ++a) {
-            std::vector<std::pair<int32_t, int32_t>> row;
-            for (int64_t e = ptr[a]; e < ptr[a + 1]; ++e) row.push_back({dst[e], w[e]});
-            row.insert(row.end(), add[a].begin(), add[a].end());
-            std::sort(row.begin(), row.end());
-            for (auto &p : row) {
-                nd.push_back(p.first);
-                nw.push_back(p.second);
+        if (over.empty() && extra.empty()) return;
+        if (base.use_count() > 1 || !extra.empty()) {
+            std::vector<std::pair<uint64_t, int32_t>> add(extra.begin(), extra.end());
+            std::sort(add.begin(), add.end());
+            auto next = std::make_shared<ArcCsr>();
+            next->ptr.assign(n + 1, 0);
+            next->arc.reserve((size_t)arcs);
+            size_t k = 0;
+            for (int32_t a = 0; a < n; ++a) {
+                for (int32_t e = base->ptr[a]; e < base->ptr[a + 1]; ++e) {
+                    for (; k < add.size() && add[k].first < key(a, base->arc[e].v); ++k)
+                        next->arc.push_back({(int32_t)(add[k].first % n), add[k].second});
+                    next->arc.push_back(base->arc[e]);
+                }
+                for (; k < add.size() && add[k].first < key(a + 1, 0); ++k)
+                    next->arc.push_back({(int32_t)(add[k].first % n), add[k].second});
+                next->ptr[a + 1] = (int32_t)next->arc.size();
             }
-            np[a + 1] = (int64_t)nd.size();
+            base = std::move(next);
+            extra.clear();
         }
-        ptr.swap(np);
-        dst.swap(nd);
-        w.swap(nw);
-        extra.clear();
+        for (auto &kv : over) base->arc[base->find((int32_t)(kv.first / n), (int32_t)(kv.first % n))].w = kv.second;
+        over.clear();
     }
 };
 
@@ -1029,20 +1045,6 @@ bc_status read_status(bc_ctx *ctx, const std::vector<const int32_t *> &words, bo
     return BC_OK;
 }
 
-// An arc set by tail (heads ascending within a tail).
-struct ArcCsr {
-    std::vector<int32_t> ptr;
-    std::vector<ArcW> arc;
-    int64_t size() const { return (int64_t)arc.size(); }
-    // from an arc list in CSR order kept as two arrays
-    template <typename P>
-    void assign(const std::vector<P> &p, const std::vector<int32_t> &v, const std::vector<int32_t> &w) {
-        ptr.assign(p.begin(), p.end());
-        arc.resize(v.size());
-        for (size_t i = 0; i < v.size(); ++i) arc[i] = {v[i], w[i]};
-    }
-};
-
 // The maintained E* as an arc list grouped by tail (heads ascending within a
 // tail), read from its by-head copy XC.  Refuses a graph with a sticky error:
 // its E* may be incomplete then.
@@ -1100,18 +1102,20 @@ bc_status upload_csr(bc_ctx *ctx, int32_t n, const ArcCsr &c, int32_t *ptr, ArcW
 void lightest_arcs(int32_t n, const ArcCsr &full, int32_t k, ArcCsr &out) {
     out.ptr.assign(n + 1, 0);
     out.arc.clear();
-    std::vector<std::pair<int32_t, int32_t>> row;  // (w, head)
+    std::vector<ArcW> row;  // the lightest so far, ascending by (weight, head)
+    const auto lighter = [](const ArcW &x, const ArcW &y) { return x.w < y.w || (x.w == y.w && x.v < y.v); };
     for (int32_t a = 0; a < n; ++a) {
         row.clear();
-        for (int32_t e = full.ptr[a]; e < full.ptr[a + 1]; ++e) row.push_back({full.arc[e].w, full.arc[e].v});
-        if ((int32_t)row.size() > k) {
-            std::nth_element(row.begin(), row.begin() + k, row.end());
-            row.resize(k);
+        for (int32_t e = full.ptr[a]; e < full.ptr[a + 1]; ++e) {
+            const ArcW x = full.arc[e];
+            if ((int32_t)row.size() == k) {
+                if (!lighter(x, row.back())) continue;
+                row.pop_back();
+            }
+            row.insert(std::upper_bound(row.begin(), row.end(), x, lighter), x);
         }
-        std::sort(row.begin(), row.end(), [](const std::pair<int32_t, int32_t> &x, const std::pair<int32_t, int32_t> &y) {
-            return x.second < y.second;
-        });
-        for (auto &p : row) out.arc.push_back({p.second, p.first});
+        std::sort(row.begin(), row.end(), [](const ArcW &x, const ArcW &y) { return x.v < y.v; });
+        out.arc.insert(out.arc.end(), row.begin(), row.end());
         out.ptr[a + 1] = (int32_t)out.arc.size();
     }
 }
@@ -1179,8 +1183,8 @@ bc_status run_check(bc_ctx *ctx, GraphRec *g, const Mirror &arcs, bool all, int3
     const int32_t n = g->n;
     Mirror m = arcs;
     m.compact();
-    ArcCsr tail, head;
-    tail.assign(m.ptr, m.dst, m.w);
+    const ArcCsr &tail = *m.base;
+    ArcCsr head;
     if (tail.size() > g->arc_cap) return fail(ctx, BC_ERR_CAPACITY, "arc capacity exceeded");
     by_head(n, tail, head);
     bc_status st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin);
@@ -1291,14 +1295,14 @@ void launch_static(bc_ctx *ctx, const GraphPtrs &P, int slots, const LaunchShape
 
 bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     const int32_t n = g->n;
-    ArcCsr full;
+    ArcCsr estar;
     if (over_estar) {
-        bc_status st = estar_by_tail(ctx, g, full);
+        bc_status st = estar_by_tail(ctx, g, estar);
         if (st) return st;
     } else {
         g->mirror.compact();
-        full.assign(g->mirror.ptr, g->mirror.dst, g->mirror.w);
     }
+    const ArcCsr &full = over_estar ? estar : *g->mirror.base;
     const int64_t m = full.size();
     if (m > g->arc_cap) return fail(ctx, BC_ERR_CAPACITY, "arc capacity exceeded");
     const bool checked = !over_estar && !ctx->full_search && use_checked_search(n, m);
@@ -1317,21 +1321,23 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     if ((st = zero_slots(ctx))) return st;
     const int g_wave = (int)std::min<int64_t>(((int64_t)n * 64 + 255) / 256, 4096);
     hipStream_t s = ctx->stream;
-    ArcCsr search;  // the arcs the distance search relaxes
+    ArcCsr subset;
+    const ArcCsr *search = &full;  // the arcs the distance search relaxes
     bool have_dist = false;
     int32_t rounds = 0;
     if (checked) {
         // every arc by tail stays in arc_* for the check; the searched set
         // goes by tail into the by-head arrays, unused until the E* build
         if ((st = upload_csr(ctx, n, full, g->P.arc_ptr, g->P.arc))) return st;
-        lightest_arcs(n, full, search_k(n), search);
+        lightest_arcs(n, full, search_k(n), subset);
+        search = &subset;
         unsigned long long *cnt = (unsigned long long *)misc_dev(ctx);
         std::vector<int32_t> ca, cb, cw;
         for (;;) {
             ++rounds;
-            if ((st = upload_csr(ctx, n, search, g->P.arcin_ptr, g->P.arcin))) return st;
+            if ((st = upload_csr(ctx, n, subset, g->P.arcin_ptr, g->P.arcin))) return st;
             hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
-            launch_search(ctx, g->P, search, g->P.arcin_ptr, g->P.arcin);
+            launch_search(ctx, g->P, subset, g->P.arcin_ptr, g->P.arcin);
             HIPCHK(hipMemsetAsync(cnt, 0, 8, s));
             hipLaunchKernelGGL(k_search_check, dim3(std::max(1, std::min(g_wave, 4096))), dim3(256), 0, s, dj,
                                g->P.yc_src, g->P.yc_dst, g->P.yc_w, g->es_cap, cnt);
@@ -1347,7 +1353,7 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
             }
             if ((int64_t)c > g->es_cap) {
                 // more candidate arcs than E* may hold: search every arc
-                search = full;
+                search = &full;
                 break;
             }
             ca.resize((size_t)c);
@@ -1359,25 +1365,23 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
                 HIPCHK(hipMemcpyAsync(cw.data(), g->P.yc_w, 4 * (size_t)c, hipMemcpyDeviceToHost, s));
                 HIPCHK(hipStreamSynchronize(s));
             }
-            if (add_missing(n, search, ca, cb, cw) == 0) {
+            if (add_missing(n, subset, ca, cb, cw) == 0) {
                 have_dist = true;
                 break;
             }
         }
-    } else {
-        search = std::move(full);
     }
-    g->search_arcs = search.size();
+    g->search_arcs = search->size();
     g->search_rounds = rounds;
     // the final arc set, by tail and by head, for the E* build
     ArcCsr head;
-    by_head(n, search, head);
-    if ((st = upload_csr(ctx, n, search, g->P.arc_ptr, g->P.arc))) return st;
+    by_head(n, *search, head);
+    if ((st = upload_csr(ctx, n, *search, g->P.arc_ptr, g->P.arc))) return st;
     if ((st = upload_csr(ctx, n, head, g->P.arcin_ptr, g->P.arcin))) return st;
-    g->P.arc_m = search.size();
+    g->P.arc_m = search->size();
     if (!have_dist) {
         hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(1), 0, s, g->P.ctl);
-        launch_search(ctx, g->P, search, g->P.arc_ptr, g->P.arc);
+        launch_search(ctx, g->P, *search, g->P.arc_ptr, g->P.arc);
     }
     hipLaunchKernelGGL(k_es_count, dim3(g_wave), dim3(256), 0, s, dj);
     hipLaunchKernelGGL(k_es_scan, dim3(1), dim3(1024), 0, s, dj);
@@ -1905,42 +1909,44 @@ bc_status bc_load_graph(bc_ctx *ctx, int32_t n, int64_t m, const int32_t *src, c
     g->arena_bytes = arena_bytes;
     Mirror &mr = g->mirror;
     mr.n = n;
-    std::vector<std::pair<uint64_t, int32_t>> keyed;
-    keyed.reserve(arcs);
+    mr.arcs = arcs;
+    mr.base = std::make_shared<ArcCsr>();
+    ArcCsr &csr = *mr.base;
+    csr.ptr.assign((size_t)n + 1, 0);
     for (int64_t i = 0; i < m; ++i) {
         const int32_t a = src[i], b = dst[i];
-        if (a < 0 || b < 0 || a >= n || b >= n) {
+        bc_status st = BC_OK;
+        if (a < 0 || b < 0 || a >= n || b >= n) st = fail(ctx, BC_ERR_INVALID_ARG, "vertex id out of range");
+        else if (a == b) st = fail(ctx, BC_ERR_SELF_LOOP, "self-loop");
+        else if (w[i] <= 0 || w[i] > W_MAX) st = fail(ctx, BC_ERR_BAD_WEIGHT, "weight out of range");
+        if (st) {
             delete g;
-            return fail(ctx, BC_ERR_INVALID_ARG, "vertex id out of range");
+            return st;
         }
-        if (a == b) {
-            delete g;
-            return fail(ctx, BC_ERR_SELF_LOOP, "self-loop");
-        }
-        if (w[i] <= 0 || w[i] > W_MAX) {
-            delete g;
-            return fail(ctx, BC_ERR_BAD_WEIGHT, "weight out of range");
-        }
-        keyed.push_back({(uint64_t)a * n + b, (int32_t)w[i]});
-        if (!directed) keyed.push_back({(uint64_t)b * n + a, (int32_t)w[i]});
+        csr.ptr[a + 1]++;
+        if (!directed) csr.ptr[b + 1]++;
     }
-    std::sort(keyed.begin(), keyed.end());
-    for (size_t i = 1; i < keyed.size(); ++i)
-        if (keyed[i].first == keyed[i - 1].first) {
+    // a counting sort by tail; the heads of a tail come out ascending when the
+    // input is sorted, else its row is sorted (one sort of all arcs took two
+    // thirds of the load of a complete graph of 2048 vertices)
+    for (int32_t a = 0; a < n; ++a) csr.ptr[a + 1] += csr.ptr[a];
+    csr.arc.resize((size_t)arcs);
+    {
+        std::vector<int32_t> fill(csr.ptr.begin(), csr.ptr.end() - 1);
+        for (int64_t i = 0; i < m; ++i) {
+            csr.arc[fill[src[i]]++] = {dst[i], (int32_t)w[i]};
+            if (!directed) csr.arc[fill[dst[i]]++] = {src[i], (int32_t)w[i]};
+        }
+    }
+    for (int32_t a = 0; a < n; ++a) {
+        const auto first = csr.arc.begin() + csr.ptr[a], last = csr.arc.begin() + csr.ptr[a + 1];
+        const auto by_vertex = [](const ArcW &x, const ArcW &y) { return x.v < y.v; };
+        if (!std::is_sorted(first, last, by_vertex)) std::sort(first, last, by_vertex);
+        if (std::adjacent_find(first, last, [](const ArcW &x, const ArcW &y) { return x.v == y.v; }) != last) {
             delete g;
             return fail(ctx, BC_ERR_DUPLICATE_EDGE, "duplicate edge");
         }
-    mr.ptr.assign(n + 1, 0);
-    mr.dst.resize(keyed.size());
-    mr.w.resize(keyed.size());
-    for (size_t i = 0; i < keyed.size(); ++i) {
-        const int32_t a = (int32_t)(keyed[i].first / n);
-        mr.dst[i] = (int32_t)(keyed[i].first % n);
-        mr.w[i] = keyed[i].second;
-        mr.ptr[a + 1]++;
     }
-    for (int32_t a = 0; a < n; ++a) mr.ptr[a + 1] += mr.ptr[a];
-    mr.arcs = (int64_t)keyed.size();
     size_t total = 0;
     g->P = carve((char *)arena, n, arc_capacity, estar_capacity, &total, &g->chk);
     g->P.directed = g->directed;
@@ -2324,7 +2330,11 @@ bc_status bc_get_arcs(bc_ctx *ctx, bc_graph_id gid, int32_t *src, int32_t *dst, 
         ++k;
     };
     for (int32_t a = 0; a < g->n; ++a)
-        for (int64_t i = M.ptr[a]; i < M.ptr[a + 1]; ++i) emit(a, M.dst[i], M.w[i]);
+        for (int32_t i = M.base->ptr[a]; i < M.base->ptr[a + 1]; ++i) {
+            const ArcW x = M.base->arc[i];
+            const auto o = M.over.empty() ? M.over.end() : M.over.find(M.key(a, x.v));
+            emit(a, x.v, o == M.over.end() ? x.w : o->second);
+        }
     for (auto &e : extra) emit((int32_t)(e.first / (uint64_t)g->n), (int32_t)(e.first % (uint64_t)g->n), e.second);
     *cnt = k;
     return BC_OK;
