@@ -1252,23 +1252,25 @@ bc_status zero_slots(bc_ctx *ctx) {
 }
 
 // The distance search over a set of arcs by tail.  Width of a step: three
-// quarters of the mean weight (at half and at twice that, the rounds and the
-// relaxations on Chung-Lu graphs multiply to more).
+// quarters of the mean weight.  It is flat there: with a quarter, a half, three
+// quarters and all of it a recompute takes 21.1, 20.0, 20.1 and 20.4 ms on a
+// Chung-Lu graph of 16384 vertices, 1.47, 1.33, 1.31 and 1.29 on an
+// out-degree-8 one of 4096.
 void launch_search(bc_ctx *ctx, const GraphPtrs &P, const ArcCsr &set, const int32_t *ptr, const ArcW *arc) {
     const int32_t n = P.n;
     int64_t sum = 0;
     for (const ArcW &a : set.arc) sum += a.w;
     const int64_t mean34 = set.size() ? sum / set.size() * 3 / 4 : 1;
     const int32_t delta = (int32_t)std::max<int64_t>(1, std::min<int64_t>(mean34, INF32 - 1));
-    // the row in LDS where it fits beside the marks and a queue; 8 to 24
+    // the row in LDS where it fits beside the marks and the queue; 8 to 24
     // vertices per thread, so that several sources share a CU (24 waves by
     // the kernel's registers)
-    const size_t marks = 8 * (((size_t)n + 63) / 64);
-    const int32_t qcap = std::max(256, std::min(n / 4, 2048));
-    const bool lds = marks + 4 * (size_t)n + 4 * (size_t)qcap <= ctx->sssp_lds_limit;
-    const size_t bytes = marks + 4 * (size_t)qcap + (lds ? 4 * (size_t)n : 0);
     const int block = n > 17000 ? 1024 : n > 9216 ? 768 : n > 4096 ? 512 : n > 2048 ? 256 : n > 512 ? 128 : 64;
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(1536 / block, 160 * 1024 / (bytes + 2048)));
+    int32_t qcap = std::max(256, std::min(n / 4, 3072));
+    if (sssp_lds(n, qcap, block, true) > ctx->sssp_lds_limit) qcap = 512;
+    const bool lds = sssp_lds(n, qcap, block, true) <= ctx->sssp_lds_limit;
+    const size_t bytes = sssp_lds(n, qcap, block, lds);
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(1536 / block, 160 * 1024 / (bytes + SSSP_STATIC)));
     const dim3 grid(std::min(n, per_cu * ctx->cu_count)), blk(block);
     if (lds) hipLaunchKernelGGL(k_sssp<true>, grid, blk, bytes, ctx->stream, P, ptr, arc, delta, qcap);
     else hipLaunchKernelGGL(k_sssp<false>, grid, blk, bytes, ctx->stream, P, ptr, arc, delta, qcap);

@@ -73,6 +73,33 @@ __device__ __forceinline__ uint32_t popc_below(uint64_t mask, int lane) {
     return (uint32_t)__popcll(mask & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
 }
 
+// Wave-wide inclusive scans by data-parallel moves (one VALU instruction per
+// step; a shuffle goes through LDS): shifts by 1, 2, 4 and 8 within rows of 16
+// lanes, then the last lane of a row, and of the first two rows, to those above.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_or_zero(const int32_t x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int32_t wave_incl_add(int32_t x) {
+    x += dpp_or_zero<0x111, 0xf>(x);
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);
+    x += dpp_or_zero<0x143, 0xc>(x);
+    return x;
+}
+// of values >= 0
+__device__ __forceinline__ int32_t wave_incl_max(int32_t x) {
+    x = max(x, dpp_or_zero<0x111, 0xf>(x));
+    x = max(x, dpp_or_zero<0x112, 0xf>(x));
+    x = max(x, dpp_or_zero<0x114, 0xf>(x));
+    x = max(x, dpp_or_zero<0x118, 0xf>(x));
+    x = max(x, dpp_or_zero<0x142, 0xa>(x));
+    x = max(x, dpp_or_zero<0x143, 0xc>(x));
+    return x;
+}
+
 // Block-wide exclusive scan of one int per thread (blockDim.x <= 1024).
 __device__ int32_t block_excl_scan(int32_t x, int32_t *sh /* >= 32 */, int32_t &total) {
     const int lane = lane_id(), wid = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
@@ -2994,154 +3021,171 @@ __global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jo
 // of the graph, or a set known or checked to contain E* (Section 6: any arc
 // set containing E* gives the same distances).
 //
-// A round is latency: the bits are scanned a 64-bit word per step of a wave
-// (no queue is kept in memory between rounds), the vertices to expand are
-// listed in LDS, and SG lanes take one vertex's arcs, two vertices at a time;
-// arcs of vertices with more than SG_DEG of them (hubs have thousands) are
-// listed in chunks, a wave per chunk.  Distances, bits and lists are all in
-// LDS, so a relaxation costs one coalesced 8-byte load and LDS work.  All
-// sources of the Chung-Lu graph take 18.7 ms (101.5 with the frontier of all
-// improved vertices, its queues and flags in global memory and a binary search
-// per four arcs), of the n = 4096 out-degree-8 graph 0.75 ms (4.10).
-constexpr int SG = 8;             // lanes per listed vertex
-constexpr int SG_DEG = 64;        // most arcs they take
-constexpr int SCHUNK = 256;       // arcs per chunk of a heavier vertex
+// The marks are two bit sets, near (below the bound) and far; a relaxation that
+// lowers a distance sets a bit without waiting for anything.  A round collects
+// the near vertices into a queue, a thread per 32 of them, and relaxes their
+// out-arcs: a wave takes an equal share of the queue, 64 vertices at most at a
+// time, their arc ranges come in one round trip, a prefix sum lays the arcs end
+// to end, and a lane finds the owner of its arc by a running maximum over marks
+// at the owners' first arcs; so hub and leaf fill the lanes alike (vertices of
+// more than SG_DEG arcs are listed in chunks, a wave per chunk).  When no near
+// vertex is left the bound moves and far vertices below it become near.
+// Distances, marks and queue are in LDS.  All sources of the Chung-Lu graph take
+// 9.0 ms, of the n = 4096 out-degree-8 graph 0.41 ms.  What bounds it are VALU
+// instructions (busy three quarters of the time): 8 lanes per vertex, or an
+// owner search by shuffles with a queue filled by returning atomics, issue
+// about 90 per 64 arcs, twice as many, and took 18.7 and 0.75 ms.
+constexpr int SG_DEG = 256;       // most arcs of a vertex taken with others'
+constexpr int SCHUNK = 256;       // arcs per chunk of a heavier one
 constexpr int SHEAVY = 256;       // chunks listed per round (more are relaxed in place)
 constexpr int SV_BITS = 18;       // vertex number in a chunk entry
+constexpr int SU = 4;             // batches of 64 arcs in flight per wave
+
+// Static LDS (the heavy list and a few words) and dynamic LDS of a search.
+constexpr size_t SSSP_STATIC = 4 * SHEAVY + 64;
+__host__ __device__ constexpr inline size_t sssp_lds(const size_t n, const size_t qcap, const size_t block, const bool lds) {
+    return 2 * 8 * ((n + 63) / 64) + (lds ? 4 * n + 2 * qcap : 4 * qcap) + SU * block;
+}
 
 template <bool LDS>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6, 8))) k_sssp(
     const GraphPtrs G, const int32_t *__restrict__ ptr, const ArcW *__restrict__ arc, const int32_t delta,
     const int32_t qcap) {
+    typedef typename std::conditional<LDS, uint16_t, int32_t>::type Q;
     extern __shared__ __align__(16) char dyn_lds[];
     __shared__ int32_t sh_q[3], sh_heavy[3], sh_min, sh_item;
     __shared__ uint32_t heavy[SHEAVY];
     const int32_t n = G.n;
-    const int32_t words = (n + 63) >> 6;
-    uint64_t *const bits = (uint64_t *)dyn_lds;
-    int32_t *const queue = (int32_t *)(bits + words);
-    int32_t *const lds_row = queue + qcap;
+    const int32_t words = 2 * ((n + 63) >> 6);  // of 32 marks
+    uint32_t *const near = (uint32_t *)dyn_lds, *const far = near + words;
+    int32_t *const lds_row = (int32_t *)(far + words);
+    Q *const queue = (Q *)(lds_row + (LDS ? n : 0));
     GraphCtl *const ctl = G.ctl;
     const int tid = threadIdx.x, bs = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = bs >> 6;
-    const int gl = tid & (SG - 1), ng = bs / SG, grp = tid / SG;
+    // this wave's owner marks, one byte per arc of SU batches, kept at zero
+    volatile uint8_t *const own_at = (volatile uint8_t *)(queue + qcap) + wid * 64 * SU;
+#pragma unroll
+    for (int k = 0; k < SU; ++k) own_at[64 * k + lane] = 0;
     bool ovf = false;
     for (int32_t s = (int32_t)blockIdx.x; s < n;) {
         int32_t *const Dg = G.D + (size_t)s * n;
         int32_t *const row = LDS ? lds_row : Dg;
-        auto dist = [&](const int32_t v) { return LDS ? row[v] : __hip_atomic_load(&row[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        auto dist = [&](const int32_t v) {
+            return LDS ? row[v] : __hip_atomic_load(&row[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        int32_t bound = delta;
         // a relaxation whose sum reaches 2^31-1 is dropped; it overflows only
         // if nothing shorter ever reaches its head, which the check after the
         // search settles (long candidates that lose are no error)
         bool long_cand = false;
         auto relax = [&](const ArcW e, const int32_t da) {
             const uint32_t nd = (uint32_t)da + (uint32_t)e.w;
-            if (nd >= (uint32_t)INF32) {
-                long_cand = true;
-            } else if ((int32_t)nd < dist(e.v)) {
-                if ((int32_t)nd < atomicMin(&row[e.v], (int32_t)nd))
-                    atomicOr((uint32_t *)bits + (e.v >> 5), 1u << (e.v & 31));
+            long_cand |= nd >= (uint32_t)INF32;
+            if (nd < (uint32_t)dist(e.v)) {
+                // (a distance is at most INF32, so a dropped sum never passes)
+                atomicMin(&row[e.v], (int32_t)nd);
+                atomicOr(&near[((int32_t)nd < bound ? 0 : words) + (e.v >> 5)], 1u << (e.v & 31));
             }
         };
         for (int32_t i = tid; i < n; i += bs) row[i] = i == s ? 0 : INF32;
-        for (int32_t i = tid; i < words; i += bs) bits[i] = i == (s >> 6) ? 1ull << (s & 63) : 0ull;
+        for (int32_t i = tid; i < 2 * words; i += bs) near[i] = i == (s >> 5) ? 1u << (s & 31) : 0u;
         if (tid < 3) {
             sh_q[tid] = 0;
             sh_heavy[tid] = 0;
         }
         __syncthreads();
-        int32_t bound = delta;
-        for (int32_t r = 0;; r = r == 2 ? 0 : r + 1) {
-            // the marked vertices below the bound, as many as the queue holds
-            // (the others keep their mark); no mark is set meanwhile
-            const int32_t rn = r == 2 ? 0 : r + 1;
-            for (int32_t w0 = wid; w0 < words; w0 += 64 * nw) {
-                const int32_t mine_at = w0 + lane * nw;
-                const uint64_t mine = mine_at < words ? bits[mine_at] : 0ull;
-                uint64_t todo = __ballot(mine != 0);
-                while (todo) {
-                    const int l = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    const int32_t w = w0 + l * nw;
-                    const uint64_t word = __shfl(mine, l, 64);
-                    const int32_t v = (w << 6) + lane;
-                    const bool near = ((word >> lane) & 1) && dist(v) < bound;
-                    const uint64_t nm = __ballot(near);
-                    if (!nm) continue;
-                    int32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&sh_q[r], (int32_t)__popcll(nm));
-                    base = __shfl(base, 0, 64);
-                    const int32_t pos = base + (int32_t)popc_below(nm, lane);
-                    const bool take = near && pos < qcap;
-                    if (take) queue[pos] = v;
-                    const uint64_t tm = __ballot(take);
-                    if (lane == 0) bits[w] = word & ~tm;
+        for (int32_t r = 0;;) {
+            // the near vertices go to the queue, as many as it holds (the
+            // others keep their mark)
+            for (int32_t w0 = tid - lane; w0 < words; w0 += bs) {
+                const int32_t w = w0 + lane;
+                uint32_t m = w < words ? near[w] : 0u;
+                const int32_t cnt = (int32_t)__popc(m);
+                const int32_t incl = wave_incl_add(cnt);
+                const int32_t total = __builtin_amdgcn_readlane(incl, 63);
+                if (total == 0) continue;
+                int32_t base = 0;
+                if (lane == 0) base = atomicAdd(&sh_q[r], total);
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (m) {
+                    far[w] &= ~m;
+                    int32_t pos = base + incl - cnt;
+                    for (; m && pos < qcap; ++pos, m &= m - 1) queue[pos] = (Q)((w << 5) + __ffs(m) - 1);
+                    near[w] = m;
                 }
             }
             __syncthreads();
             const int32_t q = min(sh_q[r], qcap);
+            const int32_t rn = r == 2 ? 0 : r + 1;
             if (tid == 0) {
                 sh_q[rn] = 0;
                 sh_heavy[rn] = 0;
+                sh_min = INF32;
             }
             if (q == 0) {
-                // the nearest marked vertex, if any, sets the next bound
-                if (tid == 0) sh_min = INF32;
+                // none: the nearest far vertex moves the bound, and those
+                // below it become near (a thread keeps to its own words)
                 __syncthreads();
-                int32_t far = INF32;
-                for (int32_t w = wid; w < words; w += nw) {
-                    const uint64_t word = bits[w];
-                    if ((word >> lane) & 1) far = min(far, dist((w << 6) + lane));
+                int32_t low = INF32;
+                for (int32_t w = tid; w < words; w += bs)
+                    for (uint32_t m = far[w]; m; m &= m - 1) low = min(low, dist((w << 5) + __ffs(m) - 1));
+                if (low != INF32) atomicMin(&sh_min, low);
+                __syncthreads();
+                low = sh_min;
+                if (low == INF32) break;
+                bound = (int32_t)min((uint32_t)low + (uint32_t)delta, (uint32_t)INF32);
+                for (int32_t w = tid; w < words; w += bs) {
+                    const uint32_t all = far[w];
+                    uint32_t below = 0;
+                    for (uint32_t m = all; m; m &= m - 1)
+                        if (dist((w << 5) + __ffs(m) - 1) < bound) below |= m & (0u - m);
+                    if (below) near[w] = below;
                 }
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) far = min(far, __shfl_xor(far, o, 64));
-                if (lane == 0 && far != INF32) atomicMin(&sh_min, far);
                 __syncthreads();
-                far = sh_min;
-                if (far == INF32) break;
-                bound = (int32_t)min((uint32_t)far + (uint32_t)delta, (uint32_t)INF32);
                 continue;
             }
-            for (int32_t i = grp; i < q; i += 2 * ng) {
-                int32_t e[2], end[2], da[2];
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const int32_t at = i + k * ng;
-                    e[k] = end[k] = da[k] = 0;
-                    if (at < q) {
-                        const int32_t a = queue[at];
-                        e[k] = ptr[a];
-                        end[k] = ptr[a + 1];
-                        da[k] = dist(a);
-                        const int32_t deg = end[k] - e[k];
-                        if (deg > SG_DEG) {
-                            // hubs: listed in chunks, or taken here where the list is full
-                            const int32_t chunks = (deg + SCHUNK - 1) / SCHUNK;
-                            int32_t pos = 0;
-                            if (gl == 0) pos = atomicAdd(&sh_heavy[r], chunks);
-                            pos = __shfl(pos, lane & ~(SG - 1), 64);
-                            if (pos + chunks <= SHEAVY) {
-                                for (int32_t c = gl; c < chunks; c += SG) heavy[pos + c] = (uint32_t)a | (uint32_t)c << SV_BITS;
-                                end[k] = e[k];
-                            } else {
-                                for (int32_t c = pos + gl; c < min(pos + chunks, SHEAVY); c += SG) heavy[c] = ~0u;
-                            }
-                        }
+            // an equal share of the queue per wave, at most a lane per vertex
+            const int32_t share = min(64, (q + nw - 1) / nw);
+            for (int32_t i0 = wid * share; i0 < q; i0 += nw * share) {
+                int32_t e0 = 0, deg = 0, da = 0;
+                if (lane < share && i0 + lane < q) {
+                    const int32_t a = (int32_t)queue[i0 + lane];
+                    e0 = ptr[a];
+                    deg = ptr[a + 1] - e0;
+                    da = dist(a);
+                    if (deg > SG_DEG) {
+                        // hubs: listed in chunks, or taken here where the list is full
+                        const int32_t chunks = (deg + SCHUNK - 1) / SCHUNK;
+                        const int32_t pos = atomicAdd(&sh_heavy[r], chunks);
+                        const bool room = pos + chunks <= SHEAVY;
+                        for (int32_t c = 0; c < chunks; ++c)
+                            if (pos + c < SHEAVY) heavy[pos + c] = room ? (uint32_t)a | (uint32_t)c << SV_BITS : ~0u;
+                        if (room) deg = 0;
                     }
-                    e[k] += gl;
                 }
-                while (__any(e[0] < end[0] || e[1] < end[1])) {
-                    ArcW x[4];
+                const int32_t incl = wave_incl_add(deg), excl = incl - deg;
+                const int32_t total = __builtin_amdgcn_readlane(incl, 63);
+                const int32_t first = e0 - excl;  // arc j of the share is arc first + j of its owner
+                int32_t last = 0;                 // owner (lane + 1) of the arc before the batch
+                for (int32_t j0 = 0; j0 < total; j0 += 64 * SU) {
+                    if (deg > 0 && excl >= j0 && excl < j0 + 64 * SU) own_at[excl - j0] = (uint8_t)(lane + 1);
+                    ArcW x[SU];
+                    int32_t d[SU];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int32_t at = e[k & 1] + (k >> 1) * SG;
+                    for (int k = 0; k < SU; ++k) {
                         x[k].w = 0;
-                        if (at < end[k & 1]) x[k] = arc[at];
+                        if (j0 + 64 * k >= total) continue;
+                        const int32_t j = j0 + 64 * k + lane;
+                        const int32_t own = max(last, wave_incl_max((int32_t)own_at[64 * k + lane]));
+                        own_at[64 * k + lane] = 0;
+                        last = __builtin_amdgcn_readlane(own, 63);
+                        const int32_t at = __builtin_amdgcn_ds_bpermute(4 * (own - 1), first) + j;
+                        d[k] = __builtin_amdgcn_ds_bpermute(4 * (own - 1), da);
+                        if (j < total) x[k] = arc[at];
                     }
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (x[k].w) relax(x[k], da[k & 1]);
-                    e[0] += 2 * SG;
-                    e[1] += 2 * SG;
+                    for (int k = 0; k < SU; ++k)
+                        if (x[k].w) relax(x[k], d[k]);
                 }
             }
             __syncthreads();
@@ -3166,6 +3210,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6, 8)
                 }
                 __syncthreads();
             }
+            r = rn;
         }
         if (__syncthreads_or(long_cand)) {
             // converged: a vertex still unreached that has an arc from a

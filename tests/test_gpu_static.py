@@ -55,7 +55,9 @@ SMALL = {
     "2049 levels": lambda: W.path_graph(2049, directed=True),
     "2500 levels": lambda: W.path_graph(2500),
     "more hubs than the queue holds": lambda: hub_row(300, 64, 700),
-    "more hubs than the heavy list holds": lambda: hub_row(300, 65, 700),
+    "65 arcs a hub": lambda: hub_row(300, 65, 700),
+    "heaviest hubs taken with others": lambda: hub_row(200, 256, 700),
+    "lightest hubs in chunks, list full": lambda: hub_row(130, 257, 700),
     "more chunks than the heavy list holds": lambda: hub_row(200, 400, 700),
     "no arc at all": lambda: W.Graph(130, True, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros(0, np.int64)),
     "one heavy weight": lambda: W.Graph(3, True, np.array([0, 1, 0], np.int32), np.array([1, 2, 2], np.int32),
