@@ -1737,12 +1737,28 @@ __device__ bool small_pass(const int32_t s, const int32_t *__restrict__ Drow, co
     return true;
 }
 
+// Alg 2 (Update-DAG) on the stored predecessors, for a one-arc update (u, v)
+// and a changed target t of source s.  A target whose distance fell
+// (WT-changed) has exactly its DAG(v) in-arcs as DAG'(s) in-arcs, or the arc
+// (u, v) alone when t = v; one whose distance stayed (NUM-changed) keeps its
+// old in-arcs and gains those (at v: gains (u, v), so it has two or more).
+// DAG(v) itself does not change (no shortest path from v enters v again), so
+// row v of the predecessors is read as it stands while other rows change.
+__device__ __forceinline__ bool one_arc_job(const UpdateJob &J) { return J.n_in == 1 && J.n_out == 0; }
+
+__device__ __forceinline__ int32_t edge_pred(const UpdateJob &J, const int32_t t, const int32_t old_pred,
+                                             const bool fell) {
+    if (t == J.v) return fell ? J.in_tail[0] : PRED_MULTI;
+    const int32_t pv = J.g.pred[(size_t)J.v * J.g.n + t];
+    if (fell) return pv;
+    return old_pred >= 0 && old_pred == pv ? pv : PRED_MULTI;
+}
+
 // Old and new partial dependency of one source in one traversal (LDS only).
 // The vertices to visit are the union of the old sub-DAG (ancestors of B in
 // DAG(s)) and the new one (ancestors of B in DAG'(s)); both are walked back
-// from B level by level at once, so the dependent gathers of a level serve
-// both.  The new distances and path counts are those of the B list for
-// targets in B and the old ones elsewhere, so D and sigma are not written
+// from B at once.  The new distances and path counts are those of the B list
+// for targets in B and the old ones elsewhere, so D and sigma are not written
 // before the new pass.  Over the merged E* segment of a head x (E* by head,
 // with the update's arcs appended), the first |E*(x)| arcs are the old E*
 // arcs with their old weights: the old Eq.1 test looks at those only, the new
@@ -1750,6 +1766,17 @@ __device__ bool small_pass(const int32_t s, const int32_t *__restrict__ Drow, co
 // The two Kahn accumulations then run over the recorded arcs, and BC gets the
 // difference delta'_B - delta_B once per vertex.  Returns false, before
 // anything global is written, when the union does not fit.
+//
+// The walk is bound by its dependent loads.  A lane follows a chain of single
+// in-arcs by itself (dd_follow), one load of the stored predecessors' row per
+// vertex: a vertex with one DAG in-arc has its tail's path count, and its
+// distance is needed only where Eq.1 is tested.  After a one-arc update the
+// changed targets' new in-arcs come from Alg 2 like stored ones.  Only vertices
+// with two or more in-arcs (and the changed targets of other updates) test
+// their E* in-arcs, in rounds of the whole workgroup; a tail's count and
+// predecessor are read when it has passed the test.  (Level by level, with
+// distance, count and predecessor read for every vertex and every tested arc,
+// X.)
 #define DD_CONSTS                          \
     constexpr int DD_SLOTS = TS;           \
     constexpr int DD_CAP = TS * 3 / 4;     \
@@ -1763,7 +1790,8 @@ struct DualDag {
     uint64_t *sold, *snew;
     // after the walk: the recorded arcs grouped by head (harc over ybeg and
     // ydeg, 2 * TS entries), each head's range end (hend over slow) and
-    // in-arc count (hdeg over xdeg), and the Kahn work list (over coef)
+    // in-arc count (hdeg over xdeg), and the Kahn work list (over coef, 2 * TS
+    // entries of slot | kind << 8)
     int32_t *harc, *hend, *hdeg, *klist;
 };
 
@@ -1788,13 +1816,14 @@ __device__ __forceinline__ DualDag dual_dag_at(char *p) {
     d.dold = (int32_t *)p;    p += 4 * DD_SLOTS;
     d.dnew = (int32_t *)p;    p += 4 * DD_SLOTS;
     d.round = (int32_t *)p;   p += 4 * DD_SLOTS;
-    d.pr = (int32_t *)p;      p += 4 * DD_SLOTS;  // stored (old) predecessor
+    d.pr = (int32_t *)p;      p += 4 * DD_SLOTS;  // changed targets: stored (old) predecessor
     d.ybeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // changed targets: merged E* in-arcs (start,
     d.ydeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // count,
-    d.xdeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // and how many are old E* arcs)
-    d.front = (int32_t *)p;   p += 4 * DD_FRONT;  // slot | memberships to expand << 16; after the walk
-                                                  // the new stored predecessor of each changed target
-    d.slow = (int32_t *)p;    p += 4 * DD_FRONT;  // a level's entries for the general expansion
+    d.xdeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // and how many are old E* arcs), or with a
+                                                  // count of -1 their one new in-arc's tail
+    d.front = (int32_t *)p;   p += 4 * DD_FRONT;  // the changed targets' slots; after the walk
+                                                  // the new stored predecessor of each
+    d.slow = (int32_t *)p;    p += 4 * DD_FRONT;  // slot | memberships << 16 whose E* in-arcs are tested
     d.arcs = (int32_t *)p;                        // tail slot | head slot << 8 | kinds << 16
     d.harc = d.ybeg;
     d.hend = d.slow;
@@ -1829,40 +1858,63 @@ __device__ __forceinline__ int32_t dd_slot(const DualDag &d, int32_t x) {
 }
 
 // One arc (a, x) of the union walk (x in slot sx; kinds: the sub-DAGs it is
-// in; sa: a's slot or -1): recorded, a's successor counts and memberships
-// raised, and a queued for the next level with any membership it gains.
-// da_o, sg, pa: d(s,a), sigma_sa and a's stored predecessor, kept at a's
-// first sight (a not in B: its new values are its old ones).
+// in; sa: a's slot, or -1 and then found): recorded, a's successor counts and
+// memberships raised.  sg: sigma_sa, kept at a's first sight (a not in B: its
+// new values are its old ones).  Returns the memberships a gains, 0 when the
+// tables are full.
 template <int TS>
-__device__ __forceinline__ void dd_add_arc(const DualDag &d, BlockShared &sh, const int32_t a, int32_t sa,
-                                           const int32_t sx, const int32_t kinds, const int32_t da_o, const uint64_t sg,
-                                           const int32_t pa) {
+__device__ __forceinline__ int32_t dd_add_arc(const DualDag &d, BlockShared &sh, const int32_t a, int32_t &sa,
+                                              const int32_t sx, const int32_t kinds, const uint64_t sg) {
     DD_CONSTS
     if (sa < 0) sa = dd_slot<TS>(d, a);
     const int32_t k = atomicAdd(&sh.tail, 1);
     if (sa < 0 || k >= DD_ARCS) {
         sh.ovf = 1;
-        return;
+        return 0;
     }
     d.arcs[k] = sa | (sx << 8) | (kinds << 16);
     atomicAdd(&d.cnt[sa], ((kinds & DF_O) ? 1 : 0) + ((kinds & DF_N) ? 1 << 16 : 0));
     const int32_t old = atomicOr(&d.flags[sa], kinds);
-    const int32_t gained = kinds & ~old;
-    if (!gained) return;
     if (!(old & (DF_O | DF_N | DF_B))) {
         if (atomicAdd(&sh.nk, 1) >= DD_CAP) {
             sh.ovf = 1;
-            return;
+            return 0;
         }
-        d.dold[sa] = da_o;
-        d.dnew[sa] = da_o;
         d.sold[sa] = sg;
         d.snew[sa] = sg;
-        d.pr[sa] = pa;
     }
-    const int32_t pos = atomicAdd(&sh.next, 1);
+    return kinds & ~old;
+}
+
+// Slot sl, newly a member of the sub-DAGs `kinds`, has two or more in-arcs.
+template <int TS>
+__device__ __forceinline__ void dd_push_slow(const DualDag &d, BlockShared &sh, const int32_t sl, const int32_t kinds) {
+    DD_CONSTS
+    const int32_t pos = atomicAdd(&sh.kpos, 1);
     if (pos >= DD_FRONT) sh.ovf = 1;
-    else d.front[pos] = sa | (gained << 16);
+    else d.slow[pos] = sl | (kinds << 16);
+}
+
+// From the vertex in slot x, whose one in-arc in the sub-DAGs `kinds` comes
+// from p (with path count sg), back along single in-arcs: to s, to a vertex
+// that has the memberships already (a changed target always has), or to one
+// with two or more in-arcs.
+template <int TS>
+__device__ __forceinline__ void dd_follow(const DualDag &d, BlockShared &sh, const int32_t s,
+                                          const int32_t *__restrict__ pred, int32_t x, int32_t p, int32_t kinds,
+                                          const uint64_t sg) {
+    for (;;) {
+        const int32_t pp = pred[p];  // (on its way while the arc is recorded)
+        int32_t sp = -1;
+        kinds = dd_add_arc<TS>(d, sh, p, sp, x, kinds, sg);
+        if (!kinds || p == s) break;
+        if (pp < 0) {
+            dd_push_slow<TS>(d, sh, sp, kinds);
+            break;
+        }
+        x = sp;
+        p = pp;
+    }
 }
 
 // The recorded arcs grouped by head (a counting sort in LDS), for the Kahn
@@ -1894,28 +1946,31 @@ __device__ __forceinline__ void dual_group_arcs(const DualDag &d, const int32_t 
     __syncthreads();
 }
 
-// Dependency accumulation over one of the two sub-DAGs (kind 1: old, 2: new)
-// from its sinks: a member x, once every successor has pushed, gives each
-// DAG predecessor a the share sigma_sa * ([x in B] + acc(x)) / sigma_sx.  The
-// lane whose push completes a carries on with a at once, so a chain takes no
-// rounds; a vertex completing two or more waits for the next round.
+// Dependency accumulation over both sub-DAGs at once from their sinks: a member
+// x of one, once every successor has pushed, gives each DAG predecessor a the
+// share sigma_sa * ([x in B] + acc(x)) / sigma_sx.  The lane whose push
+// completes a carries on with a at once, so a chain takes no rounds; a vertex
+// completing two or more waits for the next round.
 template <int TS>
-__device__ __forceinline__ void dual_kahn(const DualDag &d, const int kind, BlockShared &sh) {
+__device__ __forceinline__ void dual_kahn(const DualDag &d, BlockShared &sh) {
     DD_CONSTS
     const int tid = threadIdx.x, bs = blockDim.x;
-    const int shift = kind == DF_O ? 0 : 16;
-    double *const acc = kind == DF_O ? d.acc_o : d.acc_n;
-    const uint64_t *const sv = kind == DF_O ? d.sold : d.snew;
     if (tid == 0) sh.kpos = 0;
     __syncthreads();
-    for (int32_t i = tid; i < DD_SLOTS; i += bs)
-        if (d.key[i] >= 0 && (d.flags[i] & kind) && ((d.cnt[i] >> shift) & 0xffff) == 0)
-            d.klist[atomicAdd(&sh.kpos, 1)] = i;
+    for (int32_t i = tid; i < DD_SLOTS; i += bs) {
+        if (d.key[i] < 0) continue;
+        const int32_t f = d.flags[i], c = d.cnt[i];
+        if ((f & DF_O) && (c & 0xffff) == 0) d.klist[atomicAdd(&sh.kpos, 1)] = i | (DF_O << 8);
+        if ((f & DF_N) && ((c >> 16) & 0xffff) == 0) d.klist[atomicAdd(&sh.kpos, 1)] = i | (DF_N << 8);
+    }
     __syncthreads();
     int32_t lo = 0, hi = sh.kpos;
     while (lo < hi) {
         for (int32_t idx = lo + tid; idx < hi; idx += bs) {
-            int32_t x = d.klist[idx];
+            int32_t x = d.klist[idx] & 0xff;
+            const int32_t kind = d.klist[idx] >> 8, shift = kind == DF_O ? 0 : 16;
+            double *const acc = kind == DF_O ? d.acc_o : d.acc_n;
+            const uint64_t *const sv = kind == DF_O ? d.sold : d.snew;
             for (;;) {
                 const double c = (((d.flags[x] & DF_B) ? 1.0 : 0.0) + acc[x]) / (double)sv[x];
                 int32_t next = -1;
@@ -1931,7 +1986,7 @@ __device__ __forceinline__ void dual_kahn(const DualDag &d, const int kind, Bloc
                                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (((left >> shift) & 0xffff) == 1) {
                         if (next < 0) next = a;
-                        else d.klist[atomicAdd(&sh.kpos, 1)] = a;
+                        else d.klist[atomicAdd(&sh.kpos, 1)] = a | (kind << 8);
                     }
                 }
                 if (next < 0) break;
@@ -1946,14 +2001,16 @@ __device__ __forceinline__ void dual_kahn(const DualDag &d, const int kind, Bloc
 }
 
 template <int TS>
-__device__ bool dual_pass(const int32_t s, const int32_t *__restrict__ Dold, const uint64_t *__restrict__ Sold,
-                          const int32_t *__restrict__ xcp, const int32_t *__restrict__ ycp,
-                          const int32_t *__restrict__ ycs, const int32_t *__restrict__ ycw,
-                          const int32_t *__restrict__ Bt, const int32_t *__restrict__ Bd,
-                          const uint64_t *__restrict__ Bs, const int32_t *__restrict__ pred, const int32_t nb,
-                          double *out, BlockShared &sh, const ExpandShared &es, const DualDag &d) {
+__device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__restrict__ Dold,
+                          const uint64_t *__restrict__ Sold, const int32_t *__restrict__ xcp,
+                          const int32_t *__restrict__ ycp, const int32_t *__restrict__ ycs,
+                          const int32_t *__restrict__ ycw, const int32_t *__restrict__ Bt,
+                          const int32_t *__restrict__ Bd, const uint64_t *__restrict__ Bs,
+                          const int32_t *__restrict__ pred, const int32_t nb, double *out, BlockShared &sh,
+                          const ExpandShared &es, const DualDag &d) {
     DD_CONSTS
     const int tid = threadIdx.x, bs = blockDim.x;
+    const bool edge = one_arc_job(J);
     for (int32_t i = tid; i < DD_SLOTS; i += bs) {
         d.key[i] = -1;
         d.flags[i] = 0;
@@ -1962,9 +2019,10 @@ __device__ bool dual_pass(const int32_t s, const int32_t *__restrict__ Dold, con
         d.acc_n[i] = 0.0;
     }
     if (tid == 0) {
-        sh.next = 0;   // frontier entries
+        sh.next = 0;   // changed targets
         sh.tail = 0;   // recorded arcs
         sh.nk = 0;     // vertices
+        sh.kpos = 0;   // slow list
         sh.ovf = 0;
     }
     __syncthreads();
@@ -1979,76 +2037,87 @@ __device__ bool dual_pass(const int32_t s, const int32_t *__restrict__ Dold, con
             sh.ovf = 1;
             continue;
         }
-        // everything the walk reads of t, in one round trip
-        const int32_t dt = Dold[t];
+        // what the walk reads of t, in one round trip
+        const int32_t dt = Dold[t], dn = Bd[i];
         const uint64_t st = Sold[t];
         const int32_t pt = pred[t];
-        const int32_t yb = ycp[t], ye = ycp[t + 1], xb = xcp[t], xe = xcp[t + 1];
+        int32_t yb, ye = 0, xb = 0, xe = 0;
+        if (edge) {
+            yb = edge_pred(J, t, pt, dn < dt);
+        } else {
+            yb = ycp[t];
+            ye = ycp[t + 1];
+            xb = xcp[t];
+            xe = xcp[t + 1];
+        }
         const int32_t mem = DF_N | (dt != INF32 ? DF_O : 0);
         d.flags[slot] = DF_B | mem;
         d.dold[slot] = dt;
-        d.dnew[slot] = Bd[i];
+        d.dnew[slot] = dn;
         d.sold[slot] = dt != INF32 ? st : 0;
         d.snew[slot] = Bs[i];
         d.pr[slot] = pt;
+        if (edge && yb < 0) {
+            // two or more new in-arcs
+            yb = ycp[t];
+            ye = ycp[t + 1];
+            xb = xcp[t];
+            xe = xcp[t + 1];
+            d.ydeg[slot] = ye - yb;
+        } else {
+            d.ydeg[slot] = edge ? -1 : ye - yb;
+        }
         d.ybeg[slot] = yb;
-        d.ydeg[slot] = ye - yb;
         d.xdeg[slot] = xe - xb;
-        d.front[pos] = slot | (mem << 16);
+        d.front[pos] = slot;
     }
     __syncthreads();
     if (sh.ovf) return false;
-    int32_t lo = 0, hi = sh.next;
-    __syncthreads();
-    // per general entry: its stored old predecessor and how many of its
-    // merged in-arcs are tested (the rest of its work items: the stored arc)
-    int32_t *const ex_pred = (int32_t *)es.val, *const ex_test = ex_pred + bs;
-    while (lo < hi) {
-        if (tid == 0) sh.kpos = 0;
-        __syncthreads();
-        // an unchanged vertex with one stored predecessor: that arc, at
-        // once, for both memberships (an unchanged pair keeps its DAG
-        // in-arcs); the others to the level's general list
-        for (int32_t idx = lo + tid; idx < hi; idx += bs) {
-            const int32_t entry = d.front[idx];
-            const int32_t sl = entry & 0xffff;
-            if (d.key[sl] == s) continue;
-            const int32_t pr = d.pr[sl];
-            if ((d.flags[sl] & DF_B) || pr < 0) {
-                d.slow[atomicAdd(&sh.kpos, 1)] = entry;
-                continue;
-            }
-            // with the distance, what a first sight of the tail needs
-            const int32_t da_o = Dold[pr];
-            const uint64_t sg = Sold[pr];
-            const int32_t pa = pred[pr];
-            dd_add_arc<TS>(d, sh, pr, dd_find<TS>(d, pr), sl, (entry >> 16) & (DF_O | DF_N), da_o, sg, pa);
+    // back from every changed target, a lane for its old in-arcs and one for
+    // its new ones (an in-arc that is both goes with the old ones)
+    const int32_t nroot = sh.next;
+    for (int32_t idx = tid; idx < 2 * nroot; idx += bs) {
+        const int32_t sl = d.front[idx >> 1];
+        const int32_t pr = (d.flags[sl] & DF_O) ? d.pr[sl] : PRED_NONE, pn = d.ydeg[sl] < 0 ? d.ybeg[sl] : PRED_MULTI;
+        const bool one = pr >= 0 && pr == pn;
+        if (idx & 1) {
+            const int32_t slow = (pr == PRED_MULTI ? DF_O : 0) | (pn < 0 ? DF_N : 0);
+            if (slow) dd_push_slow<TS>(d, sh, sl, slow);
+            if (pn >= 0 && !one) dd_follow<TS>(d, sh, s, pred, sl, pn, DF_N, d.snew[sl]);
+        } else if (pr >= 0) {
+            dd_follow<TS>(d, sh, s, pred, sl, pr, one ? DF_O | DF_N : DF_O, d.sold[sl]);
         }
-        __syncthreads();
-        const int32_t nslow = sh.kpos;
-        for (int32_t c = 0; c < nslow; c += bs) {
+    }
+    __syncthreads();
+    // the vertices whose E* in-arcs are tested: arc-parallel, and back from
+    // every tail found
+    int32_t lo = 0, hi = sh.kpos;
+    bool ovf = sh.ovf != 0;
+    __syncthreads();
+    while (lo < hi && !ovf) {
+        for (int32_t c = lo; c < hi; c += bs) {
             const int32_t idx = c + tid;
-            int32_t entry = 0, b0 = 0, cnt = 0, ntest = 0, olen = 0, pr = PRED_NONE;
-            if (idx < nslow) {
+            int32_t entry = 0, b0 = 0, cnt = 0, olen = 0;
+            if (idx < hi) {
                 entry = d.slow[idx];
                 const int32_t sl = entry & 0xffff, mem = entry >> 16;
                 const int32_t x = d.key[sl];
-                pr = d.pr[sl];
-                if (d.flags[sl] & DF_B) {
-                    // a changed target: its new DAG in-arcs by Eq.1 over the
-                    // merged E*; its old ones from the stored predecessor, or
-                    // by Eq.1 over the old E* arcs where two or more
+                if ((d.flags[sl] & DF_B) && d.ydeg[sl] >= 0) {
                     b0 = d.ybeg[sl];
-                    ntest = d.ydeg[sl];
-                    olen = ((mem & DF_O) && pr < 0) ? d.xdeg[sl] : 0;
-                    cnt = ntest + (((mem & DF_O) && pr >= 0) ? 1 : 0);
+                    cnt = d.ydeg[sl];
+                    olen = d.xdeg[sl];
                 } else {
-                    // two or more DAG in-arcs: Eq.1 over E*
                     b0 = ycp[x];
-                    ntest = ycp[x + 1] - b0;
-                    olen = (mem & DF_O) ? xcp[x + 1] - xcp[x] : 0;
-                    cnt = ntest;
+                    cnt = ycp[x + 1] - b0;
+                    olen = xcp[x + 1] - xcp[x];
+                    if (!(d.flags[sl] & DF_B)) {
+                        const int32_t dx = Dold[x];
+                        d.dold[sl] = dx;
+                        d.dnew[sl] = dx;
+                    }
                 }
+                // old in-arcs alone: the old E* arcs alone are tested
+                if (mem == DF_O) cnt = olen;
             }
             int32_t total;
             const int32_t off = block_excl_scan(cnt, sh.scan, total);
@@ -2056,52 +2125,38 @@ __device__ bool dual_pass(const int32_t s, const int32_t *__restrict__ Dold, con
             es.vtx[tid] = entry;
             es.beg[tid] = b0;
             es.dx[tid] = olen;
-            ex_pred[tid] = pr;
-            ex_test[tid] = ntest;
             __syncthreads();
-            const int32_t nv = min(bs, nslow - c);
+            const int32_t nv = min(bs, hi - c);
             for (int32_t j = tid; j < total; j += bs) {
+                if (*(volatile int32_t *)&sh.ovf) break;
                 const int32_t i = find_owner(es, nv, j);
                 const int32_t ent = es.vtx[i];
                 const int32_t sx = ent & 0xffff, mem = ent >> 16;
                 const int32_t rel = j - es.off[i];
-                int32_t a, da_o, pa, sa, kinds;
-                uint64_t sg;
-                if (rel < ex_test[i]) {
-                    const int32_t e = es.beg[i] + rel;
-                    a = ycs[e];
-                    const int32_t w = ycw[e];
-                    // with the distance, what a first sight of a needs
-                    da_o = Dold[a];
-                    sg = Sold[a];
-                    pa = pred[a];
-                    sa = dd_find<TS>(d, a);
-                    const int32_t da_n = (sa >= 0 && (d.flags[sa] & DF_B)) ? d.dnew[sa] : da_o;
-                    const bool po = (mem & DF_O) && rel < es.dx[i] && da_o != INF32 &&
-                                    (int64_t)da_o + w == (int64_t)d.dold[sx];
-                    const bool pn = (mem & DF_N) && da_n != INF32 && (int64_t)da_n + w == (int64_t)d.dnew[sx];
-                    if (!po && !pn) continue;
-                    kinds = (po ? DF_O : 0) | (pn ? DF_N : 0);
-                } else {
-                    // the stored predecessor of a changed target: old
-                    // membership only
-                    a = ex_pred[i];
-                    da_o = Dold[a];
-                    sg = Sold[a];
-                    pa = pred[a];
-                    sa = dd_find<TS>(d, a);
-                    kinds = DF_O;
-                }
-                dd_add_arc<TS>(d, sh, a, sa, sx, kinds, da_o, sg, pa);
+                const int32_t e = es.beg[i] + rel;
+                const int32_t a = ycs[e], w = ycw[e];
+                const int32_t da_o = Dold[a];
+                int32_t sa = dd_find<TS>(d, a);
+                const int32_t da_n = (sa >= 0 && (d.flags[sa] & DF_B)) ? d.dnew[sa] : da_o;
+                const bool po = (mem & DF_O) && rel < es.dx[i] && da_o != INF32 &&
+                                (int64_t)da_o + w == (int64_t)d.dold[sx];
+                const bool pn = (mem & DF_N) && da_n != INF32 && (int64_t)da_n + w == (int64_t)d.dnew[sx];
+                if (!po && !pn) continue;
+                const uint64_t sg = Sold[a];
+                const int32_t pa = pred[a];
+                const int32_t gained = dd_add_arc<TS>(d, sh, a, sa, sx, (po ? DF_O : 0) | (pn ? DF_N : 0), sg);
+                if (!gained || a == s) continue;
+                if (pa < 0) dd_push_slow<TS>(d, sh, sa, gained);
+                else dd_follow<TS>(d, sh, s, pred, sa, pa, gained, sg);
             }
             __syncthreads();
         }
-        const bool ovf = sh.ovf != 0;
         lo = hi;
-        hi = sh.next;
+        hi = sh.kpos;
+        ovf = sh.ovf != 0;
         __syncthreads();
-        if (ovf) return false;
     }
+    if (ovf) return false;
     const int32_t narcs = sh.tail;
     // the new stored predecessor of each changed target: its only recorded
     // new-DAG in-arc (every new in-arc of a changed target was tested and
@@ -2121,8 +2176,7 @@ __device__ bool dual_pass(const int32_t s, const int32_t *__restrict__ Dold, con
             d.front[i] = d.round[i] == 0 ? PRED_NONE : PRED_MULTI;
     __syncthreads();
     dual_group_arcs<TS>(d, narcs, sh);
-    dual_kahn<TS>(d, DF_O, sh);
-    dual_kahn<TS>(d, DF_N, sh);
+    dual_kahn<TS>(d, sh);
     for (int32_t i = tid; i < DD_SLOTS; i += bs) {
         const int32_t x = d.key[i];
         if (x < 0 || x == s) continue;
@@ -2540,23 +2594,6 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
     }
 }
 
-// Alg 2 (Update-DAG) on the stored predecessors, for a one-arc update (u, v)
-// and a changed target t of source s.  A target whose distance fell
-// (WT-changed) has exactly its DAG(v) in-arcs as DAG'(s) in-arcs, or the arc
-// (u, v) alone when t = v; one whose distance stayed (NUM-changed) keeps its
-// old in-arcs and gains those (at v: gains (u, v), so it has two or more).
-// DAG(v) itself does not change (no shortest path from v enters v again), so
-// row v of the predecessors is read as it stands while other rows change.
-__device__ __forceinline__ bool one_arc_job(const UpdateJob &J) { return J.n_in == 1 && J.n_out == 0; }
-
-__device__ __forceinline__ int32_t edge_pred(const UpdateJob &J, const int32_t t, const int32_t old_pred,
-                                             const bool fell) {
-    if (t == J.v) return fell ? J.in_tail[0] : PRED_MULTI;
-    const int32_t pv = J.g.pred[(size_t)J.v * J.g.n + t];
-    if (fell) return pv;
-    return old_pred >= 0 && old_pred == pv ? pv : PRED_MULTI;
-}
-
 // One listed source with its changed targets B (Bt, Bd, Bs; nb of them):
 // both partial dependencies in one traversal in LDS (dual_pass) and then the
 // changed pairs written to D and sigma; or, when the two sub-DAGs do not fit
@@ -2585,8 +2622,8 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     const bool fits = nb < TS * 3 / 4;
     const bool dual_fits = nb < TS * 3 / 8;
     int32_t *const pred_row = J.g.pred + (size_t)s * n;
-    const bool dual = dual_fits && dual_pass<TS>(s, Drow, Sg, J.g.xc_ptr, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, Bd, Bs,
-                                            pred_row, nb, bc_delta, sh, es, dd);
+    const bool dual = dual_fits && dual_pass<TS>(J, s, Drow, Sg, J.g.xc_ptr, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, Bd,
+                                                 Bs, pred_row, nb, bc_delta, sh, es, dd);
     // when the union outgrew the table it is mostly the old sub-DAG that did:
     // the old pass goes straight to the slot (it follows stored
     // predecessors), the new one tries the LDS table first
