@@ -369,8 +369,8 @@ int lds_cap_for(int32_t n_max) { return std::min<int32_t>(n_max, LDS_ROW_MAX); }
 // expansion arrays, and the LDS sub-DAG tables of `table` slots (0: none; the
 // wide kernel and the dependency-row kernel use none).
 size_t table_bytes(int table) {
-    if (table == 256) return std::max(small_dag_bytes<256>(), dual_dag_bytes<256>());
-    if (table == 128) return std::max(small_dag_bytes<128>(), dual_dag_bytes<128>());
+    if (table == 256) return dag_table_bytes<256>();
+    if (table == 128) return dag_table_bytes<128>();
     return 0;
 }
 size_t source_lds_bytes(int lds_cap, int block, int table) {
