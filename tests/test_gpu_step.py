@@ -1,6 +1,6 @@
 """Edges of an update step's launches.
 
-E* sizes around the 2048 arcs one workgroup places at a time, the keep masks
+E* sizes around one and two times the 1024 arcs a workgroup places at a time, the keep masks
 scanned by their own launch (an E* capacity above 2^20 arcs), graphs up to and
 past the size where a source can be deferred, and 8 and 64 arcs per direction
 (loads go out eight at a time), on directed and undirected graphs.  Plain and
@@ -31,8 +31,8 @@ def _run(g, ups, label, **kw):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [2046, 2047, 2048, 2049])
-def test_estar_around_one_placing_chunk(n):
+@pytest.mark.parametrize("n", [1022, 1023, 1024, 1025, 2046, 2047, 2048, 2049])
+def test_estar_around_the_placing_chunks(n):
     g = W.cycle_graph(n, directed=True)
     _run(g, [W.Update("edge", u=0, v=n // 2, w=3), W.Update("edge", u=n // 2, v=0, w=2)], f"cycle {n}")
 
@@ -56,6 +56,18 @@ def test_arcs_per_update(k, directed):
     g = W.random_small(150, 0.9, 50, seed=k, directed=directed)
     cap = 2 * 150 * 150
     _run(g, W.vertex_stream(g, 2, k, 50, k), f"{k} arcs", arc_capacity=cap, estar_capacity=cap)
+
+
+@pytest.mark.parametrize("gap", [15, 16, 17, 400])
+def test_runs_of_heads_without_arcs(gap):
+    """E* arcs into every gap-th vertex only: more long runs per chunk than are listed, and none."""
+    n = 1600
+    heads = W.np.arange(gap, n, gap)
+    src = W.np.concatenate([W.np.zeros(heads.size), heads[:-1]]).astype(W.np.int32)
+    dst = W.np.concatenate([heads, heads[1:]]).astype(W.np.int32)
+    g = W.Graph(n, True, src, dst, W.np.full(src.size, 5, W.np.int64))
+    _run(g, [W.Update("edge", u=0, v=int(heads[0]), w=1), W.Update("edge", u=int(heads[0]), v=1, w=2),
+             W.Update("edge", u=0, v=n - 1, w=1)], f"gap {gap}")
 
 
 def test_nothing_to_merge_into():
