@@ -64,7 +64,8 @@ struct GraphCtl {
 
 // Per-source scalars of the update in flight (Alg 4 output).
 //   dv = d'(s,v), sv = sigma'_sv, hv = sigma-hat'_sv (new paths through E_i);
-//   flag bit 0: d'(s,v) == d(s,v) ("same"), bit 1: s is affected.
+//   flag bit 0: d'(s,v) == d(s,v) ("same"), bit 1: s is affected, bits 8..:
+//   1 + the place of the in-arc that alone attains a lower d'(s,v), else 0.
 struct SrcScal {
     int32_t dv;
     int32_t flags;
@@ -121,7 +122,7 @@ struct GraphPtrs {
     double *bc_delta;       // per-update difference, folded into (hi, lo) at commit
     // E* by head: XC current, YC with the updated arcs merged in (during an
     // update).  x_src and x_dst hold the filter's keep masks and their prefix.
-    int32_t *x_ptr, *x_src, *x_dst, *x_w;
+    int32_t *x_src, *x_dst;
     int32_t *xc_ptr, *xc_src, *xc_dst, *xc_w;
     int32_t *yc_ptr, *yc_src, *yc_dst, *yc_w;
     int32_t *es_cnt;  // n + 1 counts / offsets for rebuilding
@@ -133,6 +134,7 @@ struct GraphPtrs {
     uint64_t *rv_S;
     int32_t *rvv_D;   // row v'' after the Out phase (n)
     uint64_t *rvv_S, *rvv_H;
+    int32_t *rvv_pred;  // stored predecessors of row v''
     int32_t *tlist;   // candidate targets of the update in flight (n)
     int32_t *tl_rvD;  // d(v,t) for each candidate (compact copy)
     int32_t *tl_rvvD; // d''(v,t) for each candidate (compact copy)
@@ -161,6 +163,7 @@ struct UpdateJob {
     int32_t n_u;
     const int32_t *row_v_D;   // row v to read during the update: live row, or the snapshot
     const uint64_t *row_v_S;  // when the Out phase rewrites row v
+    const int32_t *row_v_pred;  // stored predecessors of row v'': the live row v, or rvv_pred
     int32_t in_tail[KMAX], in_w[KMAX];
     int32_t out_head[KMAX], out_w[KMAX];
     int32_t u_tail[2 * KMAX], u_head[2 * KMAX], u_w[2 * KMAX];

@@ -392,8 +392,7 @@ GraphPtrs carve(char *base, int32_t n, int64_t arc_cap, int64_t es_cap, size_t *
     const size_t nn = (size_t)n * (size_t)n;
     size_t oD = c.take(4 * nn), oS = c.take(8 * nn), oPr = c.take(4 * nn);
     size_t ohi = c.take(8 * (size_t)n), olo = c.take(8 * (size_t)n), odl = c.take(8 * (size_t)n);
-    size_t oxp = c.take(4 * ((size_t)n + 1)), oxs = c.take(4 * (size_t)es_cap), oxd = c.take(4 * (size_t)es_cap),
-           oxw = c.take(4 * (size_t)es_cap);
+    size_t orvvp = c.take(4 * (size_t)n), oxs = c.take(4 * (size_t)es_cap), oxd = c.take(4 * (size_t)es_cap);
     size_t oxcp = c.take(4 * ((size_t)n + 1)), oxcs = c.take(4 * (size_t)es_cap), oxcd = c.take(4 * (size_t)es_cap),
            oxcw = c.take(4 * (size_t)es_cap);
     size_t oyp = c.take(4 * ((size_t)n + 1)), oys = c.take(4 * (size_t)es_cap), oyd = c.take(4 * (size_t)es_cap),
@@ -421,10 +420,9 @@ GraphPtrs carve(char *base, int32_t n, int64_t arc_cap, int64_t es_cap, size_t *
     P.bc_hi = (double *)(base + ohi);
     P.bc_lo = (double *)(base + olo);
     P.bc_delta = (double *)(base + odl);
-    P.x_ptr = (int32_t *)(base + oxp);
+    P.rvv_pred = (int32_t *)(base + orvvp);
     P.x_src = (int32_t *)(base + oxs);
     P.x_dst = (int32_t *)(base + oxd);
-    P.x_w = (int32_t *)(base + oxw);
     P.xc_ptr = (int32_t *)(base + oxcp);
     P.xc_src = (int32_t *)(base + oxcs);
     P.xc_dst = (int32_t *)(base + oxcd);
@@ -917,9 +915,11 @@ void build_jobs(const GraphRec *g, int32_t v, const std::vector<std::pair<int32_
         }
         if (j.n_out > 0) {
             j.row_v_D = g->P.rv_D;
+            j.row_v_pred = g->P.rvv_pred;
             j.row_v_S = g->P.rv_S;
         } else {
             j.row_v_D = g->P.D + (size_t)v * g->n;
+            j.row_v_pred = g->P.pred + (size_t)v * g->n;
             j.row_v_S = g->P.S + (size_t)v * g->n;
         }
         out.push_back(j);

@@ -147,9 +147,12 @@ __device__ int32_t block_excl_scan(int32_t x, int32_t *sh /* >= 32 */, int32_t &
 // then the new finite d'(s,v)).  Distances and counts into column u are read
 // from row u where the graph is undirected (the state is symmetric between
 // updates): coalesced over the sources, against a cache line per source.
+// `one` is the winning in-arc's place + 1 where d'(s,v) fell and one arc
+// attains it, else 0.
 struct ScanOut {
     int64_t d0, cur;
     uint64_t sig, hat;
+    int32_t one;
 };
 
 __device__ __forceinline__ ScanOut scan_source(const UpdateJob &J, const int32_t s, bool &ovf_s, bool &ovf_d) {
@@ -180,6 +183,7 @@ __device__ __forceinline__ ScanOut scan_source(const UpdateJob &J, const int32_t
     }
     // the counts of those alone (one round trip each; rarely more than one)
     bool strict = o.cur < o.d0;
+    o.one = strict && (win & (win - 1)) == 0 ? __ffsll((unsigned long long)win) : 0;
     for (; win; win &= win - 1) {
         const uint64_t su = S[J.in_tail[__ffsll((unsigned long long)win) - 1] * cs];
         if (strict) {
@@ -203,7 +207,7 @@ __device__ __forceinline__ ScanOut scan_source(const UpdateJob &J, const int32_t
 __device__ __forceinline__ SrcScal scan_scal(const ScanOut &o, const bool aff) {
     SrcScal sc;
     sc.dv = o.cur == INF64 ? INF32 : (int32_t)o.cur;
-    sc.flags = (o.cur == o.d0 ? 1 : 0) | (aff ? 2 : 0);
+    sc.flags = (o.cur == o.d0 ? 1 : 0) | (aff ? 2 : 0) | (o.one << 8);
     sc.sv = o.sig;
     sc.hv = o.hat;
     return sc;
@@ -262,6 +266,11 @@ __device__ __forceinline__ void prep_scan(const UpdateJob &J, const int64_t firs
     if (ovf_d) atomicOr(&J.g.ctl->status, ST_DIST_OVF);
 }
 
+// Stored predecessor of a vertex whose DAG in-arcs are those of a and of b.
+__device__ __forceinline__ int32_t pred_union(const int32_t a, const int32_t b) {
+    return a == PRED_NONE ? b : b == PRED_NONE || a == b ? a : PRED_MULTI;
+}
+
 // Targets role: row v'' and the candidate targets of an update, one thread per
 // target t.
 //
@@ -271,7 +280,10 @@ __device__ __forceinline__ void prep_scan(const UpdateJob &J, const int64_t firs
 // the In-phase rule from the old rows and the scalars of the sources x_j
 // (formed here once per workgroup: the scan role writes them in the same
 // launch).  The old row v is snapshotted, since the source v itself rewrites
-// it during the update.
+// it during the update.  rvv_pred is the stored-predecessor row of v'': the
+// DAG''(v) in-arcs of t are those of DAG(v) where d''(v,t) = d(v,t), and those
+// of every DAG(x_j) whose arc attains d''(v,t) ((v,x_j) itself at t = x_j); a
+// path from x_j that enters v again attains nothing.
 //
 // Candidates: a pair (s,t) can change in the In phase only if
 // d'(s,v) + d(v,t) <= d(s,t) with d'(s,v) = d(s,u_j) + w'_j for some in-arc,
@@ -316,6 +328,7 @@ __device__ __forceinline__ void prep_targets(const UpdateJob &J, const int64_t f
             cur = dvt;
             if (J.n_out > 0) {
                 const uint64_t svt = S[(size_t)v * n + t];
+                const int32_t pvt = J.g.pred[(size_t)v * n + t];
                 J.g.rv_D[t] = dvt;
                 J.g.rv_S[t] = svt;
                 // 64-bit sums with INF64 for unreachable, as in scan_source:
@@ -347,17 +360,21 @@ __device__ __forceinline__ void prep_targets(const UpdateJob &J, const int64_t f
                 }
                 // sigma'_(x,t) of those alone, by the In rule
                 bool strict = c64 < v64;
+                int32_t pr = strict ? PRED_NONE : pvt;
                 for (; win; win &= win - 1) {
                     const int32_t k = __ffsll((unsigned long long)win) - 1, x = J.out_head[k];
                     const SrcScal sc = xs[k];
                     const int32_t d1 = D[(size_t)x * n + t];
+                    const uint64_t sxt = S[(size_t)x * n + t];
+                    const int32_t pxt = J.g.pred[(size_t)x * n + t];
+                    pr = pred_union(pr, t == x ? v : pxt);
                     int64_t c;
                     uint64_t s1;
                     const bool in = in_rule(d1, sc.dv, dvt, c) && c < INF32;
                     if (in && c < d1) {
                         s1 = mul_chk(sc.sv, svt, ovf_s);
                     } else {
-                        s1 = S[(size_t)x * n + t];
+                        s1 = sxt;
                         if (in) s1 = add_chk(s1, mul_chk((sc.flags & 1) ? sc.hv : sc.sv, svt, ovf_s), ovf_s);
                     }
                     if (strict) {
@@ -378,6 +395,7 @@ __device__ __forceinline__ void prep_targets(const UpdateJob &J, const int64_t f
                 J.g.rvv_D[t] = cur;
                 J.g.rvv_S[t] = sig;
                 J.g.rvv_H[t] = hat;
+                J.g.rvv_pred[t] = pr;
                 cand_out = cur < dvt || hat != 0;
                 cand = cand || cand_out;
             }
@@ -933,64 +951,6 @@ __device__ __forceinline__ void chunk_arcs(const ExpandShared &es, const int32_t
     }
 }
 
-// Stored predecessors of the changed pairs (s, t), t in Bt[0..nb), from the
-// new row Dnew and the merged E* by head (cptr/csrc/cw): the tail of t's only
-// DAG'(s) in-arc, else PRED_MULTI.  A pair whose distance and count did not
-// change keeps its DAG in-arcs (a new in-arc, or a tail whose own distance or
-// count changed, would change the pair), so these are the only stored
-// predecessors an update changes.  One workgroup; arc-parallel, RU arcs per
-// lane in flight.
-template <int RU>
-__device__ void refresh_preds(const int32_t *__restrict__ Dnew, const int32_t *__restrict__ cptr,
-                              const int32_t *__restrict__ csrc, const int32_t *__restrict__ cw,
-                              const int32_t *__restrict__ Bt, const int32_t nb, int32_t *pred, BlockShared &sh,
-                              const ExpandShared &es) {
-    const int tid = threadIdx.x, bs = blockDim.x;
-    for (int32_t i = tid; i < nb; i += bs) pred[Bt[i]] = PRED_NONE;
-    __syncthreads();
-    for (int32_t c = 0; c < nb; c += bs) {
-        const int32_t idx = c + tid;
-        int32_t t = 0, b0 = 0, deg = 0, dt = INF32;
-        if (idx < nb) {
-            t = Bt[idx];
-            b0 = cptr[t];
-            deg = cptr[t + 1] - b0;
-            dt = Dnew[t];
-        }
-        int32_t total;
-        const int32_t off = block_excl_scan(deg, sh.scan, total);
-        es.off[tid] = off;
-        es.vtx[tid] = t;
-        es.beg[tid] = b0;
-        es.dx[tid] = dt;
-        __syncthreads();
-        const int32_t nv = min(bs, nb - c);
-        for (int32_t j0 = tid; j0 < total; j0 += bs * RU) {
-            int32_t iv[RU], av[RU], wv[RU];
-            bool ok[RU];
-#pragma unroll
-            for (int k = 0; k < RU; ++k) {
-                const int32_t j = j0 + k * bs;
-                ok[k] = j < total;
-                iv[k] = ok[k] ? find_owner(es, nv, j) : 0;
-                const int32_t e = es.beg[iv[k]] + (j - es.off[iv[k]]);
-                av[k] = ok[k] ? csrc[e] : 0;
-                wv[k] = ok[k] ? cw[e] : 0;
-            }
-#pragma unroll
-            for (int k = 0; k < RU; ++k) {
-                if (!ok[k]) continue;
-                const int32_t da = Dnew[av[k]];
-                if (da != INF32 && (int64_t)da + wv[k] == (int64_t)es.dx[iv[k]]) {
-                    int32_t *const p = &pred[es.vtx[iv[k]]];
-                    if (atomicCAS(p, PRED_NONE, av[k]) != PRED_NONE) *p = PRED_MULTI;
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
 // The accumulation of a restricted pass over a recorded sub-DAG of nsub
 // vertices and nk arcs in LDS: the vertices are renumbered in the order they
 // were found, the arcs grouped by head, and Kahn runs as in dual_kahn (the
@@ -1006,8 +966,7 @@ __host__ __device__ constexpr inline size_t lds_kahn_bytes(const size_t nsub, co
 
 __device__ __forceinline__ void kahn_in_lds(const int32_t s, const int32_t nsub, const int32_t nk, const USlot &u,
                                             const uint64_t *__restrict__ Srow, const bool counts, const double sign,
-                                            double *out, const int32_t *__restrict__ Bt, const int32_t nB,
-                                            int32_t *new_pred, BlockShared &sh, char *buf) {
+                                            double *out, BlockShared &sh, char *buf) {
     const int tid = threadIdx.x, bs = blockDim.x;
     double *const acc = (double *)buf;
     uint64_t *const sig = (uint64_t *)(acc + nsub);  // with counts
@@ -1076,16 +1035,6 @@ __device__ __forceinline__ void kahn_in_lds(const int32_t s, const int32_t nsub,
         const double ax = acc[i];
         if (x != s && ax != 0.0) atomicAdd(&out[x], sign * ax);
     }
-    // the new stored predecessors of the changed targets: every E* in-arc of
-    // a B vertex was tested, so its recorded in-arcs are all its DAG in-arcs
-    if (new_pred)
-        for (int32_t i = tid; i < nB; i += bs) {
-            const int32_t t = Bt[i];
-            if (t == s) continue;
-            const uint32_t r = range[u.kend[t]];
-            const int32_t deg = (int32_t)(r >> 16);
-            new_pred[t] = deg == 1 ? u.sub[tails[(r & 0xffffu) - 1]] : deg == 0 ? PRED_NONE : PRED_MULTI;
-        }
     __syncthreads();
 }
 
@@ -1118,14 +1067,13 @@ __device__ __forceinline__ void kahn_in_lds(const int32_t s, const int32_t nsub,
 // independent loads or atomics before it uses any).
 // kbuf: kbytes of LDS for the accumulation of a sub-DAG that fits (0: none).
 template <bool OUT_ROW, int RU, int LU = 1>
-__device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t *__restrict__ Drow,
+__device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t *__restrict__ Drow,
                                 const uint64_t *__restrict__ Srow, const int32_t *__restrict__ cptr,
                                 const int32_t *__restrict__ csrc, const int32_t *__restrict__ cdst,
                                 const int32_t *__restrict__ cw, const int32_t *__restrict__ Bt, const int32_t nB,
                                 const bool full, const USlot &u, const double sign, double *out,
-                                const int32_t *__restrict__ pred, int32_t *new_pred, const bool b_pred,
-                                BlockShared &sh, const ExpandShared &es, char *kbuf = nullptr,
-                                const size_t kbytes = 0) {
+                                const int32_t *__restrict__ pred, BlockShared &sh, const ExpandShared &es,
+                                char *kbuf = nullptr, const size_t kbytes = 0) {
     const int tid = threadIdx.x, bs = blockDim.x;
     const int32_t kcap = (int32_t)u.kcap;
     if (tid == 0) {
@@ -1156,9 +1104,7 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
     __syncthreads();
     int32_t nsub;
     bool rec = false;  // Kahn walks recorded arcs
-    // a full pass over a B that covers much of the row tests most in-arcs
-    // anyway: one coalesced sweep over E* serves it better than the list
-    const bool sweep = full && (!pred || (int64_t)nB * 4 >= (int64_t)n);
+    const bool sweep = full && !pred;
     if (sweep) {
         // 1. every DAG(s) arc: one more successor of its tail, and (with an
         //    arc record) the arc itself with one more arc into its head
@@ -1195,9 +1141,8 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
             }
         }
     } else if (full) {
-        // 1. every reachable vertex's DAG(s) in-arcs: its stored predecessor
-        //    (an unchanged pair keeps its DAG in-arcs), else (a changed target,
-        //    or two or more in-arcs) Eq.1 over its E* in-arcs, below
+        // 1. every reachable vertex's DAG(s) in-arcs: its stored predecessor,
+        //    else (two or more in-arcs) Eq.1 over its E* in-arcs, below
         for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
             int32_t pv[LU];
             bool live[LU];
@@ -1207,9 +1152,9 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
                 live[k] = false;
                 pv[k] = PRED_MULTI;
                 if (x < n) {
-                    const int32_t dx = Drow[x], o = u.outdeg[x], pr = pred[x];
+                    const int32_t dx = Drow[x];
+                    pv[k] = pred[x];
                     live[k] = x != s && dx != INF32;
-                    pv[k] = ((o & W_B) && !b_pred) ? PRED_MULTI : pr;
                 }
             }
 #pragma unroll
@@ -1237,21 +1182,19 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
         // 1. backward walk from B.  A lane follows a chain of stored
         //    predecessors itself (a vertex's one DAG in-arc, then its tail's,
         //    and so on) until it reaches a vertex already in the sub-DAG, or
-        //    s, or a vertex with two or more DAG in-arcs.  Those vertices (and
-        //    the B vertices whose stored predecessor may not be read) test
+        //    s, or a vertex with two or more DAG in-arcs.  Those vertices test
         //    their E* in-arcs by Eq.1 in a round of their own, arc-parallel,
         //    and the tails first found there start the next round's walks.
         //    So the rounds follow the vertices with two or more in-arcs along
         //    a path, not its levels.
         int32_t wlo = 0, whi = sh.next;
-        bool first = true;
         for (;;) {
             if (tid == 0) sh.head = 0;
             __syncthreads();
             for (int32_t idx = wlo + tid; idx < whi; idx += bs) {
                 int32_t x = u.sub[idx];
                 int32_t p = PRED_MULTI;
-                if (pred && (b_pred || !first || !(u.outdeg[x] & W_B))) p = pred[x];
+                if (pred) p = pred[x];
                 for (;;) {
                     if (p < 0) {
                         // s has no DAG in-arc; any other vertex tests E*
@@ -1276,7 +1219,6 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
                     p = pp;
                 }
             }
-            first = false;
             __syncthreads();
             const int32_t nslow = sh.head;
             if (nslow == 0) break;
@@ -1331,90 +1273,53 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
             whi = sh.next;
         }
     } else if (!sweep) {
-        // 1. one round over the vertices to test (a full pass: the others
-        //    took their stored predecessor above), arc-parallel.  B vertices
-        //    (always) and vertices with two or more DAG in-arcs test their E*
-        //    in-arcs by Eq.1.
-        int32_t lo = 0, hi = sh.next;
-        __syncthreads();
-        while (lo < hi) {
-            if (tid == 0) sh.head = 0;
-            __syncthreads();
-            // the stored arcs first, one lane per vertex; the vertices that
-            // test E* in-arcs go to the level's general list (the Kahn queue,
-            // idle until the walk ends)
-            for (int32_t idx = lo + tid; idx < hi; idx += bs) {
-                const int32_t x = u.sub[idx];
-                const int32_t p = (pred && (b_pred || !(u.outdeg[x] & W_B))) ? pred[x] : PRED_MULTI;
-                if (p < 0) {
-                    u.q1[atomicAdd(&sh.head, 1)] = x;
-                    continue;
-                }
-                if ((atomicAdd(&u.outdeg[p], 1) & (W_COUNT | W_VIS)) == 0 && !full)
-                    u.sub[atomicAdd(&sh.next, 1)] = p;
-                if (kcap > 0) {
-                    const int32_t k = atomicAdd(&sh.nk, 1);
-                    if (k < kcap) {
-                        u.ka[k] = p;
-                        u.kb[k] = x;
-                        atomicAdd(&u.kcnt[x], 1);
-                    }
-                }
+        // the vertices of a full pass with two or more DAG in-arcs test their
+        // E* in-arcs by Eq.1, arc-parallel
+        const int32_t nslow = sh.next;
+        for (int32_t c = 0; c < nslow; c += bs) {
+            const int32_t idx = c + tid;
+            int32_t x = 0, b0 = 0, deg = 0, dx = 0;
+            if (idx < nslow) {
+                x = u.sub[idx];
+                b0 = cptr[x];
+                deg = cptr[x + 1] - b0;
+                dx = Drow[x];
             }
+            int32_t total;
+            const int32_t off = block_excl_scan(deg, sh.scan, total);
+            es.off[tid] = off;
+            es.vtx[tid] = x;
+            es.beg[tid] = b0;
+            es.dx[tid] = dx;
             __syncthreads();
-            const int32_t nslow = sh.head;
-            for (int32_t c = 0; c < nslow; c += bs) {
-                const int32_t idx = c + tid;
-                int32_t x = 0, b0 = 0, deg = 0, dx = 0;
-                if (idx < nslow) {
-                    x = u.q1[idx];
-                    b0 = cptr[x];
-                    deg = cptr[x + 1] - b0;
-                    dx = Drow[x];
+            const int32_t nv = min(bs, nslow - c);
+            for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
+                int32_t iv[RU], ev[RU], av[RU], wv[RU];
+                bool ok[RU];
+                chunk_arcs(es, nv, total, jb, iv, ev, ok);
+#pragma unroll
+                for (int k = 0; k < RU; ++k) {
+                    av[k] = ok[k] ? csrc[ev[k]] : 0;
+                    wv[k] = ok[k] ? cw[ev[k]] : 0;
                 }
-                int32_t total;
-                const int32_t off = block_excl_scan(deg, sh.scan, total);
-                es.off[tid] = off;
-                es.vtx[tid] = x;
-                es.beg[tid] = b0;
-                es.dx[tid] = dx;
-                __syncthreads();
-                const int32_t nv = min(bs, nslow - c);
-                for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
-                    int32_t iv[RU], ev[RU], av[RU], wv[RU];
-                    bool ok[RU];
-                    chunk_arcs(es, nv, total, jb, iv, ev, ok);
 #pragma unroll
-                    for (int k = 0; k < RU; ++k) {
-                        av[k] = ok[k] ? csrc[ev[k]] : 0;
-                        wv[k] = ok[k] ? cw[ev[k]] : 0;
-                    }
-#pragma unroll
-                    for (int k = 0; k < RU; ++k) {
-                        if (!ok[k]) continue;
-                        const int32_t a = av[k];
-                        const int32_t da = Drow[a];
-                        if (da == INF32 || (int64_t)da + wv[k] != (int64_t)es.dx[iv[k]]) continue;
-                        // one more successor inside the sub-DAG; the first arc
-                        // found into a vertex not yet seen adds it to the list
-                        // (a full pass has every vertex already)
-                        if ((atomicAdd(&u.outdeg[a], 1) & (W_COUNT | W_VIS)) == 0 && !full)
-                            u.sub[atomicAdd(&sh.next, 1)] = a;
-                        if (kcap > 0) {
-                            const int32_t p = atomicAdd(&sh.nk, 1);
-                            if (p < kcap) {
-                                const int32_t x = es.vtx[iv[k]];
-                                u.ka[p] = a;
-                                u.kb[p] = x;
-                                atomicAdd(&u.kcnt[x], 1);
-                            }
+                for (int k = 0; k < RU; ++k) {
+                    if (!ok[k]) continue;
+                    const int32_t a = av[k];
+                    const int32_t da = Drow[a];
+                    if (da == INF32 || (int64_t)da + wv[k] != (int64_t)es.dx[iv[k]]) continue;
+                    atomicAdd(&u.outdeg[a], 1);
+                    if (kcap > 0) {
+                        const int32_t p = atomicAdd(&sh.nk, 1);
+                        if (p < kcap) {
+                            const int32_t h = es.vtx[iv[k]];
+                            u.ka[p] = a;
+                            u.kb[p] = h;
+                            atomicAdd(&u.kcnt[h], 1);
                         }
                     }
                 }
-                __syncthreads();
             }
-            lo = hi;
-            hi = full ? hi : sh.next;
             __syncthreads();
         }
     }
@@ -1475,9 +1380,8 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
         const int32_t nk = sh.nk;
         rec = kcap > 0 && nk <= kcap;
         if (!OUT_ROW && rec && nk < 0xffff && nsub < 0xffff && lds_kahn_bytes(nsub, nk, false) <= kbytes) {
-            kahn_in_lds(s, nsub, nk, u, Srow, lds_kahn_bytes(nsub, nk, true) <= kbytes, sign, out, Bt, nB, new_pred, sh,
-                        kbuf);
-            return new_pred != nullptr;
+            kahn_in_lds(s, nsub, nk, u, Srow, lds_kahn_bytes(nsub, nk, true) <= kbytes, sign, out, sh, kbuf);
+            return;
         }
         if (rec) {
             // group the recorded arcs by head (the sub-DAG vertices)
@@ -1515,15 +1419,16 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
         if (pred || rec) {
             // a vertex with one DAG in-arc (a, x): sigma_sx = sigma_sa, so a
             // receives [x in B] + acc(x) itself (no count, no scan).  Its
-            // tail is the stored predecessor for a vertex outside B, else
-            // the one recorded arc.  The others go to the back of the next
+            // tail is the stored predecessor, or the one recorded arc where
+            // none are stored.  The others go to the back of the next
             // round's queue (the two never meet: a vertex queued for the
             // next round is not in this one) for the general step.
             for (int32_t idx = tid; idx < qn; idx += bs) {
                 const int32_t x = qa[idx];
                 const bool in_b = (u.outdeg[x] & W_B) != 0;
-                int32_t p = (pred && (b_pred || !in_b)) ? pred[x] : PRED_MULTI;
-                if (p < 0 && rec && u.kcnt[x] == 1) p = u.kr[u.kend[x] - 1];
+                int32_t p = PRED_MULTI;
+                if (pred) p = pred[x];
+                else if (u.kcnt[x] == 1) p = u.kr[u.kend[x] - 1];
                 if (p < 0) {
                     qb[n - 1 - atomicAdd(&sh.kpos, 1)] = x;
                     continue;
@@ -1611,35 +1516,6 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
         qb = tmp;
         __syncthreads();
     }
-    // the new stored predecessors of the changed targets: every E* in-arc of
-    // a B vertex was tested, so its recorded in-arcs are all its DAG in-arcs
-    const bool preds_done = rec && new_pred != nullptr;
-    if (preds_done) {
-        for (int32_t i0 = tid; i0 < nB; i0 += LU * bs) {
-            int32_t tv[LU], cv[LU], ev[LU];
-            bool live[LU];
-#pragma unroll
-            for (int k = 0; k < LU; ++k) tv[k] = i0 + k * bs < nB ? Bt[i0 + k * bs] : s;
-#pragma unroll
-            for (int k = 0; k < LU; ++k) {
-                live[k] = false;
-                cv[k] = 0;
-                ev[k] = 0;
-                if (tv[k] != s) {
-                    const int32_t dt = Drow[tv[k]];
-                    cv[k] = u.kcnt[tv[k]];
-                    ev[k] = u.kend[tv[k]];
-                    live[k] = dt != INF32;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < LU; ++k) {
-                if (!live[k]) continue;
-                new_pred[tv[k]] = cv[k] == 1 ? u.kr[ev[k] - 1] : cv[k] == 0 ? PRED_NONE : PRED_MULTI;
-            }
-        }
-        __syncthreads();
-    }
     if (full) {
         for (int32_t x = tid; x < n; x += bs) {
             u.outdeg[x] = 0;
@@ -1655,7 +1531,6 @@ __device__ bool restricted_pass(const int32_t s, const int32_t n, const int32_t 
         }
     }
     __syncthreads();
-    return preds_done;
 }
 
 // Small sub-DAGs in LDS.  Most sources' sub-DAGs hold a few dozen vertices,
@@ -1756,8 +1631,7 @@ template <int TS>
 __device__ bool small_pass(const int32_t s, const int32_t *__restrict__ Drow, const uint64_t *__restrict__ Srow,
                            const int32_t *__restrict__ cptr, const int32_t *__restrict__ csrc,
                            const int32_t *__restrict__ cw, const int32_t *__restrict__ Bt, const int32_t nB,
-                           const double sign, double *out, const int32_t *__restrict__ pred, const bool b_pred,
-                           BlockShared &sh, const ExpandShared &es, const SmallDag &d) {
+                           const double sign, double *out, const int32_t *__restrict__ pred, BlockShared &sh, const ExpandShared &es, const SmallDag &d) {
     SD_CONSTS
     const int tid = threadIdx.x, bs = blockDim.x;
     for (int32_t i = tid; i < SD_SLOTS; i += bs) {
@@ -1796,13 +1670,13 @@ __device__ bool small_pass(const int32_t s, const int32_t *__restrict__ Drow, co
     while (lo < hi) {
         if (tid == 0) sh.head = 0;
         __syncthreads();
-        // a vertex with one stored predecessor (outside B, or any with
-        // b_pred): that arc, at once; the others (their E* in-arcs tested)
-        // listed in d.round, idle until the accumulation
+        // a vertex with one stored predecessor: that arc, at once; the others
+        // (their E* in-arcs tested) listed in d.round, idle until the
+        // accumulation
         for (int32_t idx = lo + tid; idx < hi; idx += bs) {
             const int32_t sx = d.sub[idx];
             const int32_t x = d.key[sx];
-            const int32_t p = (pred && (b_pred || !(d.flags[sx] & F_B))) ? pred[x] : PRED_MULTI;
+            const int32_t p = pred[x];
             if (p < 0) {
                 d.round[atomicAdd(&sh.head, 1)] = sx;
                 continue;
@@ -1881,21 +1755,25 @@ __device__ bool small_pass(const int32_t s, const int32_t *__restrict__ Drow, co
     return true;
 }
 
-// Alg 2 (Update-DAG) on the stored predecessors, for a one-arc update (u, v)
-// and a changed target t of source s.  A target whose distance fell
-// (WT-changed) has exactly its DAG(v) in-arcs as DAG'(s) in-arcs, or the arc
-// (u, v) alone when t = v; one whose distance stayed (NUM-changed) keeps its
-// old in-arcs and gains those (at v: gains (u, v), so it has two or more).
-// DAG(v) itself does not change (no shortest path from v enters v again), so
-// row v of the predecessors is read as it stands while other rows change.
-__device__ __forceinline__ bool one_arc_job(const UpdateJob &J) { return J.n_in == 1 && J.n_out == 0; }
-
-__device__ __forceinline__ int32_t edge_pred(const UpdateJob &J, const int32_t t, const int32_t old_pred,
-                                             const bool fell) {
-    if (t == J.v) return fell ? J.in_tail[0] : PRED_MULTI;
-    const int32_t pv = J.g.pred[(size_t)J.v * J.g.n + t];
-    if (fell) return pv;
-    return old_pred >= 0 && old_pred == pv ? pv : PRED_MULTI;
+// Alg 2 (Update-DAG) on the stored predecessors: the new one of a changed
+// target t of source s.  A target whose distance fell has exactly its DAG''(v)
+// in-arcs as DAG'(s) in-arcs (at t = v: the in-arcs of the update that attain
+// d'(s,v)); one whose distance stayed keeps its old in-arcs and gains those (at
+// v: gains an arc, so it has two or more).  The row of v'' is that of v itself
+// without out-arcs (no shortest path from v enters v again, so that row stands
+// while others change), else the one the targets role formed.
+// Testing the E* in-arcs of every changed target by Eq.1 instead (which any
+// update but that of one arc did) is a round of gathers per pass and a record
+// of all arcs per changed target: a submitted batch at n = 32768 took 34.4 ms
+// that way and takes 32.0, a served queue of three Chung-Lu graphs 16.6 and 14.9.
+__device__ __forceinline__ int32_t new_pred(const UpdateJob &J, const int32_t s, const int32_t t,
+                                            const int32_t old_pred, const bool fell) {
+    if (t == J.v) {
+        const int32_t one = fell ? J.g.scal[s].flags >> 8 : 0;
+        return one ? J.in_tail[one - 1] : PRED_MULTI;
+    }
+    const int32_t pv = J.row_v_pred[t];
+    return fell ? pv : pred_union(old_pred, pv);
 }
 
 // Old and new partial dependency of one source in one traversal (LDS only).
@@ -1914,11 +1792,10 @@ __device__ __forceinline__ int32_t edge_pred(const UpdateJob &J, const int32_t t
 // The walk is bound by its dependent loads.  A lane follows a chain of single
 // in-arcs by itself (dd_follow), one load of the stored predecessors' row per
 // vertex: a vertex with one DAG in-arc has its tail's path count, and its
-// distance is needed only where Eq.1 is tested.  After a one-arc update the
-// changed targets' new in-arcs come from Alg 2 like stored ones.  Only vertices
-// with two or more in-arcs (and the changed targets of other updates) test
-// their E* in-arcs, in rounds of the whole workgroup; a tail's count and
-// predecessor are read when it has passed the test.  A listed source of the
+// distance is needed only where Eq.1 is tested.  The changed targets' new
+// in-arcs come from Alg 2 like stored ones.  Only vertices with two or more
+// in-arcs test their E* in-arcs, in rounds of the whole workgroup; a tail's
+// count and predecessor are read when it has passed the test.  A listed source of the
 // n = 32768 Chung-Lu updates takes 28 us, one of a 64-vertex graph 14.6; level by
 // level, with distance, count and predecessor read for every vertex and every
 // tested arc, 35 and 17.6.
@@ -1930,7 +1807,7 @@ __device__ __forceinline__ int32_t edge_pred(const UpdateJob &J, const int32_t t
 enum : int32_t { DF_O = 1, DF_N = 2, DF_B = 4 };
 
 struct DualDag {
-    int32_t *key, *flags, *cnt, *dold, *dnew, *round, *pr, *ybeg, *ydeg, *xdeg, *front, *slow, *arcs;
+    int32_t *key, *flags, *cnt, *dold, *dnew, *pr, *ybeg, *ydeg, *xdeg, *front, *slow, *arcs;
     double *acc_o, *acc_n, *coef;
     uint64_t *sold, *snew;
     // after the walk: the recorded arcs grouped by head (harc over ybeg and
@@ -1943,7 +1820,7 @@ struct DualDag {
 template <int TS>
 __host__ __device__ constexpr size_t dual_dag_bytes() {
     DD_CONSTS
-    return (size_t)DD_SLOTS * (10 * 4 + 5 * 8) + (size_t)DD_FRONT * 8 + (size_t)DD_ARCS * 4 + 256;
+    return (size_t)DD_SLOTS * (9 * 4 + 5 * 8) + (size_t)DD_FRONT * 8 + (size_t)DD_ARCS * 4 + 256;
 }
 
 template <int TS>
@@ -1960,14 +1837,12 @@ __device__ __forceinline__ DualDag dual_dag_at(char *p) {
     d.cnt = (int32_t *)p;     p += 4 * DD_SLOTS;  // successors: old in bits 0-15, new in 16-31
     d.dold = (int32_t *)p;    p += 4 * DD_SLOTS;
     d.dnew = (int32_t *)p;    p += 4 * DD_SLOTS;
-    d.round = (int32_t *)p;   p += 4 * DD_SLOTS;
     d.pr = (int32_t *)p;      p += 4 * DD_SLOTS;  // changed targets: stored (old) predecessor
     d.ybeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // changed targets: merged E* in-arcs (start,
     d.ydeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // count,
     d.xdeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // and how many are old E* arcs), or with a
                                                   // count of -1 their one new in-arc's tail
-    d.front = (int32_t *)p;   p += 4 * DD_FRONT;  // the changed targets' slots; after the walk
-                                                  // the new stored predecessor of each
+    d.front = (int32_t *)p;   p += 4 * DD_FRONT;  // the changed targets' slots
     d.slow = (int32_t *)p;    p += 4 * DD_FRONT;  // slot | memberships << 16 whose E* in-arcs are tested
     d.arcs = (int32_t *)p;                        // tail slot | head slot << 8 | kinds << 16
     d.harc = d.ybeg;
@@ -2155,7 +2030,6 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
                           const ExpandShared &es, const DualDag &d) {
     DD_CONSTS
     const int tid = threadIdx.x, bs = blockDim.x;
-    const bool edge = one_arc_job(J);
     for (int32_t i = tid; i < DD_SLOTS; i += bs) {
         d.key[i] = -1;
         d.flags[i] = 0;
@@ -2186,15 +2060,7 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
         const int32_t dt = Dold[t], dn = Bd[i];
         const uint64_t st = Sold[t];
         const int32_t pt = pred[t];
-        int32_t yb, ye = 0, xb = 0, xe = 0;
-        if (edge) {
-            yb = edge_pred(J, t, pt, dn < dt);
-        } else {
-            yb = ycp[t];
-            ye = ycp[t + 1];
-            xb = xcp[t];
-            xe = xcp[t + 1];
-        }
+        int32_t yb = new_pred(J, s, t, pt, dn < dt), deg = -1, olen = 0;
         const int32_t mem = DF_N | (dt != INF32 ? DF_O : 0);
         d.flags[slot] = DF_B | mem;
         d.dold[slot] = dt;
@@ -2202,18 +2068,15 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
         d.sold[slot] = dt != INF32 ? st : 0;
         d.snew[slot] = Bs[i];
         d.pr[slot] = pt;
-        if (edge && yb < 0) {
+        if (yb < 0) {
             // two or more new in-arcs
             yb = ycp[t];
-            ye = ycp[t + 1];
-            xb = xcp[t];
-            xe = xcp[t + 1];
-            d.ydeg[slot] = ye - yb;
-        } else {
-            d.ydeg[slot] = edge ? -1 : ye - yb;
+            deg = ycp[t + 1] - yb;
+            olen = xcp[t + 1] - xcp[t];
         }
         d.ybeg[slot] = yb;
-        d.xdeg[slot] = xe - xb;
+        d.ydeg[slot] = deg;
+        d.xdeg[slot] = olen;
         d.front[pos] = slot;
     }
     __syncthreads();
@@ -2303,23 +2166,6 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
     }
     if (ovf) return false;
     const int32_t narcs = sh.tail;
-    // the new stored predecessor of each changed target: its only recorded
-    // new-DAG in-arc (every new in-arc of a changed target was tested and
-    // recorded when it was expanded), else MULTI
-    for (int32_t i = tid; i < DD_SLOTS; i += bs) d.round[i] = 0;
-    __syncthreads();
-    for (int32_t k = tid; k < narcs; k += bs) {
-        const int32_t e = d.arcs[k];
-        if (!((e >> 16) & DF_N)) continue;
-        const int32_t sx = (e >> 8) & 0xff;
-        if (!(d.flags[sx] & DF_B)) continue;
-        if (atomicAdd(&d.round[sx], 1) == 0) d.front[sx] = d.key[e & 0xff];
-    }
-    __syncthreads();
-    for (int32_t i = tid; i < DD_SLOTS; i += bs)
-        if (d.key[i] >= 0 && (d.flags[i] & DF_B) && d.round[i] != 1)
-            d.front[i] = d.round[i] == 0 ? PRED_NONE : PRED_MULTI;
-    __syncthreads();
     dual_group_arcs<TS>(d, narcs, sh);
     dual_kahn<TS>(d, sh);
     for (int32_t i = tid; i < DD_SLOTS; i += bs) {
@@ -2780,36 +2626,23 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     // predecessors), the new one tries the LDS table first
     if (!dual)
         restricted_pass<false, XU>(s, n, Drow, Sg, J.g.xc_ptr, J.g.xc_src, J.g.xc_dst, J.g.xc_w, Bt, nb, false, u,
-                                   -1.0, bc_delta, pred_row, nullptr, true, sh, es, table, dag_table_bytes<TS>());
-    // a one-arc update gives the changed targets' new predecessors by Alg 2
-    // (before the old distances are overwritten); the new pass then follows
-    // them like any stored predecessor and tests no E* in-arcs of B
-    const bool edge = one_arc_job(J);
+                                   -1.0, bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
+    // the changed targets' new predecessors by Alg 2 (before the old distances
+    // are overwritten); the new pass follows them like any stored predecessor
     for (int32_t i = tid; i < nb; i += bs) {
         const int32_t t = Bt[i];
         const int32_t d = Bd[i];
-        if (edge && !dual) pred_row[t] = edge_pred(J, t, pred_row[t], d < Drow[t]);
+        pred_row[t] = new_pred(J, s, t, pred_row[t], d < Drow[t]);
         Sg[t] = Bs[i];
         Dg[t] = d;
         if (lds) lds_row[t] = d;
-        if (dual) {
-            // the union walk found the changed targets' new predecessors
-            const int32_t sl = dd_find<TS>(dd, t);
-            if (sl >= 0) pred_row[t] = dd.front[sl];
-        }
     }
     __syncthreads();
     if (dual) return;
-    // the new pass reads the stored predecessors of unchanged pairs only (and
-    // of a one-arc update's changed targets, written above), so it may write
-    // the changed targets' new ones from its arc record
-    bool preds_done = false;
-    if (!fits || !small_pass<TS>(s, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row,
-                                 edge, sh, es, sd))
-        preds_done = restricted_pass<false, XU>(s, n, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_dst, J.g.yc_w, Bt, nb,
-                                                false, u, 1.0, bc_delta, pred_row, edge ? nullptr : pred_row, edge, sh,
-                                                es, table, dag_table_bytes<TS>());
-    if (!preds_done && !edge) refresh_preds<4>(Drow, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, pred_row, sh, es);
+    if (!fits || !small_pass<TS>(s, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row, sh,
+                                 es, sd))
+        restricted_pass<false, XU>(s, n, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_dst, J.g.yc_w, Bt, nb, false, u, 1.0,
+                                   bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
 }
 
 // The sources of a step's segments (one list per job, or two), numbered
@@ -2946,9 +2779,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))
 // one workgroup of up to 1024 threads per unit of work.  The first
 // item_regions deferred sources (over the jobs in order) run as two units on
 // two workgroups at once: the old pass (it also stores the changed pairs in
-// the source's item region) and the new pass (it forms the new row and path
-// counts in its slot from the old ones and the changed pairs).  Neither
-// writes D or sigma; k_wide_apply does afterwards.  Further deferred sources
+// the source's item region) and the new pass (it forms the new row, path counts
+// and stored predecessors in its slot from the old ones and the changed pairs).
+// Neither writes D, sigma or the predecessors; k_wide_apply does afterwards.  Further deferred sources
 // run as one unit each: scan, old pass, write the changed pairs, new pass.
 // Every unit scans its row again into the slot's full-length list.
 __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restrict__ jobs,
@@ -2977,7 +2810,6 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         const int32_t t_count = *(volatile int32_t *)&ctl->t_count;
         const bool use_tlist = (int64_t)t_count * 8 <= (int64_t)n;
         const BList L{u.bl_t, u.bl_d, u.bl_s, n};
-        const bool edge = one_arc_job(J);
         bool ovf_s = false, ovf_d = false;
         if (tid == 0) {
             sh.nb = 0;
@@ -3020,34 +2852,43 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         // more than B itself (a hub update with 19 000 deferred sources
         // took 80 ms this way, 127 ms with whole-DAG passes from 1/16)
         const bool full = (int64_t)nb * 2 >= (int64_t)n;
-        bool preds_done = false;
         // phase 0: old pass (roles 0 and 2); phase 1: new pass (roles 1 and 2)
         for (int ph = role == 1 ? 1 : 0; ph <= (role == 0 ? 0 : 1); ++ph) {
             const int32_t *Dr = lds ? lds_row : Dg;
             const uint64_t *Sr = Sg;
+            const int32_t *Pr = pred_row;
             if (ph == 1) {
                 if (role == 1) {
-                    // the new row and counts: the old ones with the changed pairs in
+                    // the new row, counts and predecessors: the old ones with the
+                    // changed pairs in (the predecessors over the list's counts,
+                    // which are in the row by then)
                     int32_t *Dn = lds ? lds_row : u.dnew;
                     if (!lds)
                         for (int32_t t = tid; t < n; t += bs) u.dnew[t] = Dg[t];
-                    for (int32_t t = tid; t < n; t += bs) u.snew[t] = Sg[t];
+                    copy_row<4>(u.snew, Sg, n);
                     __syncthreads();
                     for (int32_t i = tid; i < nb; i += bs) {
                         const int32_t t = u.bl_t[i];
-                        if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], u.bl_d[i] < Dn[t]);
-                        Dn[t] = u.bl_d[i];
+                        const int32_t d = u.bl_d[i];
                         u.snew[t] = u.bl_s[i];
+                        u.bl_d[i] = new_pred(J, s, t, pred_row[t], d < Dn[t]);
+                        Dn[t] = d;
                     }
+                    __syncthreads();
+                    int32_t *const Pn = (int32_t *)u.bl_s;
+                    copy_row<4>(Pn, pred_row, n);
+                    __syncthreads();
+                    for (int32_t i = tid; i < nb; i += bs) Pn[u.bl_t[i]] = u.bl_d[i];
                     Dr = Dn;
                     Sr = u.snew;
+                    Pr = Pn;
                 } else {
                     int32_t *Dw = J.g.D + (size_t)s * n;
                     uint64_t *Sw = J.g.S + (size_t)s * n;
                     for (int32_t i = tid; i < nb; i += bs) {
                         const int32_t t = u.bl_t[i];
                         const int32_t d = u.bl_d[i];
-                        if (edge) pred_row[t] = edge_pred(J, t, pred_row[t], d < (lds ? lds_row[t] : Dw[t]));
+                        pred_row[t] = new_pred(J, s, t, pred_row[t], d < (lds ? lds_row[t] : Dw[t]));
                         Sw[t] = u.bl_s[i];
                         Dw[t] = d;
                         if (lds) lds_row[t] = d;
@@ -3055,31 +2896,15 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
                 }
                 __syncthreads();
             }
-            // The old pass of a paired source tests its B vertices' E*
-            // in-arcs, so it never uses a stored predecessor that its new
-            // pass (another workgroup, at the same time) rewrites: its walk
-            // may load one ahead, but stops at the B vertex, which is in the
-            // sub-DAG from the start.  A source updated by one workgroup
-            // rewrites its predecessors only after the old pass, so that
-            // pass takes the B vertices' stored (old) predecessors.  The new
-            // pass of a one-arc update takes theirs from Alg 2 (written
-            // above); other updates test the B vertices' E* in-arcs and
-            // write the predecessors from the arc record
-            preds_done = restricted_pass<false, 2, 4>(
-                s, n, Dr, Sr, ph ? J.g.yc_ptr : J.g.xc_ptr, ph ? J.g.yc_src : J.g.xc_src,
-                ph ? J.g.yc_dst : J.g.xc_dst, ph ? J.g.yc_w : J.g.xc_w, u.bl_t, nb, full, u, ph ? 1.0 : -1.0,
-                J.g.bc_delta, pred_row, ph && !edge ? pred_row : nullptr, ph ? edge : role == 2, sh, es);
+            restricted_pass<false, 2, 4>(s, n, Dr, Sr, ph ? J.g.yc_ptr : J.g.xc_ptr, ph ? J.g.yc_src : J.g.xc_src,
+                                         ph ? J.g.yc_dst : J.g.xc_dst, ph ? J.g.yc_w : J.g.xc_w, u.bl_t, nb, full, u,
+                                         ph ? 1.0 : -1.0, J.g.bc_delta, Pr, sh, es);
         }
-        // the new row of the new pass: in LDS, in the slot (role 1 without
-        // staging) or written back to D (role 2)
-        if (role != 0 && !preds_done && !edge)
-            refresh_preds<1>(lds ? lds_row : role == 1 ? u.dnew : Dg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, u.bl_t, nb,
-                             pred_row, sh, es);
     }
 }
 
-// Writes the changed pairs of the deferred sources whose two passes ran
-// apart (same item-region assignment as k_source_wide).
+// Writes the changed pairs (and, by Alg 2, their predecessors) of the deferred
+// sources whose two passes ran apart (same item-region assignment as k_source_wide).
 __global__ void __launch_bounds__(256) k_wide_apply(const UpdateJob *__restrict__ jobs,
                                                     const int32_t *__restrict__ njobs_p, char *__restrict__ items,
                                                     int32_t item_regions, int32_t n_layout) {
@@ -3109,9 +2934,10 @@ __global__ void __launch_bounds__(256) k_wide_apply(const UpdateJob *__restrict_
             const int32_t nb = *ir.nb;
             int32_t *Dg = J.g.D + (size_t)s * n;
             uint64_t *Sg = J.g.S + (size_t)s * n;
+            int32_t *pred_row = J.g.pred + (size_t)s * n;
             const int32_t stride = per * (int32_t)blockDim.x;
             for (int32_t i0 = slice * (int32_t)blockDim.x + (int32_t)threadIdx.x; i0 < nb; i0 += U * stride) {
-                int32_t tv[U], dv[U];
+                int32_t tv[U], dv[U], od[U], op[U];
                 uint64_t sv[U];
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
@@ -3126,8 +2952,15 @@ __global__ void __launch_bounds__(256) k_wide_apply(const UpdateJob *__restrict_
 #pragma unroll
                 for (int k = 0; k < U; ++k)
                     if (tv[k] >= 0) {
+                        od[k] = Dg[tv[k]];
+                        op[k] = pred_row[tv[k]];
+                    }
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (tv[k] >= 0) {
                         Dg[tv[k]] = dv[k];
                         Sg[tv[k]] = sv[k];
+                        pred_row[tv[k]] = new_pred(J, s, tv[k], op[k], dv[k] < od[k]);
                     }
             }
         }
@@ -3881,7 +3714,7 @@ __device__ __forceinline__ void delta_row(const GraphPtrs &G, int32_t s, char *_
     if (lds) Drow = lds_row;
     __syncthreads();
     restricted_pass<true, XU>(s, n, Drow, G.S + (size_t)s * n, G.xc_ptr, G.xc_src, G.xc_dst, G.xc_w, u.bl_t, sh.nb,
-                              true, u, 1.0, out_row, nullptr, nullptr, false, sh, es);
+                              true, u, 1.0, out_row, nullptr, sh, es);
 }
 
 __global__ void __launch_bounds__(1024) k_delta_row(const UpdateJob *__restrict__ jobs, int32_t s, char *__restrict__ scratch,
