@@ -525,6 +525,7 @@ struct LaunchShape {
     char *src_base, *wide_base, *items_base;
     int item_regions;
     int wide_lds_cap; // and its LDS staging limit
+    size_t wide_lds;  // dynamic LDS of the wide kernel
     int32_t n_layout;
     bool may_defer;      // some source may go to the wide kernel
     bool es_long;        // some E* may hold more than ES_LONG arcs
@@ -561,8 +562,8 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part,
             HIPCHK(hipEventRecord(ctx->fork_ev, st));
             HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
             hipLaunchKernelGGL(k_source_wide, dim3(L.wide_slots), dim3(ctx->wide_block),
-                               source_lds_bytes(L.wide_lds_cap, ctx->wide_block, 0), st, jobs, nj, L.wide_base,
-                               L.wide_bytes, L.wide_lds_cap, L.n_layout, L.items_base, L.item_regions, pool);
+                               L.wide_lds, st, jobs, nj, L.wide_base, L.wide_bytes, L.wide_lds_cap, L.n_layout,
+                               L.items_base, L.item_regions, pool, L.wide_lds);
         }
         const size_t lds = source_lds_bytes(L.src_lds_cap, ctx->block, ctx->table);
         if (ctx->table == 128)
@@ -664,7 +665,14 @@ bc_status shape_for(bc_ctx *ctx, const std::vector<UpdateJob> &jobs, LaunchShape
     const size_t wide_lds = source_lds_bytes(L->n_max, ctx->wide_block, 0);
     const bool stage = ctx->wide_stage == 1 && wide_lds <= ctx->wide_lds_limit;
     L->wide_lds_cap = stage ? L->n_max : 0;
-    const int per_cu = (stage && wide_lds * 2 > ctx->wide_lds_limit) || ctx->wide_block > 512 ? 1 : 2;
+    // past the row, LDS for a pass's accumulation: 20 bytes per vertex where
+    // that fits (a whole row at n = 8192 in 12, see full_pass, or a sub-DAG of
+    // up to 8000 vertices of any n, see kahn_in_lds)
+    L->wide_lds = source_lds_bytes(L->wide_lds_cap, ctx->wide_block, 0);
+    if (stage)
+        L->wide_lds = std::max(L->wide_lds, std::min(ctx->wide_lds_limit & ~(size_t)255,
+                                                     align256(20 * (size_t)L->n_max) + align256(XB * (size_t)ctx->wide_block)));
+    const int per_cu = (stage && L->wide_lds * 2 > ctx->wide_lds_limit) || ctx->wide_block > 512 ? 1 : 2;
     L->wide_slots = std::min(sp.wide, ctx->wide_slots > 0 ? ctx->wide_slots : per_cu * ctx->cu_count);
     return BC_OK;
 }

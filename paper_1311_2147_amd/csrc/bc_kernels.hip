@@ -892,6 +892,14 @@ __device__ __forceinline__ void copy_row(T *dst, const T *__restrict__ src, cons
     }
 }
 
+// A value other lanes of the workgroup change by atomics: in global memory
+// those act in L2, so it is read there too.
+template <bool LDS, typename T>
+__device__ __forceinline__ T shared_value(const T *p) {
+    if (LDS) return *p;
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Arc-parallel expansion helpers: the in-arcs of a list of vertices are
 // flattened with a block-wide scan of their in-degrees; each lane takes XU
 // consecutive arcs and issues their loads together.  Two keep the DAG kernel
@@ -1104,8 +1112,7 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
     __syncthreads();
     int32_t nsub;
     bool rec = false;  // Kahn walks recorded arcs
-    const bool sweep = full && !pred;
-    if (sweep) {
+    if (full) {
         // 1. every DAG(s) arc: one more successor of its tail, and (with an
         //    arc record) the arc itself with one more arc into its head
         const int32_t m = cptr[n];
@@ -1140,45 +1147,9 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
                 }
             }
         }
-    } else if (full) {
-        // 1. every reachable vertex's DAG(s) in-arcs: its stored predecessor,
-        //    else (two or more in-arcs) Eq.1 over its E* in-arcs, below
-        for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
-            int32_t pv[LU];
-            bool live[LU];
-#pragma unroll
-            for (int k = 0; k < LU; ++k) {
-                const int32_t x = x0 + k * bs;
-                live[k] = false;
-                pv[k] = PRED_MULTI;
-                if (x < n) {
-                    const int32_t dx = Drow[x];
-                    pv[k] = pred[x];
-                    live[k] = x != s && dx != INF32;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < LU; ++k) {
-                if (!live[k]) continue;
-                const int32_t x = x0 + k * bs, p = pv[k];
-                if (p >= 0) {
-                    atomicAdd(&u.outdeg[p], 1);
-                    if (kcap > 0) {
-                        const int32_t q = atomicAdd(&sh.nk, 1);
-                        if (q < kcap) {
-                            u.ka[q] = p;
-                            u.kb[q] = x;
-                            atomicAdd(&u.kcnt[x], 1);
-                        }
-                    }
-                } else {
-                    u.sub[atomicAdd(&sh.next, 1)] = x;
-                }
-            }
-        }
     }
     __syncthreads();
-    if (!sweep && !full) {
+    if (!full) {
         // 1. backward walk from B.  A lane follows a chain of stored
         //    predecessors itself (a vertex's one DAG in-arc, then its tail's,
         //    and so on) until it reaches a vertex already in the sub-DAG, or
@@ -1271,56 +1242,6 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
                 __syncthreads();
             }
             whi = sh.next;
-        }
-    } else if (!sweep) {
-        // the vertices of a full pass with two or more DAG in-arcs test their
-        // E* in-arcs by Eq.1, arc-parallel
-        const int32_t nslow = sh.next;
-        for (int32_t c = 0; c < nslow; c += bs) {
-            const int32_t idx = c + tid;
-            int32_t x = 0, b0 = 0, deg = 0, dx = 0;
-            if (idx < nslow) {
-                x = u.sub[idx];
-                b0 = cptr[x];
-                deg = cptr[x + 1] - b0;
-                dx = Drow[x];
-            }
-            int32_t total;
-            const int32_t off = block_excl_scan(deg, sh.scan, total);
-            es.off[tid] = off;
-            es.vtx[tid] = x;
-            es.beg[tid] = b0;
-            es.dx[tid] = dx;
-            __syncthreads();
-            const int32_t nv = min(bs, nslow - c);
-            for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
-                int32_t iv[RU], ev[RU], av[RU], wv[RU];
-                bool ok[RU];
-                chunk_arcs(es, nv, total, jb, iv, ev, ok);
-#pragma unroll
-                for (int k = 0; k < RU; ++k) {
-                    av[k] = ok[k] ? csrc[ev[k]] : 0;
-                    wv[k] = ok[k] ? cw[ev[k]] : 0;
-                }
-#pragma unroll
-                for (int k = 0; k < RU; ++k) {
-                    if (!ok[k]) continue;
-                    const int32_t a = av[k];
-                    const int32_t da = Drow[a];
-                    if (da == INF32 || (int64_t)da + wv[k] != (int64_t)es.dx[iv[k]]) continue;
-                    atomicAdd(&u.outdeg[a], 1);
-                    if (kcap > 0) {
-                        const int32_t p = atomicAdd(&sh.nk, 1);
-                        if (p < kcap) {
-                            const int32_t h = es.vtx[iv[k]];
-                            u.ka[p] = a;
-                            u.kb[p] = h;
-                            atomicAdd(&u.kcnt[h], 1);
-                        }
-                    }
-                }
-            }
-            __syncthreads();
         }
     }
     if (full) {
@@ -1531,6 +1452,256 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
         }
     }
     __syncthreads();
+}
+
+// Partial dependency of source s over a target set B that is most of the row,
+// from the stored predecessors (one workgroup): the pass of restricted_pass
+// over all of DAG(s) instead of the ancestors of B.  The vertices with two or
+// more DAG in-arcs test their E* in-arcs by Eq.1 and record them grouped by
+// head; every other vertex has its tail in pred.  Then, with the successor
+// counts in LDS over the staged row (lcnt; the row is not needed any more) and,
+// where it fits, the accumulated dependency too (lacc), the leaves push first
+// (several per lane in flight), and each lane carries on with the vertex that
+// its push completes, along single in-arcs; a vertex with more of them waits
+// for the workgroup's next arc-parallel step.  The share lands before the count
+// drops (release), and the last pusher sees the others' (acquire).
+// A pass is bound by the dependent accesses of one workgroup: rounds over the
+// levels with counts and the record of all arcs in L2, after a sweep over all
+// of E*, took 680 us at n = 32768, this takes 245 (half of it along the single
+// in-arcs, with the dependency in L2); at n = 8192 255 and 56.
+// Returns false, with nothing written but the slot's scratch, when the arcs
+// outgrow the record.
+__device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow, const uint64_t *__restrict__ Srow,
+                          const int32_t *__restrict__ cptr, const int32_t *__restrict__ csrc,
+                          const int32_t *__restrict__ cw, const int32_t *__restrict__ Bt, const int32_t nB,
+                          const USlot &u, const double sign, double *out, const int32_t *__restrict__ pred,
+                          BlockShared &sh, const ExpandShared &es, int32_t *lcnt, double *lacc) {
+    constexpr int RU = 4, LU = 4;
+    const int tid = threadIdx.x, bs = blockDim.x;
+    const int32_t kcap = (int32_t)u.kcap;
+    auto cnt_at = [&](const int32_t x) -> int32_t { return lcnt ? lcnt[x] : shared_value<false>(&u.outdeg[x]); };
+    auto cnt_inc = [&](const int32_t x) {
+        if (lcnt) atomicAdd(&lcnt[x], 1);
+        else atomicAdd(&u.outdeg[x], 1);
+    };
+    auto cnt_dec = [&](const int32_t x) -> int32_t {
+        return lcnt ? __hip_atomic_fetch_sub(&lcnt[x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                    : __hip_atomic_fetch_sub(&u.outdeg[x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto acc_at = [&](const int32_t x) -> double { return lacc ? lacc[x] : shared_value<false>(&u.acc[x]); };
+    auto acc_add = [&](const int32_t x, const double v) {
+        if (lacc) atomicAdd(&lacc[x], v);
+        else atomicAdd(&u.acc[x], v);
+    };
+    if (tid == 0) {
+        sh.next = 0;
+        sh.nk = 0;
+        sh.kpos = 0;
+        sh.tail = 0;
+        sh.head = 0;
+    }
+    __syncthreads();
+    // the vertices with two or more DAG in-arcs, and those arcs
+    for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
+        int32_t pv[LU];
+#pragma unroll
+        for (int k = 0; k < LU; ++k) pv[k] = x0 + k * bs < n ? pred[x0 + k * bs] : PRED_NONE;
+#pragma unroll
+        for (int k = 0; k < LU; ++k)
+            if (pv[k] == PRED_MULTI) u.sub[atomicAdd(&sh.next, 1)] = x0 + k * bs;
+    }
+    __syncthreads();
+    const int32_t nmulti = sh.next;
+    for (int32_t c = 0; c < nmulti; c += bs) {
+        const int32_t idx = c + tid;
+        int32_t x = 0, b0 = 0, deg = 0, dx = 0;
+        if (idx < nmulti) {
+            x = u.sub[idx];
+            b0 = cptr[x];
+            deg = cptr[x + 1] - b0;
+            dx = Drow[x];
+        }
+        int32_t total;
+        const int32_t off = block_excl_scan(deg, sh.scan, total);
+        es.off[tid] = off;
+        es.vtx[tid] = x;
+        es.beg[tid] = b0;
+        es.dx[tid] = dx;
+        __syncthreads();
+        const int32_t nv = min(bs, nmulti - c);
+        for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
+            int32_t iv[RU], ev[RU], av[RU], wv[RU];
+            bool ok[RU];
+            chunk_arcs(es, nv, total, jb, iv, ev, ok);
+#pragma unroll
+            for (int k = 0; k < RU; ++k) {
+                av[k] = ok[k] ? csrc[ev[k]] : 0;
+                wv[k] = ok[k] ? cw[ev[k]] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < RU; ++k) {
+                if (!ok[k]) continue;
+                const int32_t da = Drow[av[k]];
+                if (da == INF32 || (int64_t)da + wv[k] != (int64_t)es.dx[iv[k]]) continue;
+                const int32_t p = atomicAdd(&sh.nk, 1);
+                if (p < kcap) {
+                    const int32_t h = es.vtx[iv[k]];
+                    u.ka[p] = av[k];
+                    u.kb[p] = h;
+                    atomicAdd(&u.kcnt[h], 1);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const int32_t nk = sh.nk;
+    if (nk > kcap) {
+        for (int32_t i = tid; i < nmulti; i += bs) u.kcnt[u.sub[i]] = 0;
+        __syncthreads();
+        return false;
+    }
+    for (int32_t i = tid; i < nmulti; i += bs) {
+        const int32_t x = u.sub[i];
+        u.kend[x] = atomicAdd(&sh.kpos, shared_value<false>(&u.kcnt[x]));
+    }
+    // (the staged row ends here)
+    if (lcnt)
+        for (int32_t x = tid; x < n; x += bs) lcnt[x] = 0;
+    if (lacc)
+        for (int32_t x = tid; x < n; x += bs) lacc[x] = 0.0;
+    __syncthreads();
+    for (int32_t i = tid; i < nB; i += bs) {
+        const int32_t t = Bt[i];
+        if (t == s) continue;
+        if (lcnt) lcnt[t] = W_B;
+        else u.outdeg[t] = W_B;
+    }
+    for (int32_t p = tid; p < nk; p += bs) u.kr[atomicAdd(&u.kend[u.kb[p]], 1)] = u.ka[p];
+    __syncthreads();
+    // successor counts
+    for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
+        int32_t pv[LU];
+#pragma unroll
+        for (int k = 0; k < LU; ++k) pv[k] = x0 + k * bs < n ? pred[x0 + k * bs] : PRED_NONE;
+#pragma unroll
+        for (int k = 0; k < LU; ++k)
+            if (pv[k] >= 0) cnt_inc(pv[k]);
+    }
+    for (int32_t p = tid; p < nk; p += bs) cnt_inc(u.ka[p]);
+    __syncthreads();
+    // the leaves (marked before any count drops; q1: vertices completed, q2:
+    // those with two or more in-arcs)
+    for (int32_t x = tid; x < n; x += bs) {
+        const int32_t c = cnt_at(x);
+        if (c & W_COUNT) continue;
+        if (lcnt) lcnt[x] = c | W_VIS;
+        else u.outdeg[x] = c | W_VIS;
+    }
+    __syncthreads();
+    for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
+        int32_t pv[LU];
+#pragma unroll
+        for (int k = 0; k < LU; ++k) pv[k] = x0 + k * bs < n ? pred[x0 + k * bs] : PRED_NONE;
+#pragma unroll
+        for (int k = 0; k < LU; ++k) {
+            if (pv[k] == PRED_NONE) continue;
+            const int32_t x = x0 + k * bs, c = cnt_at(x);
+            if (!(c & W_VIS)) pv[k] = PRED_NONE;
+            else if (pv[k] < 0) u.q2[atomicAdd(&sh.head, 1)] = x;
+            else if (c & W_B) acc_add(pv[k], 1.0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        int32_t was[LU];
+#pragma unroll
+        for (int k = 0; k < LU; ++k) was[k] = pv[k] >= 0 ? cnt_dec(pv[k]) : 0;
+#pragma unroll
+        for (int k = 0; k < LU; ++k)
+            if ((was[k] & W_COUNT) == 1) u.q1[atomicAdd(&sh.tail, 1)] = pv[k];
+    }
+    __syncthreads();
+    int32_t lo = 0, hi = sh.tail;
+    for (;;) {
+        // along single in-arcs
+        for (int32_t idx = lo + tid; idx < hi; idx += bs) {
+            int32_t x = u.q1[idx], p = pred[x];
+            for (;;) {
+                if (p < 0) {
+                    if (p == PRED_MULTI) u.q2[atomicAdd(&sh.head, 1)] = x;
+                    break;
+                }
+                const int32_t pp = pred[p];
+                const double push = ((cnt_at(x) & W_B) ? 1.0 : 0.0) + acc_at(x);
+                if (push != 0.0) acc_add(p, push);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if ((cnt_dec(p) & W_COUNT) != 1) break;
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                x = p;
+                p = pp;
+            }
+        }
+        __syncthreads();
+        const int32_t nslow = sh.head;
+        lo = hi;
+        __syncthreads();
+        if (nslow == 0) break;
+        if (tid == 0) sh.head = 0;
+        for (int32_t c = 0; c < nslow; c += bs) {
+            const int32_t idx = c + tid;
+            int32_t b0 = 0, deg = 0;
+            double coef = 0.0;
+            if (idx < nslow) {
+                const int32_t x = u.q2[idx];
+                // each predecessor a receives sigma_sa * coef
+                coef = (((cnt_at(x) & W_B) ? 1.0 : 0.0) + acc_at(x)) / (double)Srow[x];
+                deg = shared_value<false>(&u.kcnt[x]);
+                b0 = shared_value<false>(&u.kend[x]) - deg;
+            }
+            int32_t total;
+            const int32_t off = block_excl_scan(deg, sh.scan, total);
+            es.off[tid] = off;
+            es.beg[tid] = b0;
+            es.val[tid] = coef;
+            __syncthreads();
+            const int32_t nv = min(bs, nslow - c);
+            for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
+                int32_t iv[RU], ev[RU], av[RU];
+                bool ok[RU];
+                chunk_arcs(es, nv, total, jb, iv, ev, ok);
+#pragma unroll
+                for (int k = 0; k < RU; ++k) av[k] = ok[k] ? u.kr[ev[k]] : 0;
+#pragma unroll
+                for (int k = 0; k < RU; ++k) {
+                    if (!ok[k]) continue;
+                    const double cf = es.val[iv[k]];
+                    if (cf != 0.0) acc_add(av[k], (double)Srow[av[k]] * cf);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+#pragma unroll
+                for (int k = 0; k < RU; ++k)
+                    if (ok[k] && (cnt_dec(av[k]) & W_COUNT) == 1) u.q1[atomicAdd(&sh.tail, 1)] = av[k];
+            }
+            __syncthreads();
+        }
+        hi = sh.tail;
+    }
+    for (int32_t x0 = tid; x0 < n; x0 += LU * bs) {
+        double av[LU];
+#pragma unroll
+        for (int k = 0; k < LU; ++k) av[k] = x0 + k * bs < n ? acc_at(x0 + k * bs) : 0.0;
+#pragma unroll
+        for (int k = 0; k < LU; ++k) {
+            const int32_t x = x0 + k * bs;
+            if (x >= n) continue;
+            if (av[k] != 0.0) {
+                if (x != s) atomicAdd(&out[x], sign * av[k]);
+                if (!lacc) u.acc[x] = 0.0;
+            }
+            if (!lcnt) u.outdeg[x] = 0;
+        }
+    }
+    for (int32_t i = tid; i < nmulti; i += bs) u.kcnt[u.sub[i]] = 0;
+    __syncthreads();
+    return true;
 }
 
 // Small sub-DAGs in LDS.  Most sources' sub-DAGs hold a few dozen vertices,
@@ -2787,7 +2958,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))
 __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restrict__ jobs,
                                                       const int32_t *__restrict__ njobs_p, char *__restrict__ scratch,
                                                       size_t slot_bytes, int32_t lds_cap, int32_t n_layout,
-                                                      char *__restrict__ items, int32_t item_regions, StepPool pool) {
+                                                      char *__restrict__ items, int32_t item_regions, StepPool pool,
+                                                      size_t lds_bytes) {
     extern __shared__ __align__(16) char dyn_lds[];
     int32_t *const lds_row = (int32_t *)dyn_lds;
     const ExpandShared es = expand_at(dyn_lds, lds_cap);
@@ -2836,22 +3008,24 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         const int32_t nb = sh.nb;
         if (role == 0) {
             const ItemRegion ir = item_region_at(items + (size_t)region * region_bytes, n_layout);
-            for (int32_t i = tid; i < nb; i += bs) {
-                ir.t[i] = u.bl_t[i];
-                ir.d[i] = u.bl_d[i];
-                ir.s[i] = u.bl_s[i];
-            }
+            copy_row<4>(ir.t, u.bl_t, nb);
+            copy_row<4>(ir.d, u.bl_d, nb);
+            copy_row<4>(ir.s, u.bl_s, nb);
             if (tid == 0) *ir.nb = nb;
         }
         if (nb == 0) continue;
         if (role != 1 && tid == 0) atomicAdd(&ctl->changed_pairs, (unsigned long long)nb);
-        // a B of half the row or more makes the sub-DAG most of DAG(s):
-        // take every vertex's DAG in-arcs instead of walking back from B.
-        // Below that the walk is cheaper: a hub update's changed targets
-        // hang mostly below the hub, so their new ancestors are little
-        // more than B itself (a hub update with 19 000 deferred sources
-        // took 80 ms this way, 127 ms with whole-DAG passes from 1/16)
-        const bool full = (int64_t)nb * 2 >= (int64_t)n;
+        // a pass over all of DAG(s) instead of walking back from B where B is
+        // an eighth of the row or more: at n = 32768 it takes 245 us whatever
+        // B is, a walk 190 from 3000 changed targets and 500 from 10 000; at
+        // n = 8192 (with the dependency in LDS too) 56 against 72 from 1400
+        const bool full = (int64_t)nb * 8 >= (int64_t)n;
+        // where the passes use the staged row's LDS: full ones for the counts
+        // and (past the expansion arrays) the dependency, walks for their
+        // accumulation
+        int32_t *const lcnt = lds ? lds_row : nullptr;
+        const size_t acc_off = align256((size_t)lds_cap * 4) + align256(XB * (size_t)bs);
+        double *const lacc = acc_off + 8 * (size_t)n <= lds_bytes ? (double *)(dyn_lds + acc_off) : nullptr;
         // phase 0: old pass (roles 0 and 2); phase 1: new pass (roles 1 and 2)
         for (int ph = role == 1 ? 1 : 0; ph <= (role == 0 ? 0 : 1); ++ph) {
             const int32_t *Dr = lds ? lds_row : Dg;
@@ -2867,12 +3041,21 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
                         for (int32_t t = tid; t < n; t += bs) u.dnew[t] = Dg[t];
                     copy_row<4>(u.snew, Sg, n);
                     __syncthreads();
-                    for (int32_t i = tid; i < nb; i += bs) {
-                        const int32_t t = u.bl_t[i];
-                        const int32_t d = u.bl_d[i];
-                        u.snew[t] = u.bl_s[i];
-                        u.bl_d[i] = new_pred(J, s, t, pred_row[t], d < Dn[t]);
-                        Dn[t] = d;
+                    for (int32_t i0 = tid; i0 < nb; i0 += 4 * bs) {
+                        int32_t tv[4], pv[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) tv[k] = i0 + k * bs < nb ? u.bl_t[i0 + k * bs] : -1;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) pv[k] = tv[k] >= 0 ? pred_row[tv[k]] : 0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int32_t i = i0 + k * bs, t = tv[k];
+                            if (t < 0) continue;
+                            const int32_t d = u.bl_d[i];
+                            u.snew[t] = u.bl_s[i];
+                            u.bl_d[i] = new_pred(J, s, t, pv[k], d < Dn[t]);
+                            Dn[t] = d;
+                        }
                     }
                     __syncthreads();
                     int32_t *const Pn = (int32_t *)u.bl_s;
@@ -2885,6 +3068,10 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
                 } else {
                     int32_t *Dw = J.g.D + (size_t)s * n;
                     uint64_t *Sw = J.g.S + (size_t)s * n;
+                    if (lds) {  // (the old pass used it)
+                        copy_row<4>(lds_row, Dg, n);
+                        __syncthreads();
+                    }
                     for (int32_t i = tid; i < nb; i += bs) {
                         const int32_t t = u.bl_t[i];
                         const int32_t d = u.bl_d[i];
@@ -2896,9 +3083,12 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
                 }
                 __syncthreads();
             }
-            restricted_pass<false, 2, 4>(s, n, Dr, Sr, ph ? J.g.yc_ptr : J.g.xc_ptr, ph ? J.g.yc_src : J.g.xc_src,
-                                         ph ? J.g.yc_dst : J.g.xc_dst, ph ? J.g.yc_w : J.g.xc_w, u.bl_t, nb, full, u,
-                                         ph ? 1.0 : -1.0, J.g.bc_delta, Pr, sh, es);
+            const int32_t *const cp = ph ? J.g.yc_ptr : J.g.xc_ptr, *const ca = ph ? J.g.yc_src : J.g.xc_src,
+                          *const cb = ph ? J.g.yc_dst : J.g.xc_dst, *const cw = ph ? J.g.yc_w : J.g.xc_w;
+            const double sign = ph ? 1.0 : -1.0;
+            if (!full || !full_pass(s, n, Dr, Sr, cp, ca, cw, u.bl_t, nb, u, sign, J.g.bc_delta, Pr, sh, es, lcnt, lacc))
+                restricted_pass<false, 2, 4>(s, n, Dr, Sr, cp, ca, cb, cw, u.bl_t, nb, full, u, sign, J.g.bc_delta, Pr,
+                                             sh, es, dyn_lds, lds_bytes);
         }
     }
 }
@@ -3371,14 +3561,6 @@ __device__ __forceinline__ SSlot sslot_at(char *base, int32_t n_layout) {
     s.hist = (int32_t *)(base + L.q2);
     s.list = (void *)(base + L.kend);  // kend, ka, kb, kr
     return s;
-}
-
-// A value other lanes of the workgroup change by atomics: in global memory
-// those act in L2, so it is read there too.
-template <bool LDS, typename T>
-__device__ __forceinline__ T shared_value(const T *p) {
-    if (LDS) return *p;
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // All of E* in place of the list, for a source with more DAG arcs than the

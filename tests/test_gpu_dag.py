@@ -5,8 +5,7 @@ front of a hub changes the hub and its leaves for every source on the chain.
 Leaf counts go over the union walk's bound (3/8 of the table's slots), the
 table's vertex capacity, and with the chain over what the accumulation in LDS
 holds (about 650 vertices with the 128-slot table, 1300 with the 256-slot one);
-two hubs give every leaf two DAG in-arcs.  Arc updates take Alg 2, vertex
-updates test E* in-arcs.
+two hubs give every leaf two DAG in-arcs.
 """
 from __future__ import annotations
 
