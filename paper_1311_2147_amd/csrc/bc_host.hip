@@ -241,7 +241,6 @@ struct bc_ctx {
     bool use_tuned = false;
     std::string tune_cache;
     std::string device_tag;
-    int32_t src_lds_max = 8192;  // per-source kernel stages rows up to this n in LDS
     std::vector<GraphRec *> graphs;
     std::string last_error;
     // staging
@@ -518,8 +517,6 @@ struct LaunchShape {
     int njobs;
     int slots;
     size_t slot_bytes;
-    int lds_cap;      // static pass: rows up to this size are staged in LDS
-    int src_lds_cap;  // per-source kernel: rows up to this size are staged in LDS
     int wide_slots;   // workgroups of the wide per-source kernel
     size_t wide_bytes;
     char *src_base, *wide_base, *items_base;
@@ -565,13 +562,13 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part,
                                L.wide_lds, st, jobs, nj, L.wide_base, L.wide_bytes, L.wide_lds_cap, L.n_layout,
                                L.items_base, L.item_regions, pool, L.wide_lds);
         }
-        const size_t lds = source_lds_bytes(L.src_lds_cap, ctx->block, ctx->table);
+        const size_t lds = source_lds_bytes(0, ctx->block, ctx->table);
         if (ctx->table == 128)
             hipLaunchKernelGGL(k_source<128>, dim3(L.slots), dim3(ctx->block), lds, dag, jobs, nj, L.src_base,
-                               L.slot_bytes, L.src_lds_cap, L.n_layout, pool);
+                               L.slot_bytes, L.n_layout, pool);
         else
             hipLaunchKernelGGL(k_source<256>, dim3(L.slots), dim3(ctx->block), lds, dag, jobs, nj, L.src_base,
-                               L.slot_bytes, L.src_lds_cap, L.n_layout, pool);
+                               L.slot_bytes, L.n_layout, pool);
         if (L.may_defer) {
             HIPCHK(hipEventRecord(ctx->join_ev, ctx->side));
             hipLaunchKernelGGL(k_wide_apply, dim3(256), dim3(256), 0, st, jobs, nj, L.items_base, L.item_regions,
@@ -600,7 +597,6 @@ bc_status part_graph(bc_ctx *ctx, int r, const LaunchShape &L, int part, hipGrap
                                       L.n_layout,
                                       L.slots,
                                       (int64_t)L.slot_bytes,
-                                      L.src_lds_cap,
                                       L.wide_slots,
                                       (int64_t)L.wide_bytes,
                                       L.wide_lds_cap,
@@ -657,9 +653,6 @@ bc_status shape_for(bc_ctx *ctx, const std::vector<UpdateJob> &jobs, LaunchShape
     L->items_base = sp.items_base;
     L->item_regions = sp.wide;
     if (ctx->run_slots > 0) L->slots = std::min(L->slots, ctx->run_slots);
-    L->lds_cap = lds_cap_for(L->n_max);
-    // the row is staged only when it fits; otherwise no LDS is reserved for it
-    L->src_lds_cap = L->n_max <= ctx->src_lds_max ? L->n_max : 0;
     // wide kernel: the row is staged when it fits beside the expansion arrays
     // and the small-DAG table; one workgroup per CU then, else two
     const size_t wide_lds = source_lds_bytes(L->n_max, ctx->wide_block, 0);

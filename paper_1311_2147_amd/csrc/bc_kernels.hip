@@ -2773,14 +2773,12 @@ __host__ __device__ constexpr size_t dag_table_bytes() {
 template <int TS>
 __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t s, const int32_t *__restrict__ Bt,
                                               const int32_t *__restrict__ Bd, const uint64_t *__restrict__ Bs,
-                                              const int32_t nb, const bool lds, int32_t *lds_row, const USlot &u,
-                                              BlockShared &sh, const ExpandShared &es, const SmallDag &sd,
+                                              const int32_t nb, const USlot &u, BlockShared &sh, const ExpandShared &es, const SmallDag &sd,
                                               const DualDag &dd, char *table) {
     const int tid = threadIdx.x, bs = blockDim.x;
     const int32_t n = J.g.n;
     int32_t *const Dg = J.g.D + (size_t)s * n;
     uint64_t *const Sg = J.g.S + (size_t)s * n;
-    const int32_t *Drow = lds ? lds_row : Dg;
     double *const bc_delta = J.g.bc_delta;
     // an LDS table holds at most 3/4 of its slots in vertices: larger B sets
     // go straight to the slot passes.  The union of both sub-DAGs with a B of
@@ -2790,29 +2788,28 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     const bool fits = nb < TS * 3 / 4;
     const bool dual_fits = nb < TS * 3 / 8;
     int32_t *const pred_row = J.g.pred + (size_t)s * n;
-    const bool dual = dual_fits && dual_pass<TS>(J, s, Drow, Sg, J.g.xc_ptr, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, Bd,
+    const bool dual = dual_fits && dual_pass<TS>(J, s, Dg, Sg, J.g.xc_ptr, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, Bd,
                                                  Bs, pred_row, nb, bc_delta, sh, es, dd);
     // when the union outgrew the table it is mostly the old sub-DAG that did:
     // the old pass goes straight to the slot (it follows stored
     // predecessors), the new one tries the LDS table first
     if (!dual)
-        restricted_pass<false, XU>(s, n, Drow, Sg, J.g.xc_ptr, J.g.xc_src, J.g.xc_dst, J.g.xc_w, Bt, nb, false, u,
+        restricted_pass<false, XU>(s, n, Dg, Sg, J.g.xc_ptr, J.g.xc_src, J.g.xc_dst, J.g.xc_w, Bt, nb, false, u,
                                    -1.0, bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
     // the changed targets' new predecessors by Alg 2 (before the old distances
     // are overwritten); the new pass follows them like any stored predecessor
     for (int32_t i = tid; i < nb; i += bs) {
         const int32_t t = Bt[i];
         const int32_t d = Bd[i];
-        pred_row[t] = new_pred(J, s, t, pred_row[t], d < Drow[t]);
+        pred_row[t] = new_pred(J, s, t, pred_row[t], d < Dg[t]);
         Sg[t] = Bs[i];
         Dg[t] = d;
-        if (lds) lds_row[t] = d;
     }
     __syncthreads();
     if (dual) return;
-    if (!fits || !small_pass<TS>(s, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row, sh,
+    if (!fits || !small_pass<TS>(s, Dg, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row, sh,
                                  es, sd))
-        restricted_pass<false, XU>(s, n, Drow, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_dst, J.g.yc_w, Bt, nb, false, u, 1.0,
+        restricted_pass<false, XU>(s, n, Dg, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_dst, J.g.yc_w, Bt, nb, false, u, 1.0,
                                    bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
 }
 
@@ -2901,24 +2898,25 @@ struct WorkList {
 };
 
 // DAG kernel (persistent): workgroups take the sources the row kernel listed
-// (WorkList) and run update_source on each.  The row is staged in LDS when n <= lds_cap
-// (dynamic LDS of 4*lds_cap bytes).  Every workgroup's slot is laid out for
-// the context-wide n_layout (the largest graph), so the zero-kept arrays sit
+// (WorkList) and run update_source on each.  Every workgroup's slot is laid out
+// for the context-wide n_layout (the largest graph), so the zero-kept arrays sit
 // at the same place for every job.  The work is bound by dependent gathers, so
-// the register budget is held to five waves per SIMD (ten 128-thread
-// workgroups per CU), 96 registers with no spills.
+// what counts is the sources in flight: the register budget is held to five
+// waves per SIMD (ten 128-thread workgroups per CU), 96 registers with no
+// spills, and the source's row is read from memory.  Staged in LDS (up to
+// n = 8192) it left room for two or three workgroups per CU: 16 unit-weight
+// insertions at n = 8191 took 16.4 ms with it and take 13.9, 64 arc updates at
+// n = 4096 9.6 and 9.0; at n = 2048 and below both are the same.
 template <int TS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) k_source(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
-                                                char *__restrict__ scratch, size_t slot_bytes, int32_t lds_cap,
-                                                int32_t n_layout, StepPool pool) {
+                                                char *__restrict__ scratch, size_t slot_bytes, int32_t n_layout,
+                                                StepPool pool) {
     extern __shared__ __align__(16) char dyn_lds[];
-    int32_t *const lds_row = (int32_t *)dyn_lds;
-    const ExpandShared es = expand_at(dyn_lds, lds_cap);
-    char *const table = dyn_lds + align256((size_t)lds_cap * 4) + align256(XB * (size_t)blockDim.x);
+    const ExpandShared es = expand_at(dyn_lds, 0);
+    char *const table = dyn_lds + align256(XB * (size_t)blockDim.x);
     const SmallDag sd = small_dag_at<TS>(table);
     const DualDag dd = dual_dag_at<TS>(table);
     __shared__ BlockShared sh;
-    const int tid = threadIdx.x, bs = blockDim.x;
     const int njobs = *njobs_p;
     const USlot u = uslot_at(scratch + (size_t)blockIdx.x * slot_bytes, n_layout);
     // the heavy sources of every job first (the front of each job's list),
@@ -2933,16 +2931,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))
     while (wl.next()) {
         const int32_t seg = sh.seg, item = sh.item;
         const UpdateJob &J = jobs[seg < njobs ? seg : seg - njobs];
-        const int32_t n = J.g.n;
-        const bool lds = n <= lds_cap;
-        const DItem it = J.g.dlist[seg < njobs ? item : n - 1 - item];
-        if (lds) {
-            const int32_t *Dg = J.g.D + (size_t)it.s * n;
-            for (int32_t t = tid; t < n; t += bs) lds_row[t] = Dg[t];
-            __syncthreads();
-        }
-        update_source<TS>(J, it.s, pool.t + it.off, pool.d + it.off, pool.s + it.off, it.nb, lds, lds_row, u, sh, es,
-                          sd, dd, table);
+        const DItem it = J.g.dlist[seg < njobs ? item : J.g.n - 1 - item];
+        update_source<TS>(J, it.s, pool.t + it.off, pool.d + it.off, pool.s + it.off, it.nb, u, sh, es, sd, dd, table);
     }
 }
 
