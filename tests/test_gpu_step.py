@@ -10,7 +10,7 @@ from __future__ import annotations
 
 import pytest
 
-from gpu_util import check_full, make_ctx, say
+from gpu_util import check_full, check_sampled, make_ctx, say
 from paper_1311_2147_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -74,3 +74,18 @@ def test_nothing_to_merge_into():
     g = W.Graph(300, True, *(W.np.zeros(0, t) for t in (W.np.int32, W.np.int32, W.np.int64)))
     _run(g, [W.Update("edge", u=5, v=299, w=1), W.Update("edge", u=299, v=0, w=1), W.Update("edge", u=0, v=5, w=4)],
          "empty graph")
+
+
+@pytest.mark.parametrize("n", [4095, 4097, 8191, 8193])
+def test_whole_rows_that_are_no_quads(n):
+    """Sizes around one and two trips of a workgroup over a row read pair by pair."""
+    g = W.cycle_graph(n, directed=True)
+    ups = [W.Update("edge", u=0, v=n // 3, w=1), W.Update("vertex", v=n // 2, edges=[(5, n // 2, 1), (n // 2, 9, 2)])]
+    say(f"step: rows of {n}")
+    ctx = make_ctx(n, slots=64)
+    gr = ctx.load_graph(g)
+    for up in ups:
+        gr.update(up)
+        g = W.apply_update(g, up)
+    check_sampled(gr, g, [0, 1, 5, 9, n // 3 - 1, n // 3, n // 2, n - 1], f"rows of {n}")
+    ctx.close()
