@@ -2259,13 +2259,13 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
         const int32_t sl = d.front[idx >> 1];
         const int32_t pr = (d.flags[sl] & DF_O) ? d.pr[sl] : PRED_NONE, pn = d.ydeg[sl] < 0 ? d.ybeg[sl] : PRED_MULTI;
         const bool one = pr >= 0 && pr == pn;
-        if (idx & 1) {
-            const int32_t slow = (pr == PRED_MULTI ? DF_O : 0) | (pn < 0 ? DF_N : 0);
-            if (slow) dd_push_slow<TS>(d, sh, sl, slow);
-            if (pn >= 0 && !one) dd_follow<TS>(d, sh, s, pred, sl, pn, DF_N, d.snew[sl]);
-        } else if (pr >= 0) {
-            dd_follow<TS>(d, sh, s, pred, sl, pr, one ? DF_O | DF_N : DF_O, d.sold[sl]);
-        }
+        // (one walk for both kinds of lane: two would run one after the other)
+        const bool odd = (idx & 1) != 0;
+        const int32_t slow = (pr == PRED_MULTI ? DF_O : 0) | (pn < 0 ? DF_N : 0);
+        if (odd && slow) dd_push_slow<TS>(d, sh, sl, slow);
+        const int32_t p = odd ? (one ? PRED_NONE : pn) : pr;
+        if (p >= 0)
+            dd_follow<TS>(d, sh, s, pred, sl, p, odd ? DF_N : one ? DF_O | DF_N : DF_O, odd ? d.snew[sl] : d.sold[sl]);
     }
     __syncthreads();
     // the vertices whose E* in-arcs are tested: arc-parallel, and back from
@@ -2811,6 +2811,7 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     if (!dual)
         restricted_pass<false, XU>(s, n, Dg, Sg, J.g.xc_ptr, J.g.xc_src, J.g.xc_dst, J.g.xc_w, Bt, nb, false, u,
                                    -1.0, bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
+    const int32_t old_sub = sh.next;  // (of the old pass; read before the barrier below)
     // the changed targets' new predecessors by Alg 2 (before the old distances
     // are overwritten); the new pass follows them like any stored predecessor
     for (int32_t i = tid; i < nb; i += bs) {
@@ -2822,8 +2823,11 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     }
     __syncthreads();
     if (dual) return;
-    if (!fits || !small_pass<TS>(s, Dg, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row, sh,
-                                 es, sd))
+    // a sub-DAG of twice the table's capacity before the update rarely fits now
+    // (with unit weights at n = 8191 the attempt cost 47 of a source's 264 us)
+    const bool small = fits && old_sub <= TS * 3 / 2;
+    if (!small || !small_pass<TS>(s, Dg, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, nb, 1.0, bc_delta, pred_row, sh, es,
+                                  sd))
         restricted_pass<false, XU>(s, n, Dg, Sg, J.g.yc_ptr, J.g.yc_src, J.g.yc_dst, J.g.yc_w, Bt, nb, false, u, 1.0,
                                    bc_delta, pred_row, sh, es, table, dag_table_bytes<TS>());
 }
