@@ -1983,13 +1983,38 @@ bc_status bc_clone_graph(bc_ctx *ctx, bc_graph_id gid, void *arena, uint64_t are
     HIPCHK(hipSetDevice(ctx->device));
     // stream-ordered: the copy sees every update enqueued on the source so far,
     // which the host mirror already holds
-    HIPCHK(hipMemcpyAsync(arena, src->arena, need, hipMemcpyDeviceToDevice, ctx->stream));
+    size_t total = 0;
+    CheckRec *chk = nullptr;
+    GraphPtrs P = carve((char *)arena, src->n, src->arc_cap, src->es_cap, &total, &chk);
+    P.directed = src->directed;
+    // what outlives a call: the state (D to bc_delta), E* by head, the affected
+    // list of the last update, the control and check records.  The rest of the
+    // arena is written before it is read (the arcs by tail and head too, by every
+    // static pass and state check)
+    CopyRanges c{};
+    auto range = [&](const void *from, const void *to) {
+        const size_t at = (size_t)((const char *)from - (char *)arena);
+        c.off[c.count] = at;
+        c.bytes[c.count++] = (size_t)((const char *)to - (char *)arena) - at;
+    };
+    range(P.D, P.rvv_pred);
+    range(P.xc_ptr, P.yc_ptr);
+    range(P.alist, P.biglist);
+    range(P.ctl, P.arc_ptr);
+    range(chk, (char *)arena + total);
+    // past the caches only what they could not keep for the clone's first update
+    // (256 MB of last-level cache, both copies in it)
+    size_t moved = 0;
+    for (int i = 0; i < c.count; ++i) moved += c.bytes[i];
+    const bool stream = 2 * moved > ((size_t)256 << 20);
+    hipLaunchKernelGGL(stream ? k_copy_ranges<true> : k_copy_ranges<false>, dim3(8 * ctx->cu_count), dim3(256), 0,
+                       ctx->stream, (char *)arena, src->arena, c);
+    HIPCHK(hipGetLastError());
     GraphRec *g = new GraphRec(*src);
     g->arena = (char *)arena;
     g->arena_bytes = arena_bytes;
-    size_t total = 0;
-    g->P = carve((char *)arena, g->n, g->arc_cap, g->es_cap, &total, &g->chk);
-    g->P.directed = g->directed;
+    g->P = P;
+    g->chk = chk;
     ctx->graphs.push_back(g);
     ctx->in_use += arena_bytes;
     *out = (bc_graph_id)(ctx->graphs.size() - 1);
