@@ -3673,42 +3673,54 @@ __device__ void static_source(const GraphPtrs &G, const int32_t s, const int32_t
     if (tid == 0) sh.nk = 0;
     if (ROW) copy_row<U>(row, Dg, n);
     __syncthreads();
-    // 1. the DAG arcs, four consecutive E* arcs per lane
+    // 1. the DAG arcs, four consecutive E* arcs per load, two loads of each kind per
+    // lane in flight (one: 20.03 ms for a recompute at n = 16384, two 19.75, three
+    // spill and take 20.03)
     auto tight = [&](const int32_t a, const int32_t b, const int32_t w) {
         const int32_t da = ROW ? row[a] : Dg[a], db = ROW ? row[b] : Dg[b];
         return da != INF32 && (int64_t)da + w == (int64_t)db;
     };
     const int4 *const src4 = (const int4 *)G.xc_src, *const dst4 = (const int4 *)G.xc_dst, *const w4 = (const int4 *)G.xc_w;
     const int32_t m4 = (m + 3) >> 2;
-    for (int32_t i0 = tid - lane; i0 < m4; i0 += bs) {
-        const int32_t i = i0 + lane;
-        int av[4] = {0, 0, 0, 0}, bv[4] = {0, 0, 0, 0}, wv[4] = {0, 0, 0, 0};
-        if (4 * i + 3 < m) {
-            const int4 a = src4[i], b = dst4[i], w = w4[i];
-            av[0] = a.x, av[1] = a.y, av[2] = a.z, av[3] = a.w;
-            bv[0] = b.x, bv[1] = b.y, bv[2] = b.z, bv[3] = b.w;
-            wv[0] = w.x, wv[1] = w.y, wv[2] = w.z, wv[3] = w.w;
-        } else if (i < m4) {
+    constexpr int Q = 2;
+    for (int32_t i0 = tid - lane; i0 < m4; i0 += Q * bs) {
+        int av[4 * Q] = {}, bv[4 * Q] = {}, wv[4 * Q] = {};
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (4 * i + k < m) av[k] = G.xc_src[4 * i + k], bv[k] = G.xc_dst[4 * i + k], wv[k] = G.xc_w[4 * i + k];
+        for (int q = 0; q < Q; ++q) {
+            const int32_t i = i0 + q * bs + lane;
+            if (4 * i + 3 < m) {
+                const int4 a = src4[i], b = dst4[i], w = w4[i];
+                av[4 * q] = a.x, av[4 * q + 1] = a.y, av[4 * q + 2] = a.z, av[4 * q + 3] = a.w;
+                bv[4 * q] = b.x, bv[4 * q + 1] = b.y, bv[4 * q + 2] = b.z, bv[4 * q + 3] = b.w;
+                wv[4 * q] = w.x, wv[4 * q + 1] = w.y, wv[4 * q + 2] = w.z, wv[4 * q + 3] = w.w;
+            } else if (i < m4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (4 * i + k < m) {
+                        av[4 * q + k] = G.xc_src[4 * i + k];
+                        bv[4 * q + k] = G.xc_dst[4 * i + k];
+                        wv[4 * q + k] = G.xc_w[4 * i + k];
+                    }
+            }
         }
         // (an entry past the end is the arc (0,0) of weight 0: not counted)
-        uint64_t mask[4];
-        int32_t before[4], cnt = 0;
+        uint32_t mine = 0;
+        int32_t before[4 * Q], cnt = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            mask[k] = __ballot(wv[k] != 0 && tight(av[k], bv[k], wv[k]));
-            before[k] = cnt + (int32_t)popc_below(mask[k], lane);
-            cnt += (int32_t)__popcll(mask[k]);
+        for (int k = 0; k < 4 * Q; ++k) {
+            const bool t = wv[k] != 0 && tight(av[k], bv[k], wv[k]);
+            const uint64_t mask = __ballot(t);
+            mine |= (t ? 1u : 0u) << k;
+            before[k] = cnt + (int32_t)popc_below(mask, lane);
+            cnt += (int32_t)__popcll(mask);
         }
         if (cnt == 0) continue;
         int32_t base = 0;
         if (lane == 0) base = atomicAdd(&sh.nk, cnt);
         base = __shfl(base, 0, 64);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if ((mask[k] >> lane) & 1) {
+        for (int k = 0; k < 4 * Q; ++k)
+            if ((mine >> k) & 1) {
                 const int32_t p = base + before[k];
                 if (p < cap) put(p, A::make((uint32_t)av[k], (uint32_t)bv[k]));
             }
