@@ -1974,7 +1974,8 @@ __device__ __forceinline__ int32_t new_pred(const UpdateJob &J, const int32_t s,
     constexpr int DD_SLOTS = TS;           \
     constexpr int DD_CAP = TS * 3 / 4;     \
     constexpr int DD_ARCS = 2 * TS;        \
-    constexpr int DD_FRONT = 2 * DD_CAP;
+    constexpr int DD_ROOTS = TS * 3 / 8;   \
+    constexpr int DD_SLOW = 2 * DD_CAP;
 enum : int32_t { DF_O = 1, DF_N = 2, DF_B = 4 };
 
 struct DualDag {
@@ -1991,7 +1992,7 @@ struct DualDag {
 template <int TS>
 __host__ __device__ constexpr size_t dual_dag_bytes() {
     DD_CONSTS
-    return (size_t)DD_SLOTS * (9 * 4 + 5 * 8) + (size_t)DD_FRONT * 8 + (size_t)DD_ARCS * 4 + 256;
+    return (size_t)DD_SLOTS * (9 * 4 + 5 * 8) + (size_t)(DD_ROOTS + DD_SLOW) * 4 + (size_t)DD_ARCS * 4 + 256;
 }
 
 template <int TS>
@@ -2013,8 +2014,8 @@ __device__ __forceinline__ DualDag dual_dag_at(char *p) {
     d.ydeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // count,
     d.xdeg = (int32_t *)p;    p += 4 * DD_SLOTS;  // and how many are old E* arcs), or with a
                                                   // count of -1 their one new in-arc's tail
-    d.front = (int32_t *)p;   p += 4 * DD_FRONT;  // the changed targets' slots
-    d.slow = (int32_t *)p;    p += 4 * DD_FRONT;  // slot | memberships << 16 whose E* in-arcs are tested
+    d.front = (int32_t *)p;   p += 4 * DD_ROOTS;  // the changed targets' slots
+    d.slow = (int32_t *)p;    p += 4 * DD_SLOW;   // slot | memberships << 16 whose E* in-arcs are tested
     d.arcs = (int32_t *)p;                        // tail slot | head slot << 8 | kinds << 16
     d.harc = d.ybeg;
     d.hend = d.slow;
@@ -2082,7 +2083,7 @@ template <int TS>
 __device__ __forceinline__ void dd_push_slow(const DualDag &d, BlockShared &sh, const int32_t sl, const int32_t kinds) {
     DD_CONSTS
     const int32_t pos = atomicAdd(&sh.kpos, 1);
-    if (pos >= DD_FRONT) sh.ovf = 1;
+    if (pos >= DD_SLOW) sh.ovf = 1;
     else d.slow[pos] = sl | (kinds << 16);
 }
 
@@ -2223,7 +2224,7 @@ __device__ bool dual_pass(const UpdateJob &J, const int32_t s, const int32_t *__
         const int32_t slot = dd_slot<TS>(d, t);
         const int32_t v = atomicAdd(&sh.nk, 1);
         const int32_t pos = atomicAdd(&sh.next, 1);
-        if (slot < 0 || v >= DD_CAP || pos >= DD_FRONT) {
+        if (slot < 0 || v >= DD_CAP || pos >= DD_ROOTS) {
             sh.ovf = 1;
             continue;
         }
@@ -2801,7 +2802,7 @@ __device__ __forceinline__ void update_source(const UpdateJob &J, const int32_t 
     // window, 120 of 20 600 such sources fit with the 128-slot table), so
     // those skip the union walk; the new sub-DAG alone often fits
     const bool fits = nb < TS * 3 / 4;
-    const bool dual_fits = nb < TS * 3 / 8;
+    const bool dual_fits = nb < TS * 3 / 8;  // (DD_ROOTS)
     int32_t *const pred_row = J.g.pred + (size_t)s * n;
     const bool dual = dual_fits && dual_pass<TS>(J, s, Dg, Sg, J.g.xc_ptr, J.g.yc_ptr, J.g.yc_src, J.g.yc_w, Bt, Bd,
                                                  Bs, pred_row, nb, bc_delta, sh, es, dd);
