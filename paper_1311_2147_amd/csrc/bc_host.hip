@@ -546,7 +546,8 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part,
         else
             hipLaunchKernelGGL(k_prep, dim3(2 * g_elem + g_wave, L.njobs), dim3(256), 0, st, jobs, nj, g_elem);
     } else if (part == 1) {
-        hipLaunchKernelGGL(k_rows, dim3(ctx->rows_grid), dim3(256), 0, st, jobs, nj, ctx->big_b, pool);
+        hipLaunchKernelGGL(k_rows, dim3(ctx->rows_grid), dim3(256), 0, st, jobs, nj, ctx->big_b,
+                           L.may_defer ? std::min<int32_t>(ctx->big_b, SOON_NB) : ctx->big_b, pool);
     } else if (part == 2) {
         // the wide kernel (deferred sources) and the DAG kernel (listed
         // sources) touch disjoint rows and run side by side: the wide one

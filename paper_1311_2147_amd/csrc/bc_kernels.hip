@@ -2683,10 +2683,10 @@ __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_
 // graph went from 2.12 to 1.61 ms, 64 of an n = 4096 one from 15.4 to 13.5).  A source's changed targets are
 // collected in LDS; up to big_b of them are copied to the step's target pool
 // and the source is listed for the DAG kernel, more (or a full pool) defer
-// the source to the wide kernel, which scans the row again.  Nothing in D or
-// sigma is written here: the old partial dependency still needs the old row.
+// the source to the wide kernel, which scans the row again; so do more than
+// soon_b while few are (see SOON_NB).  Nothing in D or sigma is written here: the old partial dependency still needs the old row.
 __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
-                                              int32_t big_b, StepPool pool) {
+                                              int32_t big_b, int32_t soon_b, StepPool pool) {
     __shared__ int32_t lt[LCAP], ld[LCAP], lf[LCAP];
     __shared__ uint64_t ls[LCAP];
     __shared__ BlockShared sh;
@@ -2695,6 +2695,7 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
     const int njobs = *njobs_p;
     const BList L{lt, ld, ls, min(big_b, LCAP)};
     const int32_t grid = (int32_t)gridDim.x;
+    const int32_t soon_max = SOON_MAX / njobs;
     int32_t dealt = 0;  // sources dealt by the jobs before this one, modulo the grid
     for (int j = 0; j < njobs; ++j) {
         const UpdateJob &J = jobs[j];
@@ -2738,7 +2739,8 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
             if (nb == 0 && sh.nf <= LCAP) continue;
             if (tid == 0) {
                 long long off = -1;
-                if (nb <= L.cap && sh.nf <= LCAP) {
+                if (nb <= L.cap && sh.nf <= LCAP &&
+                    !(nb > soon_b && *(volatile int32_t *)&ctl->big_count < soon_max)) {
                     const unsigned long long o = atomicAdd(pool.next, (unsigned long long)nb);
                     if (o + (unsigned long long)nb <= (unsigned long long)pool.cap) off = (long long)o;
                 }

@@ -71,3 +71,25 @@ def test_dependency_in_lds_and_out_of_it(n):
     assert st["deferred_sources"] > 0
     check_sampled(gr, g, [7, 100, 101, 109, 0, n - 1], f"n={n}")
     ctx.close()
+
+
+@pytest.mark.parametrize("chain,leaves", [(200, 320), (100, 500), (330, 256), (330, 255)])
+def test_sources_deferred_before_the_threshold(chain, leaves):
+    """A chain into a hub: every source on it gets leaves + 1 changed targets, more than 256 and
+    fewer than big_b; of these at most about 128 go to the wide kernel, with the rest listed."""
+    n = chain + 1 + leaves
+    src = list(range(chain)) + [chain] * leaves
+    dst = list(range(1, chain + 1)) + list(range(chain + 1, n))
+    g = W.Graph(n, True, np.array(src, np.int32), np.array(dst, np.int32), np.full(len(src), 9, np.int64))
+    say(f"wide: {chain} sources with {leaves + 1} changed targets")
+    ctx = make_ctx(n, slots=16)
+    gr = ctx.load_graph(g)
+    for up in [W.Update("edge", u=chain - 1, v=chain, w=4),
+               W.Update("vertex", v=chain, edges=[(chain - 1, chain, 3), (chain, n - 1, 2)])]:
+        gr.update(up)
+        deferred = gr.stats()["deferred_sources"]
+        g = W.apply_update(g, up)
+        check_full(gr, g, f"{chain} {leaves}", dags=(0, chain - 1, chain))
+        if n > 512:
+            assert (0 < deferred <= chain) if leaves + 1 > 256 else deferred == 0
+    ctx.close()
