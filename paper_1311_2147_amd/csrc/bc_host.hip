@@ -539,12 +539,16 @@ bc_status launch_update_part(bc_ctx *ctx, int r, const LaunchShape &L, int part,
     hipStream_t st = ctx->stream;
     const int g_elem = (int)std::min<int64_t>(((int64_t)L.n_max + 255) / 256, 2048);
     const int g_wave = (int)std::min<int64_t>(((int64_t)L.n_max * 64 + 255) / 256, 4096);
+    // the merge's workgroups run beside the two other roles' and have a few arcs
+    // per thread: with one per 64 vertices (4096 a job at n = 16384) starting them
+    // was most of the launch (40 us of three jobs, 17.7 with 170 each)
+    const int g_merge = (int)std::min<int64_t>(g_wave, std::max(512 / L.njobs, 64));
     const StepPool pool = step_pool(ctx);
     if (part == 0) {
         if (one)
-            hipLaunchKernelGGL(k_prep_one, dim3(2 * g_elem + g_wave), dim3(256), 0, st, *one, jobs, nj, g_elem);
+            hipLaunchKernelGGL(k_prep_one, dim3(2 * g_elem + g_merge), dim3(256), 0, st, *one, jobs, nj, g_elem);
         else
-            hipLaunchKernelGGL(k_prep, dim3(2 * g_elem + g_wave, L.njobs), dim3(256), 0, st, jobs, nj, g_elem);
+            hipLaunchKernelGGL(k_prep, dim3(2 * g_elem + g_merge, L.njobs), dim3(256), 0, st, jobs, nj, g_elem);
     } else if (part == 1) {
         hipLaunchKernelGGL(k_rows, dim3(ctx->rows_grid), dim3(256), 0, st, jobs, nj, ctx->big_b,
                            L.may_defer ? std::min<int32_t>(ctx->big_b, SOON_NB) : ctx->big_b, pool);
