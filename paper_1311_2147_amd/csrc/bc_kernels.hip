@@ -2157,6 +2157,8 @@ __device__ __forceinline__ void dual_kahn(const DualDag &d, BlockShared &sh) {
     }
     __syncthreads();
     int32_t lo = 0, hi = sh.kpos;
+    // (every wave has read the end of the first round before one lists more)
+    __syncthreads();
     while (lo < hi) {
         for (int32_t idx = lo + tid; idx < hi; idx += bs) {
             int32_t x = d.klist[idx] & 0xff;
