@@ -1470,7 +1470,7 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
 // of E*, took 680 us at n = 32768, this takes 245 (half of it along the single
 // in-arcs, with the dependency in L2); at n = 8192 255 and 56.
 // Returns false, with nothing written but the slot's scratch, when the arcs
-// outgrow the record.
+// outgrow the record (or a sample says that they would).
 __device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow, const uint64_t *__restrict__ Srow,
                           const int32_t *__restrict__ cptr, const int32_t *__restrict__ csrc,
                           const int32_t *__restrict__ cw, const int32_t *__restrict__ Bt, const int32_t nB,
@@ -1512,27 +1512,20 @@ __device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow,
     }
     __syncthreads();
     const int32_t nmulti = sh.next;
-    for (int32_t c = 0; c < nmulti; c += bs) {
-        const int32_t idx = c + tid;
-        int32_t x = 0, b0 = 0, deg = 0, dx = 0;
-        if (idx < nmulti) {
-            x = u.sub[idx];
-            b0 = cptr[x];
-            deg = cptr[x + 1] - b0;
-            dx = Drow[x];
-        }
+    // the DAG in-arcs of one vertex per thread (-1: none), arc-parallel
+    auto dag_in_arcs = [&](const int32_t x, auto &&f) {
+        const int32_t b0 = x >= 0 ? cptr[x] : 0, deg = x >= 0 ? cptr[x + 1] - b0 : 0;
         int32_t total;
         const int32_t off = block_excl_scan(deg, sh.scan, total);
         es.off[tid] = off;
         es.vtx[tid] = x;
         es.beg[tid] = b0;
-        es.dx[tid] = dx;
+        es.dx[tid] = x >= 0 ? Drow[x] : 0;
         __syncthreads();
-        const int32_t nv = min(bs, nmulti - c);
         for (int32_t jb = tid * RU; jb < total; jb += bs * RU) {
             int32_t iv[RU], ev[RU], av[RU], wv[RU];
             bool ok[RU];
-            chunk_arcs(es, nv, total, jb, iv, ev, ok);
+            chunk_arcs(es, bs, total, jb, iv, ev, ok);
 #pragma unroll
             for (int k = 0; k < RU; ++k) {
                 av[k] = ok[k] ? csrc[ev[k]] : 0;
@@ -1542,17 +1535,31 @@ __device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow,
             for (int k = 0; k < RU; ++k) {
                 if (!ok[k]) continue;
                 const int32_t da = Drow[av[k]];
-                if (da == INF32 || (int64_t)da + wv[k] != (int64_t)es.dx[iv[k]]) continue;
-                const int32_t p = atomicAdd(&sh.nk, 1);
-                if (p < kcap) {
-                    const int32_t h = es.vtx[iv[k]];
-                    u.ka[p] = av[k];
-                    u.kb[p] = h;
-                    atomicAdd(&u.kcnt[h], 1);
-                }
+                if (da != INF32 && (int64_t)da + wv[k] == (int64_t)es.dx[iv[k]]) f(av[k], es.vtx[iv[k]]);
             }
         }
         __syncthreads();
+    };
+    // where E* has many arcs per vertex, a sample first: a record that these
+    // would overfill is not begun
+    if (cptr[n] > 4 * kcap && nmulti > bs) {
+        dag_in_arcs(u.sub[(int64_t)tid * nmulti / bs], [&](int32_t, int32_t) { atomicAdd(&sh.nk, 1); });
+        const bool over = (int64_t)sh.nk * nmulti > (int64_t)kcap * bs;
+        __syncthreads();
+        if (over) return false;
+        if (tid == 0) sh.nk = 0;
+        __syncthreads();
+    }
+    for (int32_t c = 0; c < nmulti; c += bs) {
+        dag_in_arcs(c + tid < nmulti ? u.sub[c + tid] : -1, [&](const int32_t a, const int32_t h) {
+            const int32_t p = atomicAdd(&sh.nk, 1);
+            if (p < kcap) {
+                u.ka[p] = a;
+                u.kb[p] = h;
+                atomicAdd(&u.kcnt[h], 1);
+            }
+        });
+        if (sh.nk > kcap) break;  // (nothing adds to it before the next chunk's barriers)
     }
     const int32_t nk = sh.nk;
     if (nk > kcap) {
@@ -3034,6 +3041,14 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         // B is, a walk 190 from 3000 changed targets and 500 from 10 000; at
         // n = 8192 (with the dependency in LDS too) 56 against 72 from 1400
         const bool full = (int64_t)nb * 8 >= (int64_t)n;
+        // where ties outgrow its record the other pass sweeps all of E* and tests
+        // it again: that pays only where B is half of the row or more.  Eight
+        // updates of 300 sources with 601, 1025 and 2501 changed targets of a row
+        // of 3901, 4325 and 5801, 22 DAG arcs per vertex, take 8.7, 9.3 and 11.0 ms;
+        // with the sweep from an eighth on and a record filled to the end 46.6,
+        // 49.2 and 56.0; with no whole-DAG pass below half of the row 14.7, 15.9
+        // and 19.8 (an earlier build)
+        const bool sweep = (int64_t)nb * 2 >= (int64_t)n;
         // where the passes use the staged row's LDS: full ones for the counts
         // and (past the expansion arrays) the dependency, walks for their
         // accumulation
@@ -3101,8 +3116,8 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
                           *const cb = ph ? J.g.yc_dst : J.g.xc_dst, *const cw = ph ? J.g.yc_w : J.g.xc_w;
             const double sign = ph ? 1.0 : -1.0;
             if (!full || !full_pass(s, n, Dr, Sr, cp, ca, cw, u.bl_t, nb, u, sign, J.g.bc_delta, Pr, sh, es, lcnt, lacc))
-                restricted_pass<false, 2, 4>(s, n, Dr, Sr, cp, ca, cb, cw, u.bl_t, nb, full, u, sign, J.g.bc_delta, Pr,
-                                             sh, es, dyn_lds, lds_bytes);
+                restricted_pass<false, 2, 4>(s, n, Dr, Sr, cp, ca, cb, cw, u.bl_t, nb, sweep, u, sign, J.g.bc_delta,
+                                             Pr, sh, es, dyn_lds, lds_bytes);
         }
     }
 }
