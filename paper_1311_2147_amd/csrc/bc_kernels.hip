@@ -1540,11 +1540,12 @@ __device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow,
         }
         __syncthreads();
     };
-    // where E* has many arcs per vertex, a sample first: a record that these
+    // where E* has many arcs per vertex, a sample first (a vertex for one thread in
+    // eight; one for each costs 7% where the record fits): a record that these
     // would overfill is not begun
     if (cptr[n] > 4 * kcap && nmulti > bs) {
-        dag_in_arcs(u.sub[(int64_t)tid * nmulti / bs], [&](int32_t, int32_t) { atomicAdd(&sh.nk, 1); });
-        const bool over = (int64_t)sh.nk * nmulti > (int64_t)kcap * bs;
+        dag_in_arcs(tid & 7 ? -1 : u.sub[(int64_t)tid * nmulti / bs], [&](int32_t, int32_t) { atomicAdd(&sh.nk, 1); });
+        const bool over = (int64_t)sh.nk * nmulti > (int64_t)kcap * (bs / 8);
         __syncthreads();
         if (over) return false;
         if (tid == 0) sh.nk = 0;
@@ -3044,7 +3045,7 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         // where ties outgrow its record the other pass sweeps all of E* and tests
         // it again: that pays only where B is half of the row or more.  Eight
         // updates of 300 sources with 601, 1025 and 2501 changed targets of a row
-        // of 3901, 4325 and 5801, 22 DAG arcs per vertex, take 8.7, 9.3 and 11.0 ms;
+        // of 3901, 4325 and 5801, 22 DAG arcs per vertex, take 7.8, 8.2 and 10.1 ms;
         // with the sweep from an eighth on and a record filled to the end 46.6,
         // 49.2 and 56.0; with no whole-DAG pass below half of the row 14.7, 15.9
         // and 19.8 (an earlier build)
