@@ -1056,8 +1056,8 @@ __device__ __forceinline__ void kahn_in_lds(const int32_t s, const int32_t nsub,
 //      sub-DAG vertex's successors inside the sub-DAG, or (full) one sweep
 //      over all of E* counting every reachable vertex's DAG successors, for
 //      large B where the sub-DAG is most of DAG(s) (vertices outside it get
-//      delta_B = 0 and change nothing); a full pass in a slot with an arc
-//      record also keeps the DAG(s) arcs it finds, grouped by head,
+//      delta_B = 0 and change nothing); with OUT_ROW, in a slot with an arc
+//      record, it also keeps the DAG(s) arcs it finds, grouped by head,
 //   2. Kahn from the sinks (a reverse topological order, which serves the
 //      accumulation, Section 2.1): each vertex pushes its term to its
 //      predecessors once all its successors have pushed to it, over the
@@ -1112,6 +1112,9 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
     __syncthreads();
     int32_t nsub;
     bool rec = false;  // Kahn walks recorded arcs
+    // a sweep records for the dependency row only: in an update it runs where the
+    // arcs have outgrown the record already (full_pass)
+    const bool sweep_rec = OUT_ROW && kcap > 0;
     if (full) {
         // 1. every DAG(s) arc: one more successor of its tail, and (with an
         //    arc record) the arc itself with one more arc into its head
@@ -1136,7 +1139,7 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
                 const int32_t da = Drow[av[k]];
                 if (da != INF32 && (int64_t)da + wv[k] == (int64_t)Drow[bv[k]]) {
                     atomicAdd(&u.outdeg[av[k]], 1);
-                    if (kcap > 0) {
+                    if (sweep_rec) {
                         const int32_t p = atomicAdd(&sh.nk, 1);
                         if (p < kcap) {
                             u.ka[p] = av[k];
@@ -1246,7 +1249,7 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
     }
     if (full) {
         const int32_t nk = sh.nk;
-        rec = kcap > 0 && nk <= kcap;
+        rec = sweep_rec && nk <= kcap;
         if (rec) {
             // group the arcs by head: each head with arcs gets a range
             // [kend - kcnt, kend); the scatter advances kend from its start
@@ -1273,7 +1276,7 @@ __device__ void restricted_pass(const int32_t s, const int32_t n, const int32_t 
                 for (int k = 0; k < LU; ++k)
                     if (hv[k] >= 0) u.kr[pos[k]] = tv[k];
             }
-        } else if (kcap > 0) {
+        } else if (sweep_rec) {
             // too many arcs to record: Kahn tests E*; undo the counts
             for (int32_t p = tid; p < kcap; p += bs) u.kcnt[u.kb[p]] = 0;
         }
