@@ -382,8 +382,8 @@ bc_status bc_reset_timing(bc_ctx *ctx);
  * BC.  A source whose changed-target set has more than big_b entries is
  * deferred to a second kernel with wider workgroups (wide_block threads),
  * which stages the source's distance row in LDS when wide_stage is set and the
- * row fits (n <= 36864); so are a few with more than 256, while that kernel
- * has CUs to spare.  Fields set to 0 keep their current value.
+ * row fits (n <= 36864); so are up to 128 of a step's sources with more than
+ * 256.  Fields set to 0 keep their current value.
  *   block:      threads per workgroup of the first kernel: 64, 128, 192, 256
  *   slots:      its persistent workgroups (at most bc_config.slots)
  *   big_b:      deferral threshold, 1..1024

@@ -33,16 +33,18 @@ constexpr int32_t W_COUNT = 0x0fffffff, W_B = 1 << 29, W_VIS = 1 << 30;
 // the per-source kernel to its wide-workgroup companion.
 constexpr int32_t BIG_B = 512;
 
-// Sources with more than SOON_NB changed targets are deferred too, up to
-// SOON_MAX of a step, in steps that have a wide kernel.  In the DAG kernel such a
-// source runs 250 to 900 us and is what a step waits for; a wide workgroup takes
-// a fifth of that, but a whole CU (the DAG kernel has five to ten sources in
-// flight there), hence the bound: both passes of 128 sources are a workgroup per
-// CU.  16 unit-weight insertions at n = 8191 take 13.9 ms with it and 15.6
-// without, 64 arc updates at n = 4096 9.05 and 9.45, a submitted batch at
-// n = 32768 35.0 and 35.5; a queue of three graphs is the same (10.87, 10.83).
-// From 128 changed targets: 13.4, 8.9, 35.2, and the queue is slower (10.87,
-// 10.77).
+// Sources with more than SOON_NB changed targets are deferred too, SOON_MAX of a
+// step at most (each takes a place from the step's counter), in steps that have a
+// wide kernel.  In the DAG kernel such a source runs 250 to 900 us and is what a
+// step waits for; a wide workgroup takes a fifth of that, but a whole CU (the DAG
+// kernel has five to ten sources in flight there), hence the bound: both passes of
+// 128 sources are a workgroup per CU.  16 unit-weight insertions at n = 8191 take
+// 13.9 ms with it and 15.6 without, 64 arc updates at n = 4096 9.05 and 9.45, a
+// submitted batch at n = 32768 35.0 and 35.5; a queue of three graphs is the same
+// (10.87, 10.83).  From 128 changed targets: 13.4, 8.9, 35.2, and the queue is
+// slower (10.87, 10.77).  With no bound in effect (a count read before the others
+// had added to it) eight updates that defer 300 sources of 400 to 440 targets each
+// took 17.5 to 23.6 ms, with it 15.4 to 17.5.
 constexpr int32_t SOON_NB = 256, SOON_MAX = 128;
 
 // Sticky status bits of a graph.
@@ -104,6 +106,7 @@ struct StepPool {
     unsigned long long *next;
     int32_t *src_next;   // listed sources handed out past the first per workgroup
     int32_t *wide_next;  // units of the wide kernel handed out past the first per workgroup
+    int32_t *soon;       // sources that asked for a place before the threshold (SOON_MAX)
     int64_t cap;
 };
 

@@ -324,6 +324,7 @@ StepPool step_pool(bc_ctx *ctx) {
     p.next = (unsigned long long *)(misc_dev(ctx) + 2048);
     p.src_next = (int32_t *)(misc_dev(ctx) + 2304);
     p.wide_next = (int32_t *)(misc_dev(ctx) + 2560);
+    p.soon = (int32_t *)(misc_dev(ctx) + 2816);
     return p;
 }
 int wide_slots_for(int slots) { return std::min(slots, WIDE_SLOTS_MAX); }

@@ -2697,7 +2697,7 @@ __device__ void rows_few_targets(const UpdateJob &J, const RowV &R, const int32_
 // collected in LDS; up to big_b of them are copied to the step's target pool
 // and the source is listed for the DAG kernel, more (or a full pool) defer
 // the source to the wide kernel, which scans the row again; so do more than
-// soon_b while few are (see SOON_NB).  Nothing in D or sigma is written here: the old partial dependency still needs the old row.
+// soon_b while the step has places for them (see SOON_NB).  Nothing in D or sigma is written here: the old partial dependency still needs the old row.
 __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs, const int32_t *__restrict__ njobs_p,
                                               int32_t big_b, int32_t soon_b, StepPool pool) {
     __shared__ int32_t lt[LCAP], ld[LCAP], lf[LCAP];
@@ -2708,7 +2708,6 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
     const int njobs = *njobs_p;
     const BList L{lt, ld, ls, min(big_b, LCAP)};
     const int32_t grid = (int32_t)gridDim.x;
-    const int32_t soon_max = SOON_MAX / njobs;
     int32_t dealt = 0;  // sources dealt by the jobs before this one, modulo the grid
     for (int j = 0; j < njobs; ++j) {
         const UpdateJob &J = jobs[j];
@@ -2752,8 +2751,7 @@ __global__ void __launch_bounds__(256) k_rows(const UpdateJob *__restrict__ jobs
             if (nb == 0 && sh.nf <= LCAP) continue;
             if (tid == 0) {
                 long long off = -1;
-                if (nb <= L.cap && sh.nf <= LCAP &&
-                    !(nb > soon_b && *(volatile int32_t *)&ctl->big_count < soon_max)) {
+                if (nb <= L.cap && sh.nf <= LCAP && !(nb > soon_b && atomicAdd(pool.soon, 1) < SOON_MAX)) {
                     const unsigned long long o = atomicAdd(pool.next, (unsigned long long)nb);
                     if (o + (unsigned long long)nb <= (unsigned long long)pool.cap) off = (long long)o;
                 }
@@ -3048,7 +3046,7 @@ __global__ void __launch_bounds__(1024) k_source_wide(const UpdateJob *__restric
         // where ties outgrow its record the other pass sweeps all of E* and tests
         // it again: that pays only where B is half of the row or more.  Eight
         // updates of 300 sources with 601, 1025 and 2501 changed targets of a row
-        // of 3901, 4325 and 5801, 22 DAG arcs per vertex, take 7.8, 8.2 and 10.1 ms;
+        // of 3901, 4325 and 5801, 22 DAG arcs per vertex, take 7.7, 8.2 and 10.1 ms;
         // with the sweep from an eighth on and a record filled to the end 46.6,
         // 49.2 and 56.0; with no whole-DAG pass below half of the row 14.7, 15.9
         // and 19.8 (an earlier build)
@@ -3242,6 +3240,7 @@ __device__ __forceinline__ void commit_job(const UpdateJob &J, const StepPool &p
         *pool.next = 0;
         *pool.src_next = 0;
         *pool.wide_next = 0;
+        *pool.soon = 0;
     }
 }
 
