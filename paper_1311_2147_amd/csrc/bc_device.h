@@ -107,6 +107,7 @@ struct StepPool {
     int32_t *src_next;   // listed sources handed out past the first per workgroup
     int32_t *wide_next;  // units of the wide kernel handed out past the first per workgroup
     int32_t *soon;       // sources that asked for a place before the threshold (SOON_MAX)
+    int32_t *errors;     // set by a step that ends with a sticky error of any of its graphs
     int64_t cap;
 };
 

@@ -231,7 +231,8 @@ struct bc_ctx {
     int rows_grid = 1024;       // workgroups of the row kernel (all resident)
     int32_t n_layout = 1;  // slot layout size: the largest graph ever loaded
     int32_t zero_layout = 0;  // the layout whose slots were last cleared (zero_slots)
-    bool rezero = false;      // a graph has reported an error since
+    bool rezero = false;      // they may hold something since: an error was read, or a static pass broke off
+    bool steps_unread = false;  // update steps have run since their error word was read
     bool full_search = false;  // BC_FLAG_FULL_SEARCH: the static pass relaxes every arc
     bool check = false;        // BC_FLAG_CHECK: state check after every load, recompute and step
     // schedules chosen by the autotuner per size bucket (ceil(log2 n) of a
@@ -325,6 +326,7 @@ StepPool step_pool(bc_ctx *ctx) {
     p.src_next = (int32_t *)(misc_dev(ctx) + 2304);
     p.wide_next = (int32_t *)(misc_dev(ctx) + 2560);
     p.soon = (int32_t *)(misc_dev(ctx) + 2816);
+    p.errors = p.soon + 1;
     return p;
 }
 int wide_slots_for(int slots) { return std::min(slots, WIDE_SLOTS_MAX); }
@@ -736,6 +738,7 @@ bc_status run_step(bc_ctx *ctx, const std::vector<UpdateJob> &jobs, bool use_gra
     int r;
     if ((st = ring_acquire(ctx, &r))) return st;
     if (se) HIPCHK(hipEventRecord(se->begin, ctx->stream));
+    ctx->steps_unread = true;
     const UpdateJob *one = !use_graph && jobs.size() == 1 ? jobs.data() : nullptr;
     if (!one && (st = ring_stage(ctx, r, jobs))) return st;
     const bool timed = ctx->timing;
@@ -1206,6 +1209,7 @@ bc_status run_check(bc_ctx *ctx, GraphRec *g, const Mirror &arcs, bool all, int3
     HIPCHK(hipMemcpyAsync(status, &g->P.ctl->status, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
     // the host arrays above are read by the copies: finish before they go
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (*status) ctx->rezero = true;
     if (*status & ST_CHECK) {
         char msg[160];
         snprintf(msg, sizeof msg, "state check failed: %s at (%d, %d), %llu condition(s) false", check_kind_name(rec.kind),
@@ -1231,30 +1235,30 @@ bc_status check_step(bc_ctx *ctx, const std::vector<UpdateJob> &jobs) {
     return BC_OK;
 }
 
-// Static pass on the GPU from the mirror's arcs: distances, E*, counts,
-// dependencies and BC (Alg 7 with the DAG taken from E*, Alg 6 steps 2-8).
-// The distance search relaxes a set of arcs that contains E*; every
-// shortest path lies in E* and any such set gives the same distances, DAGs,
-// counts and BC (Section 6):
-//   over_estar: the maintained E* (a graph without sticky errors);
-//   a dense graph (checked search): the k lightest out-arcs of every vertex
-//     first; then one pass over all arcs lists those with w(a,b) <= d_H(a,b)
-//     for the distances d_H of the searched set H; the listed arcs H lacks
-//     join it and the search runs again, until none is missing, when d_H is
-//     the distance matrix and H contains E* (see k_search_check).  On
-//     complete graphs with random weights E* has about n ln n arcs
-//     (Section 1), so H stays a small fraction of the n^2 arcs;
-//   otherwise (sparse graphs, or BC_FLAG_FULL_SEARCH): every arc.
-// The kernels keep the flags and sums of every work slot at zero between
-// uses.  The slots are cleared only when their layout has changed (n_layout
-// has grown, so they may hold another layout's lists) or a graph has reported
-// an error: clearing them twice per static pass took 0.8 ms at n = 16384.
+// The kernels keep the flags and sums of every work slot at zero between uses,
+// also where a graph is halted (whole sources are skipped then, never broken
+// off).  As a second line the slots are cleared by a static pass whose layout is
+// another than theirs (n_layout has grown, so they may hold another layout's
+// lists), after any graph's error, read by the host or not (an update step that
+// ends with one sets the step pool's error word), and after a static pass that
+// broke off.  Clearing them twice per static pass took 0.8 ms at n = 16384; the
+// word is read only where steps have run since.
 bc_status zero_slots(bc_ctx *ctx) {
-    if (ctx->zero_layout == ctx->n_layout && !ctx->rezero) return BC_OK;
-    const ScratchPlan sp = plan_scratch(ctx, ctx->n_layout);
-    HIPCHK(hipMemsetAsync(sp.src_base, 0, (size_t)sp.src * sp.src_bytes + (size_t)sp.wide * sp.wide_bytes, ctx->stream));
-    ctx->zero_layout = ctx->n_layout;
-    ctx->rezero = false;
+    const StepPool pool = step_pool(ctx);
+    if (ctx->steps_unread) {
+        int32_t errors = 0;
+        HIPCHK(hipMemcpyAsync(&errors, pool.errors, 4, hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        if (errors) ctx->rezero = true;
+        ctx->steps_unread = false;
+    }
+    if (ctx->zero_layout != ctx->n_layout || ctx->rezero) {
+        const ScratchPlan sp = plan_scratch(ctx, ctx->n_layout);
+        HIPCHK(hipMemsetAsync(sp.src_base, 0, (size_t)sp.src * sp.src_bytes + (size_t)sp.wide * sp.wide_bytes, ctx->stream));
+        HIPCHK(hipMemsetAsync(pool.errors, 0, 4, ctx->stream));
+        ctx->zero_layout = ctx->n_layout;
+    }
+    ctx->rezero = true;  // until the static pass that starts here has ended well
     return BC_OK;
 }
 
@@ -1302,6 +1306,20 @@ void launch_static(bc_ctx *ctx, const GraphPtrs &P, int slots, const LaunchShape
         hipLaunchKernelGGL(k_static<ST_GLOBAL>, grid, blk, lds, ctx->stream, P, L.src_base, L.slot_bytes, lhist, L.n_layout);
 }
 
+// Static pass on the GPU from the mirror's arcs: distances, E*, counts,
+// dependencies and BC (Alg 7 with the DAG taken from E*, Alg 6 steps 2-8).
+// The distance search relaxes a set of arcs that contains E*; every
+// shortest path lies in E* and any such set gives the same distances, DAGs,
+// counts and BC (Section 6):
+//   over_estar: the maintained E* (a graph without sticky errors);
+//   a dense graph (checked search): the k lightest out-arcs of every vertex
+//     first; then one pass over all arcs lists those with w(a,b) <= d_H(a,b)
+//     for the distances d_H of the searched set H; the listed arcs H lacks
+//     join it and the search runs again, until none is missing, when d_H is
+//     the distance matrix and H contains E* (see k_search_check).  On
+//     complete graphs with random weights E* has about n ln n arcs
+//     (Section 1), so H stays a small fraction of the n^2 arcs;
+//   otherwise (sparse graphs, or BC_FLAG_FULL_SEARCH): every arc.
 bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     const int32_t n = g->n;
     ArcCsr estar;
@@ -1407,6 +1425,7 @@ bc_status static_pass(bc_ctx *ctx, GraphRec *g, bool over_estar = false) {
     int32_t status = 0;
     if ((st = read_status(ctx, g, &status))) return st;
     if (status) return fail(ctx, sticky_to_status(status), "static pass failed");
+    ctx->rezero = false;
     if (ctx->check) {
         g->dev = g->mirror;
         return run_check(ctx, g, g->dev, true, &status);
@@ -1960,7 +1979,7 @@ bc_status bc_load_graph(bc_ctx *ctx, int32_t n, int64_t m, const int32_t *src, c
     g->P = carve((char *)arena, n, arc_capacity, estar_capacity, &total, &g->chk);
     g->P.directed = g->directed;
     g->live = true;
-    ctx->n_layout = std::max(ctx->n_layout, n);  // the static pass below re-zeroes every slot
+    ctx->n_layout = std::max(ctx->n_layout, n);  // (the static pass below clears the slots if it grew)
     ctx->graphs.push_back(g);
     ctx->in_use += arena_bytes;
     *out = (bc_graph_id)(ctx->graphs.size() - 1);

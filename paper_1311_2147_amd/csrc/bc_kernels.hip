@@ -3241,6 +3241,7 @@ __device__ __forceinline__ void commit_job(const UpdateJob &J, const StepPool &p
         *pool.src_next = 0;
         *pool.wide_next = 0;
         *pool.soon = 0;
+        if (*(volatile int32_t *)&c->status) *pool.errors = 1;
     }
 }
 
