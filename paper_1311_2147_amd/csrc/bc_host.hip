@@ -365,8 +365,6 @@ ScratchPlan plan_scratch(bc_ctx *ctx, int32_t n) {
     return p;
 }
 
-int lds_cap_for(int32_t n_max) { return std::min<int32_t>(n_max, LDS_ROW_MAX); }
-
 // Dynamic LDS of the per-source kernels: staged row, XB bytes per thread of
 // expansion arrays, and the LDS sub-DAG tables of `table` slots (0: none; the
 // wide kernel and the dependency-row kernel use none).
@@ -1165,9 +1163,6 @@ int64_t add_missing(int32_t n, ArcCsr &set, const std::vector<int32_t> &a, const
 int32_t search_k(int32_t n) { return (int32_t)std::ceil(2.0 * std::log((double)std::max(n, 2))) + 4; }
 bool use_checked_search(int32_t n, int64_t m) { return m >= 4 * (int64_t)search_k(n) * n; }
 
-// Static pass: all-pairs distances, path counts, E* and BC from scratch
-// (Alg 7 with the DAG taken from E*, Alg 6 steps 2-8).
-//
 const char *check_kind_name(int32_t k) {
     switch (k) {
         case CK_SOURCE: return "source entry";

@@ -2969,7 +2969,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))
     }
 }
 
-// Wide kernel (persistent, runs after the DAG kernel): the deferred sources,
+// Wide kernel (persistent, beside the DAG kernel): the deferred sources,
 // one workgroup of up to 1024 threads per unit of work.  The first
 // item_regions deferred sources (over the jobs in order) run as two units on
 // two workgroups at once: the old pass (it also stores the changed pairs in
