@@ -627,7 +627,8 @@ __global__ void __launch_bounds__(256) k_es_scatter(const UpdateJob *__restrict_
 // then every kept arc and every head's segment start is placed directly
 // (k_es_place; the masks' popcounts are summed by each of its workgroups for
 // itself, or scanned before by one workgroup per job where an E* may hold more
-// than ES_LONG arcs: 16 bytes of masks per thread and workgroup).
+// than ES_LONG arcs: at that size the last workgroups read 128 KiB of masks, 512
+// bytes per thread).
 __device__ __forceinline__ uint64_t *es_mask(const UpdateJob &J) { return (uint64_t *)J.g.x_src; }
 __device__ __forceinline__ int32_t *es_wpre(const UpdateJob &J) { return J.g.x_dst; }
 
@@ -3253,8 +3254,10 @@ __global__ void __launch_bounds__(256) k_commit(const UpdateJob *__restrict__ jo
 // ------------------------------------------------------------ static pass --
 
 // Distances from every source: a near/far search with the row in LDS
-// (Dijkstra's order up to a width `delta` in distance; positive weights make
-// any order converge to d(s,.)).  A vertex whose distance has fallen since its
+// (Dijkstra's order up to a width `delta` in distance, as in the delta-stepping
+// of Meyer and Sanders, 2003, with one near and one far set as in Davidson,
+// Baxter, Garland and Owens, 2014; positive weights make any order converge to
+// d(s,.)).  A vertex whose distance has fallen since its
 // out-arcs were last relaxed has its bit set; a round relaxes the out-arcs of
 // the marked vertices below a bound, and when none is left the bound moves to
 // the nearest marked vertex plus delta.  With delta three quarters of the mean
@@ -3843,7 +3846,9 @@ __device__ void static_source(const GraphPtrs &G, const int32_t s, const int32_t
         static_dense<MODE>(G, s, m, ROW ? row : Dg, VAL ? row + n : sl.lev, sl, pred, Srow, sh);
         return;
     }
-    // 2. levels
+    // 2. levels (rounds until none changes; with as many levels as vertices that
+    // costs about what a frontier per level does: a recomputation of a chain of
+    // 16384 vertices takes 2.15 s against 2.41, of 20000 4.2 against 3.8)
     int32_t *const lev = ROW ? row : sl.lev;
     if (ROW) {
         for (int32_t i = tid; i < n; i += bs) lev[i] = 0;
