@@ -1546,10 +1546,12 @@ __device__ bool full_pass(const int32_t s, const int32_t n, const int32_t *Drow,
     };
     // where E* has many arcs per vertex, a sample first (a vertex for one thread in
     // eight; one for each costs 7% where the record fits): a record that these
-    // would overfill is not begun
+    // would overfill is not begun, nor, below half of the row, one that they would
+    // nearly fill (8 updates, 100 sources, 6001 changed targets of a row of 26101,
+    // a record filled to the brim: 11.2 ms with it, 6.5 to 7.4 without)
     if (cptr[n] > 4 * kcap && nmulti > bs) {
         dag_in_arcs(tid & 7 ? -1 : u.sub[(int64_t)tid * nmulti / bs], [&](int32_t, int32_t) { atomicAdd(&sh.nk, 1); });
-        const bool over = (int64_t)sh.nk * nmulti > (int64_t)kcap * (bs / 8);
+        const bool over = (int64_t)sh.nk * nmulti > (int64_t)(2 * (int64_t)nB >= n ? kcap : kcap / 4 * 3) * (bs / 8);
         __syncthreads();
         if (over) return false;
         if (tid == 0) sh.nk = 0;
