@@ -2369,6 +2369,8 @@ bc_status bc_get_arcs(bc_ctx *ctx, bc_graph_id gid, int32_t *src, int32_t *dst, 
     GraphRec *g = get_graph(ctx, gid);
     if (!g || !cnt || cap < 0) return fail(ctx, BC_ERR_INVALID_ARG, "bad arguments");
     const Mirror &M = g->mirror;
+    *cnt = g->directed ? M.arcs : M.arcs / 2;
+    if (cap == 0) return BC_OK;
     // the CSR in tail order with the new weights merged in, then the arcs
     // inserted since its last rebuild (sorted); an undirected edge once, from its
     // smaller endpoint
@@ -2395,7 +2397,6 @@ bc_status bc_get_arcs(bc_ctx *ctx, bc_graph_id gid, int32_t *src, int32_t *dst, 
         }
     }
     for (auto &e : extra) emit((int32_t)(e.first / (uint64_t)g->n), (int32_t)(e.first % (uint64_t)g->n), e.second);
-    *cnt = k;
     return BC_OK;
 }
 
